@@ -915,13 +915,15 @@ extern "C" ctaug_status ctaug_gaussian_smooth(const ctaug_vol *in, ctaug_vol *ou
         return CTAUG_ESHAPE;
     if (!sigma)
         return CTAUG_EINVAL;
+    int32_t R[3];
     int active[3], m = 0;
     for (int k = 0; k < 3; ++k) {
         if (!std::isfinite(sigma[k]) || sigma[k] < 0.0f)
             return CTAUG_EINVAL;
-        if (gauss_radius(sigma[k]) > kMaxGaussRadius)
+        R[k] = gauss_radius(sigma[k]);
+        if (R[k] > kMaxGaussRadius)
             return CTAUG_EINVAL;
-        if (gauss_radius(sigma[k]) > 0)
+        if (R[k] > 0)
             active[m++] = k;
     }
     const int64_t n = nelem(in->dim);
@@ -940,6 +942,8 @@ extern "C" ctaug_status ctaug_gaussian_smooth(const ctaug_vol *in, ctaug_vol *ou
     if (m == 0)                            // no smoothing: a converting copy
         return hip_status(launch_smooth_axis(in->data, in->dtype == CTAUG_I16, dst, d, 2,
                                              gauss_taps(0.0f), s));
+    if (smooth_fused_ok(R, d))
+        return hip_status(launch_smooth_fused(in->data, in->dtype == CTAUG_I16, dst, d, sigma, s));
     // ping-pong so that the last pass writes `out`
     const void *src = in->data;
     bool src_i16 = in->dtype == CTAUG_I16;
