@@ -203,18 +203,11 @@ void set_tiles(FwdJob &J, const Tiling &TL)
     J.tiles_x = (J.ox + (1 << TL.lx) - 1) >> TL.lx;
     J.tiles_y = (J.oy + (1 << TL.ly) - 1) >> TL.ly;
     J.tiles_z = (J.oz + (1 << TL.lz) - 1) >> TL.lz;
+    J.rcp_ty = rcp_u32((uint32_t)J.tiles_y);
+    J.rcp_tz = rcp_u32((uint32_t)J.tiles_z);
     J.sub[0] = TL.lx;
     J.sub[1] = TL.ly;
     J.sub[2] = TL.lz;
-}
-
-// Stage each tile of J in sub-tiles whose footprint fits `cells` LDS cells.
-void set_subtiles(FwdJob &J, const Tiling &TL, int32_t cells)
-{
-    const Tiling SL = choose_subtile(J, TL, cells);
-    J.sub[0] = SL.lx;
-    J.sub[1] = SL.ly;
-    J.sub[2] = SL.lz;
 }
 
 // Validate the arguments of one forward warp and build its descriptor.
@@ -1071,17 +1064,24 @@ ctaug_status apply_tiling(ctaug_batch_plan *p, const ctaug_tuning &t)
         cells = lds_cells_for(kDispLdsCells, 4);
     } else if (t.lds_cells == 0) {
         // the largest footprint of the current jobs, with headroom for later
-        // updates; tiles that still exceed it take the direct-gather path
+        // updates, up to kAffineLdsCells unless a job needs more; tiles that
+        // still exceed it are staged as sub-tiles
         int64_t need = 0;
         for (int i = 0; i < p->n; ++i)
             need = std::max<int64_t>(need, footprint_cells_bound(p->jobs[i], TL));
-        cells = lds_cells_for((int32_t)std::min<int64_t>(need + need / 4 + 64, 1 << 20),
-                              p->elem_bytes);
+        need = std::min<int64_t>(need + need / 4 + 64, 1 << 20);
+        cells = lds_cells_for((int32_t)need, p->elem_bytes);
+        const int32_t few = kAffineLdsCells * 4 / p->elem_bytes;
+        bool fits = true;
+        for (int i = 0; i < p->n; ++i)
+            fits = choose_subtile(p->jobs[i], TL, few) && fits;
+        if (fits)
+            cells = std::min(cells, few);
     } else if (cells > lds_cells_cap(p->elem_bytes)) {
         return CTAUG_EINVAL;
     }
     for (int i = 0; i < p->n; ++i)
-        set_subtiles(p->jobs[i], TL, cells);
+        (void)choose_subtile(p->jobs[i], TL, cells);
     if (p->upload_recorded && hipEventSynchronize(p->upload_done) != hipSuccess)
         return CTAUG_EHIP;
     std::memcpy(p->staging, p->jobs.data(), sizeof(FwdJob) * p->n);
@@ -1429,7 +1429,7 @@ ctaug_status prepare_jobs(const ctaug_batch_plan *p, const ctaug_job *jobs,
     for (int i = 0; i < p->n; ++i) {
         if (p->elem_bytes == 2)
             next[i].flags |= kFlagLds16;
-        set_subtiles(next[i], p->TL, p->lds_cells);
+        (void)choose_subtile(next[i], p->TL, p->lds_cells);
     }
     return CTAUG_OK;
 }
@@ -1643,9 +1643,11 @@ extern "C" ctaug_status ctaug_batch_plan_autotune(ctaug_batch_plan *p, const cta
     st = apply_tiling(p, cand[best_i]);
     if (st != CTAUG_OK)
         return st;
-    cache_put(tune_key(p->arch, p->num_cu, p->jobs, p->spline), cand[best_i]);
+    // the choice as the plan now holds it (a reservation of 0 cells, sized from the
+    // jobs, by its size), so that the cache, *best and the plan agree
+    cache_put(tune_key(p->arch, p->num_cu, p->jobs, p->spline), p->tune);
     if (best)
-        *best = cand[best_i];
+        *best = p->tune;
     return CTAUG_OK;
 }
 

@@ -98,8 +98,33 @@ struct FwdJob {
     float occ_lo, occ_hi;              // occluded output slab occ_lo <= z <= occ_hi
     uint32_t vol_id, key0, key1;
     int32_t tiles_x, tiles_y, tiles_z; // tile grid of this job's output
+    uint32_t rcp_ty, rcp_tz;           // floor(2^32 / tiles_y), floor(2^32 / tiles_z) (rcp_u32)
     int32_t sub[3];                    // log2 extents of the sub-tiles a tile is staged in
+    // Footprint window of a sub-tile (forward affine warps): the coordinate of
+    // axis i over the sub-tile lies in [q0 + box_dn, q0 + box_up] (q0 at its
+    // first voxel, FP32 rounding included), and its cells in box_e[i] cells from
+    // floor(q0 + box_dn).  box_e[0] = 0: no window fits, gathers from memory.
+    float box_dn[3], box_up[3];
+    int32_t box_e[3];
+    int32_t box_pitch;                 // LDS cells per row: lds_pitch(box_e[2])
+    // A sub-tile's samples use the quad of 4 cells centred at c only if
+    // |inv (c - q_mid)| <= reach per axis: inv = A^-1, q_mid the coordinate at the
+    // sub-tile's centre, q0 + box_mid.
+    float inv[9], reach[3], box_mid[3];
 };
+
+// floor(t / d) from r = rcp_u32(d) = min(floor(2^32 / d), 2^32 - 1): the estimate
+// is at most one too small.  Scalar for uniform operands (no division).
+__host__ __device__ __forceinline__ uint32_t rcp_u32(uint32_t d)
+{
+    return d <= 1 ? 0xffffffffu : (uint32_t)(0x100000000ull / d);
+}
+__device__ __forceinline__ uint32_t div_rcp(uint32_t t, uint32_t d, uint32_t r)
+{
+    uint32_t q = (uint32_t)(((uint64_t)t * r) >> 32);
+    q += (t - q * d) >= d ? 1u : 0u;
+    return q;
+}
 
 // Launch shape: tile extents as log2 (voxels), z extent >= 4.
 struct Tiling {
@@ -180,6 +205,23 @@ template <> struct Elem<int16_t> {
 __device__ __forceinline__ int8_t load_i8(rsrc_t r, uint32_t off)
 {
     return (int8_t)__builtin_amdgcn_raw_buffer_load_b8(r, off, 0, 0);
+}
+
+// floor(q) as an integer in one instruction (the compiler emits a floor and a
+// conversion).
+__device__ __forceinline__ int32_t flr_i32(float q)
+{
+    int32_t r;
+    asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(r) : "v"(q));
+    return r;
+}
+
+// a s + c modulo 2^32 from the low 24 bits of a and the scalar s (signed).
+__device__ __forceinline__ int32_t mad_i24(int32_t a, int32_t s, int32_t c)
+{
+    int32_t r;
+    asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "s"(s), "v"(c));
+    return r;
 }
 
 // 24-bit multiply (full rate); operands and product must stay below 2^24 / 2^32.
@@ -307,7 +349,7 @@ __device__ __forceinline__ float sample_checked(const Src &S, float qx, float qy
 }
 
 // Nearest label: j = floorf(q + 0.5f) per axis (FP32, ties up).
-__device__ __forceinline__ int32_t nn_index(float q) { return (int32_t)floorf(q + 0.5f); }
+__device__ __forceinline__ int32_t nn_index(float q) { return flr_i32(q + 0.5f); }
 
 __device__ __forceinline__ int8_t label_checked(const Src &S, float qx, float qy, float qz,
                                                 int8_t label_fill)
@@ -319,6 +361,18 @@ __device__ __forceinline__ int8_t label_checked(const Src &S, float qx, float qy
     const int8_t l = load_i8(S.lbl, elem_index(S, min(max(jx, 0), S.nx - 1),
                                                min(max(jy, 0), S.ny - 1),
                                                min(max(jz, 0), S.nz - 1)));
+    return ok ? l : label_fill;
+}
+
+// The same for coordinates already moved into [-2, n], whose nearest voxel is
+// outside the volume wherever the guard fails.
+__device__ __forceinline__ int8_t label_clamped(const Src &S, float qx, float qy, float qz,
+                                                int8_t label_fill)
+{
+    const int32_t jx = nn_index(qx), jy = nn_index(qy), jz = nn_index(qz);
+    const bool ok = (uint32_t)jx < (uint32_t)S.nx && (uint32_t)jy < (uint32_t)S.ny &&
+                    (uint32_t)jz < (uint32_t)S.nz;
+    const int8_t l = load_i8(S.lbl, ok ? elem_index(S, jx, jy, jz) : 0u);
     return ok ? l : label_fill;
 }
 
@@ -361,9 +415,11 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c[4], uint32_t k0, uint32
     }
 }
 
+// ((w >> 9) + 0.5) 2^-23 from the bits: 0x7f : w shifted right by 9 is the float
+// 1 + (w >> 9) 2^-23; taking off 1 - 2^-24 is exact.
 __device__ __forceinline__ float uniform01(uint32_t w)
 {
-    return ((float)(w >> 9) + 0.5f) * 0x1p-23f;
+    return __uint_as_float(__builtin_amdgcn_alignbit(0x7fu, w, 9)) - 0x1.fffffep-1f;
 }
 
 // (r cos theta, r sin theta) with r = sqrt(-2 ln U(wr)), theta = 2 pi U(wt),
@@ -437,8 +493,8 @@ __device__ __forceinline__ float photometric(const Photo &P, float V, float n)
     if (P.flags & kFlagWindow) {
         float t = (v - P.win_lo) * P.inv_range;
         t = fminf(fmaxf(t, 0.0f), 1.0f);
-        if (P.flags & kFlagGamma)
-            t = t > 0.0f ? __builtin_amdgcn_exp2f(P.gamma * __builtin_amdgcn_logf(t)) : 0.0f;
+        if (P.flags & kFlagGamma)      // t = 0: exp2(gamma * -inf) = 0, as gamma > 0
+            t = __builtin_amdgcn_exp2f(P.gamma * __builtin_amdgcn_logf(t));
         v = t;
     }
     return v;

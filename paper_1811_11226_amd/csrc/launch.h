@@ -20,6 +20,12 @@ enum : int { kBatchMixed = 0, kBatchI16F32 = 1, kBatchI16I16 = 2, kBatchF32 = 3,
 // reservation, since the footprint has no a-priori bound.
 constexpr Tiling kDispTiling = {3, 3, 4};
 constexpr int32_t kDispLdsCells = 10224;
+// Affine warps: reservations that a caller does not size stop here, so that four
+// workgroups share a CU (40 KB each) and tiles past it are staged as sub-tiles.
+// With up to 15352 cells (60 KB, two workgroups) a 512 x 512 x 320 scan took 441
+// us against 420, a batch of five odd volumes 126 against 91 (7152 and 8176 cells:
+// 436 us, 91).
+constexpr int32_t kAffineLdsCells = 10208;
 hipError_t launch_warp_batch(const FwdJob *jobs_dev, const int32_t *prefix_dev, int32_t njobs,
                              int32_t total_tiles, int32_t grid, const Tiling &TL,
                              int32_t lds_cells, int32_t elem_bytes, int mode, bool aligned,
@@ -31,7 +37,7 @@ int32_t footprint_cells_bound(const FwdJob &J, const Tiling &TL);
 int32_t lds_cells_cap(int32_t elem_bytes);
 int32_t lds_cells_for(int32_t bound, int32_t elem_bytes);
 size_t lds_bytes_for(int32_t cells, int32_t elem_bytes);
-Tiling choose_subtile(const FwdJob &J, const Tiling &TL, int32_t lds_cells);
+bool choose_subtile(FwdJob &J, const Tiling &TL, int32_t lds_cells);
 hipError_t launch_photometric(float *data, int64_t n, int64_t nz, const Photo &P, float occ_lo,
                               float occ_hi, uint32_t vol, uint32_t k0, uint32_t k1, bool vec,
                               hipStream_t s);

@@ -149,9 +149,20 @@ template <> struct QuadRaw<float> {
     {
         return __builtin_amdgcn_raw_buffer_load_b128(r, e * 4u, 0, 0);
     }
+    // at byte offset off + base (base uniform)
+    static __device__ __forceinline__ type load_at(rsrc_t r, uint32_t off, uint32_t base)
+    {
+        return __builtin_amdgcn_raw_buffer_load_b128(r, off, base, 0);
+    }
     static __device__ __forceinline__ void store(type w, float *dst)
     {
         *reinterpret_cast<u32x4 *>(dst) = w;
+    }
+    static __device__ __forceinline__ void cells(type w, float (&c)[4])
+    {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            c[u] = __uint_as_float(w[u]);
     }
 };
 template <> struct QuadRaw<int16_t> {
@@ -159,6 +170,17 @@ template <> struct QuadRaw<int16_t> {
     static __device__ __forceinline__ type load(rsrc_t r, uint32_t e)
     {
         return __builtin_amdgcn_raw_buffer_load_b64(r, e * 2u, 0, 0);
+    }
+    static __device__ __forceinline__ type load_at(rsrc_t r, uint32_t off, uint32_t base)
+    {
+        return __builtin_amdgcn_raw_buffer_load_b64(r, off, base, 0);
+    }
+    template <typename LT> static __device__ __forceinline__ void cells(type w, LT (&c)[4])
+    {
+        c[0] = (LT)(int16_t)(w.x & 0xffffu);
+        c[1] = (LT)(int16_t)(w.x >> 16);
+        c[2] = (LT)(int16_t)(w.y & 0xffffu);
+        c[3] = (LT)(int16_t)(w.y >> 16);
     }
     static __device__ __forceinline__ void store(type w, int16_t *dst)
     {
@@ -273,7 +295,7 @@ struct RowWalk {
 // converts and writes them.  Other footprints test each row and quad: rows
 // outside the volume are filled without loads, quads crossing its z ends
 // load per cell from clamped indices.
-template <typename T, typename LT>
+template <typename T, typename LT, int NT = kThreads>
 __device__ __forceinline__ void stage_footprint(const FwdJob &J, const Src &S, const TileGeom &G,
                                                 LT *s_img)
 {
@@ -284,12 +306,12 @@ __device__ __forceinline__ void stage_footprint(const FwdJob &J, const Src &S, c
         // last whole row stay idle (ql = qpr)
         lpr = qpr;
         row0 = div_small(threadIdx.x, qpr, 1.0f / (float)qpr);
-        rpp = kThreads / qpr;
+        rpp = NT / qpr;
         ql = row0 < rpp ? threadIdx.x - row0 * qpr : qpr;
     } else {
         lpr = 16;
         row0 = threadIdx.x >> 4;
-        rpp = kThreads >> 4;
+        rpp = NT >> 4;
         ql = threadIdx.x & 15;
     }
     RowWalk W;

@@ -7,13 +7,16 @@
 // coordinate, a trilinear gather of the image and a nearest-neighbour gather
 // of the labels, then gain/offset, noise, window and gamma in registers.
 //
-// Each tile is classified once (uniformly for the workgroup) from the
-// coordinates of its eight corners, widened by a bound on FP32 rounding:
+// Each sub-tile is classified once (uniformly for the workgroup) from the
+// bounds of its coordinates, widened by a bound on FP32 rounding:
 //   outside  -- every sample fails the (-1, n) guard: fill / label_fill only;
 //   interior -- every cell floor(q)..floor(q)+1 is inside the volume: no
-//               per-corner bounds checks;
-//   boundary -- per-sample guard and per-corner fill substitution.
-// The three paths compute identical values where they overlap.
+//               bounds checks;
+//   boundary -- the footprint staged with fill outside the volume, coordinates
+//               clamped to it (guard_coord).
+// Footprints that fit no reservation are gathered from memory, with
+// per-sample guard and per-corner fill.  All paths compute identical values
+// where they overlap.
 //
 // Workgroup-to-tile mapping is XCD-aware (xcd_tile): consecutive workgroup
 // ids are dispatched round-robin over the 8 XCDs, and tiles are dealt to the
@@ -28,121 +31,198 @@
 
 namespace ctaug {
 
+// Workgroup size: affine tiles, displacement tiles (one run per thread).
+constexpr int kAffineThreads = 256;
+template <int DISP> constexpr int kFwdThreads = DISP == kDispNone ? kAffineThreads : kThreads;
+
 enum : int { kPathOutside, kPathLdsInterior, kPathLdsBoundary, kPathDirectInterior,
              kPathDirectBoundary };
 
 // Sample coordinates of one thread's run, computed once by a displacement
-// tile (which needs them to bound its footprint) and reused for sampling.
+// tile (which needs them to bound its footprint) and reused for sampling;
+// already through guard_coord.
 struct RunQ {
     float q[3][4];
 };
 
-// All runs of one tile along one sampling path.  Each thread owns runs of 4
-// consecutive output voxels along z.  With a displacement (DISP) the tile has
-// exactly one run per thread and its coordinates come precomputed in Q.
-template <typename T, typename LT, int PATH, bool ALIGNED, bool LBL, int DISP>
-__device__ __forceinline__ void run_tile(const FwdJob &J, const TileGeom &G, const Tiling &SL,
-                                         const LT *s_img, const RunQ &Q)
+// A box of output voxels and its input footprint in LDS, uniform over the
+// workgroup: voxels from (x0, y0, z0) up to (x1, y1, z1) inclusive; input cell
+// (i, j, k) at byte c0 + i sx + j sy + k sizeof(cell) of the LDS (modulo 2^32).
+struct Box {
+    int x0, y0, z0, x1, y1, z1;
+    int sx, sy, c0;
+};
+
+// A coordinate moved into [-2, n] without changing its sample: at or below -1
+// (and NaN) it goes to -2, at or above n to n.  There every corner is outside the volume,
+// so the trilinear value is fill and the nearest voxel is outside, which is what
+// the guard (-1, n) gives; a footprint of cells within [-2, n + 2), fill where
+// outside the volume, then needs no test per sample.
+__device__ __forceinline__ float guard_coord(float q, float n)
 {
+    return fminf(q > -1.0f ? q : -2.0f, n);
+}
+
+// A job in constant memory (kernel arguments or the batch's table, which no
+// kernel writes): its fields are scalar loads.  reload() hides the pointer's
+// origin, so that a phase's fields are loaded anew there rather than kept in
+// scalar registers through the phases before it (all of them together spill).
+typedef __attribute__((address_space(4))) const FwdJob *JobPtr;
+__device__ __forceinline__ JobPtr reload(JobPtr p)
+{
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
+// All runs of one box along one sampling path (uniform).  Each thread owns runs
+// of 4 consecutive output voxels along z.  With a displacement (DISP) the box
+// has exactly one run per thread and its coordinates come precomputed in Q.
+//
+// What bounds the affine warps is shared between the vector memory path (lines of
+// footprint and labels fetched through L1: without the staging loads the
+// 16-volume batch takes 170 us of 241, without the label gathers 198, without the
+// stores 198) and VALU issue (57 % busy; 158 instructions per voxel before,
+// 134 now), so the per-voxel chain is kept short: floor and fraction are one instruction each where q >= 0 (v_cvt_flr_i32_f32,
+// v_fract_f32 equals q - floor(q) there), the LDS byte address three (24-bit
+// multiply-adds on strides that are the job's, one origin per box), and the
+// samples of a boundary box cost the same as an interior one's plus the clamp
+// above (fill cells are staged).
+template <typename T, typename LT, bool ALIGNED, int DISP>
+__device__ __forceinline__ void run_box(JobPtr Jp, const Box &B, int path, const Tiling &SL,
+                                        const uint8_t *s_lds, const RunQ &Q)
+{
+    const FwdJob &J = *(const FwdJob *)reload(Jp);
     const Src S = make_src<T>(J);
     gmut<float> *out = gm<float>(J.out);
     gmut<int8_t> *lout = gm<int8_t>(J.lout);
     Photo P = photo_of(J);
     const int runs_z_log = SL.lz - 2;
     const int nruns = 1 << (SL.lx + SL.ly + runs_z_log);
-    const int pitch = G.pitch, sxy = G.e[1] * G.pitch;
-    // LDS cell index of input cell i: (i - lo) . (sxy, pitch, 1), evaluated in
-    // FP32 (full-rate FMA) on integer values below 2^24, hence exactly
-    const float lo_f[3] = {(float)G.lo[0], (float)G.lo[1], (float)G.lo[2]};
-    const float sxy_f = (float)sxy, pitch_f = (float)pitch;
     const int8_t lfill = (int8_t)J.label_fill;
+    const bool labels = (J.flags & kFlagLabels) != 0;
 
-    for (int r = threadIdx.x; r < nruns; r += kThreads) {
+    for (int r = threadIdx.x; r < nruns; r += kFwdThreads<DISP>) {
         if (DISP != kDispNone && r != (int)threadIdx.x)
             break;
         const int zr = r & ((1 << runs_z_log) - 1);
         const int rr = r >> runs_z_log;
-        const int y = G.y0 + (rr & ((1 << SL.ly) - 1));
-        const int x = G.x0 + (rr >> SL.ly);
-        const int z = G.z0 + 4 * zr;
-        if (x > G.x1 || y > G.y1 || z > G.z1)
+        const int y = B.y0 + (rr & ((1 << SL.ly) - 1));
+        const int x = B.x0 + (rr >> SL.ly);
+        const int z = B.z0 + 4 * zr;
+        if (x > B.x1 || y > B.y1 || z > B.z1)
             continue;
-        // The flags are re-read each iteration so that the compiler tests their
-        // bits in SALU where they are used instead of keeping one 64-bit lane
-        // mask per flag live across the loop (scalar register pressure).
-        uint32_t fl = J.flags;
-        asm volatile("" : "+s"(fl));
-        constexpr bool labels = LBL;      // a template parameter: the 4 voxels of a
-                                          // run stay one basic block
-        const bool vec = (fl & kFlagVec) != 0;
-        P.flags = fl;
         const int nvalid = ALIGNED ? 4 : min(4, J.oz - z);
         const uint32_t v0 = (uint32_t)((x * J.oy + y) * J.oz + z);
-        float rb[3];
-        row_base(J.M, (float)x, (float)y, rb);
-
         float V[4];
         int8_t L[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             V[k] = J.fill;
             L[k] = lfill;
-            if (PATH == kPathOutside || (!ALIGNED && k >= nvalid))
-                continue;
-            const float zf = (float)(z + k);
-            float qx = coord(J.M, 0, rb, zf), qy = coord(J.M, 1, rb, zf),
-                  qz = coord(J.M, 2, rb, zf);
-            if (DISP != kDispNone) {
-                qx = Q.q[0][k];
-                qy = Q.q[1][k];
-                qz = Q.q[2][k];
+        }
+        float q[4][3];
+        if (DISP == kDispNone) {
+            float rb[3];
+            row_base(J.M, (float)x, (float)y, rb);
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int i = 0; i < 3; ++i)
+                    q[k][i] = coord(J.M, i, rb, (float)(z + k));
+        } else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int i = 0; i < 3; ++i)
+                    q[k][i] = Q.q[i][k];
+        }
+        // the 8 corners of a cell whose LDS byte address is a
+        auto cell = [&](int32_t ix, int32_t iy, int32_t iz, float tx, float ty, float tz) {
+            int32_t a = iz * (int)sizeof(LT) + B.c0;
+            a = mad_i24(iy, B.sy, a);
+            a = mad_i24(ix, B.sx, a);
+            const LT *c00 = reinterpret_cast<const LT *>(s_lds + a);
+            const LT *c01 = reinterpret_cast<const LT *>(s_lds + (a + B.sy));
+            const LT *c10 = reinterpret_cast<const LT *>(s_lds + (a + B.sx));
+            const LT *c11 = reinterpret_cast<const LT *>(s_lds + (a + B.sx + B.sy));
+            const float kk[8] = {(float)c00[0], (float)c00[1], (float)c01[0], (float)c01[1],
+                                 (float)c10[0], (float)c10[1], (float)c11[0], (float)c11[1]};
+            return tri(kk, tx, ty, tz);
+        };
+        if (DISP == kDispNone && path == kPathLdsInterior) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (ALIGNED || k < nvalid)
+                    V[k] = cell(flr_i32(q[k][0]), flr_i32(q[k][1]), flr_i32(q[k][2]),
+                                __builtin_amdgcn_fractf(q[k][0]),
+                                __builtin_amdgcn_fractf(q[k][1]),
+                                __builtin_amdgcn_fractf(q[k][2]));
+                if (k == 1)
+                    __builtin_amdgcn_sched_barrier(0);     // two voxels' corners at a time
             }
-            if (PATH == kPathLdsInterior || PATH == kPathLdsBoundary) {
-                // A boundary tile samples without branches: a sample outside the
-                // guard is moved to the footprint's first cell pair (lo .. lo + 1
-                // on each axis, inside every footprint of a box that is not
-                // outside, as box_geom and geom_from_cells make e >= 2), and its
-                // results are replaced by fill / label_fill below.
-                // labels straight from global memory: an interior tile's
-                // nearest voxel is inside the volume
-                if (labels)
-                    L[k] = PATH == kPathLdsInterior ? label_interior(S, qx, qy, qz)
-                                                    : label_checked(S, qx, qy, qz, lfill);
-                bool guarded = true;
-                if (PATH == kPathLdsBoundary) {
-                    guarded = in_guard(qx, qy, qz, J.nx, J.ny, J.nz);
-                    qx = guarded ? qx : lo_f[0] + 0.25f;
-                    qy = guarded ? qy : lo_f[1] + 0.25f;
-                    qz = guarded ? qz : lo_f[2] + 0.25f;
+            if (labels)                // an interior box's nearest voxels are inside
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (ALIGNED || k < nvalid)
+                        L[k] = label_interior(S, q[k][0], q[k][1], q[k][2]);
+        } else if (path == kPathLdsBoundary) {
+            if (DISP == kDispNone) {
+                const float nf[3] = {(float)J.nx, (float)J.ny, (float)J.nz};
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+#pragma unroll
+                    for (int i = 0; i < 3; ++i)
+                        q[k][i] = guard_coord(q[k][i], nf[i]);
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (ALIGNED || k < nvalid) {
+                    const float fx = floorf(q[k][0]), fy = floorf(q[k][1]), fz = floorf(q[k][2]);
+                    V[k] = cell((int)fx, (int)fy, (int)fz, q[k][0] - fx, q[k][1] - fy,
+                                q[k][2] - fz);
                 }
-                const float fx = floorf(qx), fy = floorf(qy), fz = floorf(qz);
-                const int base = (int)__builtin_fmaf(
-                    fx - lo_f[0], sxy_f, __builtin_fmaf(fy - lo_f[1], pitch_f, fz - lo_f[2]));
-                float kk[8];
-                kk[0] = (float)s_img[base];
-                kk[1] = (float)s_img[base + 1];
-                kk[2] = (float)s_img[base + pitch];
-                kk[3] = (float)s_img[base + pitch + 1];
-                kk[4] = (float)s_img[base + sxy];
-                kk[5] = (float)s_img[base + sxy + 1];
-                kk[6] = (float)s_img[base + sxy + pitch];
-                kk[7] = (float)s_img[base + sxy + pitch + 1];
-                V[k] = tri(kk, qx - fx, qy - fy, qz - fz);
-                if (PATH == kPathLdsBoundary)
-                    V[k] = guarded ? V[k] : J.fill;
-            } else {
-                if (PATH == kPathDirectInterior) {
-                    V[k] = sample_interior<T>(S, qx, qy, qz);
-                    if (labels)
-                        L[k] = label_interior(S, qx, qy, qz);
-                } else {
-                    V[k] = sample_checked<T>(S, qx, qy, qz, J.fill);
-                    if (labels)
-                        L[k] = label_checked(S, qx, qy, qz, lfill);
+                if (k & 1)
+                    __builtin_amdgcn_sched_barrier(0);
+            }
+            if (labels)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    if (ALIGNED || k < nvalid)
+                        L[k] = label_clamped(S, q[k][0], q[k][1], q[k][2], lfill);
+                    if (k == 1)
+                        __builtin_amdgcn_sched_barrier(0);
                 }
+        } else if (DISP == kDispNone && path == kPathDirectInterior) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (ALIGNED || k < nvalid)
+                    V[k] = sample_interior<T>(S, q[k][0], q[k][1], q[k][2]);
+                if (k == 1)
+                    __builtin_amdgcn_sched_barrier(0);
+            }
+            if (labels)
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (ALIGNED || k < nvalid)
+                        L[k] = label_interior(S, q[k][0], q[k][1], q[k][2]);
+        } else if (path == kPathDirectBoundary) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (ALIGNED || k < nvalid) {
+                    V[k] = sample_checked<T>(S, q[k][0], q[k][1], q[k][2], J.fill);
+                    if (labels)
+                        L[k] = label_checked(S, q[k][0], q[k][1], q[k][2], lfill);
+                }
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
 
+        // The flags are re-read each iteration so that the compiler tests their
+        // bits in SALU where they are used instead of keeping one 64-bit lane
+        // mask per flag live across the loop (scalar register pressure).
+        uint32_t fl = J.flags;
+        asm volatile("" : "+s"(fl));
+        P.flags = fl;
         if (fl & kFlagOcclude) {
             // I_occ: the occluded output slab is 0 in place of the warped image
 #pragma unroll
@@ -166,7 +246,7 @@ __device__ __forceinline__ void run_tile(const FwdJob &J, const TileGeom &G, con
                 V[k] = photometric(P, V[k], n[k]);
         }
 
-        if (ALIGNED && vec) {
+        if (ALIGNED && (fl & kFlagVec)) {
             *reinterpret_cast<gmut<f32x4> *>(out + v0) = f32x4{V[0], V[1], V[2], V[3]};
             if (labels) {
                 const uint32_t packed = (uint32_t)(uint8_t)L[0] | ((uint32_t)(uint8_t)L[1] << 8) |
@@ -186,156 +266,389 @@ __device__ __forceinline__ void run_tile(const FwdJob &J, const TileGeom &G, con
     }
 }
 
-// ALIGNED: the output z extent is a multiple of 4, so every run is one noise
-// group and (with 16-byte aligned outputs) one vector store.  LT: type of the
-// LDS footprint cells (FP32, or int16 for int16 inputs: half the LDS, twice
-// the LDS reads).
-template <typename T, typename LT, bool ALIGNED, bool LBL, int DISP>
-__device__ __forceinline__ void fwd_box_l(const FwdJob &J, const TileGeom &G, const Tiling &SL,
-                                         uint8_t *s_lds, int32_t lds_cells, const RunQ &Q)
-{
-    LT *s_img = reinterpret_cast<LT *>(s_lds);
-    if (G.cls == kOutside) {
-        run_tile<T, LT, kPathOutside, ALIGNED, LBL, DISP>(J, G, SL, s_img, Q);
-    } else if (G.lds) {
-        stage_footprint<T, LT>(J, make_src<T>(J), G, s_img);
-        __syncthreads();
-        if (G.cls == kInterior)
-            run_tile<T, LT, kPathLdsInterior, ALIGNED, LBL, DISP>(J, G, SL, s_img, Q);
-        else
-            run_tile<T, LT, kPathLdsBoundary, ALIGNED, LBL, DISP>(J, G, SL, s_img, Q);
-        __syncthreads();               // LDS is reused by the next box
-    } else if (G.cls == kInterior) {
-        run_tile<T, LT, kPathDirectInterior, ALIGNED, LBL, DISP>(J, G, SL, s_img, Q);
-    } else {
-        run_tile<T, LT, kPathDirectBoundary, ALIGNED, LBL, DISP>(J, G, SL, s_img, Q);
-    }
-}
-
+// Displacement tile (ALIGNED, LT: see fwd_tile_affine).  A displacement has no
+// a-priori footprint bound: the tile (one run of 4 z voxels per thread)
+// computes its coordinates once, reduces their cells, and stages that
+// footprint when it fits the reservation.
 template <typename T, typename LT, bool ALIGNED, int DISP>
-__device__ __forceinline__ void fwd_box(const FwdJob &J, const TileGeom &G, const Tiling &SL,
-                                       uint8_t *s_lds, int32_t lds_cells, const RunQ &Q)
+__device__ __forceinline__ void fwd_tile_disp(JobPtr Jp, const Box &B0, const Tiling &TL,
+                                              int32_t lds_cells, uint8_t *s_lds)
 {
-    if (J.flags & kFlagLabels)
-        fwd_box_l<T, LT, ALIGNED, true, DISP>(J, G, SL, s_lds, lds_cells, Q);
-    else
-        fwd_box_l<T, LT, ALIGNED, false, DISP>(J, G, SL, s_lds, lds_cells, Q);
-}
-
-// One output tile, processed as sub-tiles of the job's sub-tile shape (the
-// whole tile unless its input footprint would not fit the LDS reservation).
-// ALIGNED: the output z extent is a multiple of 4, so every run is one noise
-// group and (with 16-byte aligned outputs) one vector store.  LT: type of the
-// LDS footprint cells (FP32, or int16 for int16 inputs: half the LDS, twice
-// the LDS reads).
-template <typename T, typename LT, bool ALIGNED, int DISP>
-__device__ __forceinline__ void fwd_tile_lt(const FwdJob &J, int t, const Tiling &TL,
-                                            int32_t lds_cells, uint8_t *s_lds)
-{
-    const int tz = t % J.tiles_z;
-    const int rest = t / J.tiles_z;
-    const int ty = rest % J.tiles_y;
-    const int tx = rest / J.tiles_y;
-    const int x0 = tx << TL.lx, y0 = ty << TL.ly, z0 = tz << TL.lz;
-    const int x1 = min(x0 + (1 << TL.lx), J.ox) - 1;
-    const int y1 = min(y0 + (1 << TL.ly), J.oy) - 1;
-    const int z1 = min(z0 + (1 << TL.lz), J.oz) - 1;
-    const Tiling SL = {J.sub[0], J.sub[1], J.sub[2]};
-    if (DISP != kDispNone) {
-        // A displacement has no a-priori footprint bound: the tile (one run of
-        // 4 z voxels per thread) computes its coordinates once, reduces floor(q)
-        // over its guarded samples, and stages that footprint when it fits the
-        // reservation.
-        __shared__ int s_red[kThreads / 64][6];
-        const int zr = threadIdx.x & ((1 << (TL.lz - 2)) - 1);
-        const int rr = threadIdx.x >> (TL.lz - 2);
-        const int x = x0 + (rr >> TL.ly), y = y0 + (rr & ((1 << TL.ly) - 1)), z = z0 + 4 * zr;
-        const bool mine = x <= x1 && y <= y1 && z <= z1;
-        const int nvalid = min(4, J.oz - z);
-        float u[3][4];
-        if (DISP == kDispSpline)
-            spline_tile_u<kThreads>(J.ctrl, J.bs, TL.lx, TL.ly, x0, y0, z0, x1, y1, z1, rr, x, y,
-                                    z, 1, nvalid, mine, reinterpret_cast<float *>(s_lds), u);
-        RunQ Q;
-        int fmn[3] = {INT_MAX, INT_MAX, INT_MAX}, fmx[3] = {INT_MIN, INT_MIN, INT_MIN};
-        if (mine) {
-            gconst<float> *disp = gc<float>(J.disp);
-            const int32_t nvox = J.ox * J.oy * J.oz;
-            const int32_t v0 = (x * J.oy + y) * J.oz + z;
-            const bool any_in = J.nx > 0 && J.ny > 0 && J.nz > 0;
-            float rb[3];
-            row_base(J.M, (float)x, (float)y, rb);
+    const FwdJob &J = *(const FwdJob *)reload(Jp);
+    Box B = B0;
+    __shared__ int s_red[kThreads / 64][6];
+    const int zr = threadIdx.x & ((1 << (TL.lz - 2)) - 1);
+    const int rr = threadIdx.x >> (TL.lz - 2);
+    const int x = B.x0 + (rr >> TL.ly), y = B.y0 + (rr & ((1 << TL.ly) - 1)), z = B.z0 + 4 * zr;
+    const bool mine = x <= B.x1 && y <= B.y1 && z <= B.z1;
+    const int nvalid = min(4, J.oz - z);
+    float u[3][4];
+    if (DISP == kDispSpline)
+        spline_tile_u<kThreads>(J.ctrl, J.bs, TL.lx, TL.ly, B.x0, B.y0, B.z0, B.x1, B.y1, B.z1, rr,
+                                x, y, z, 1, nvalid, mine, reinterpret_cast<float *>(s_lds), u);
+    const float nf[3] = {(float)J.nx, (float)J.ny, (float)J.nz};
+    RunQ Q;
+    int fmn[3] = {INT_MAX, INT_MAX, INT_MAX}, fmx[3] = {INT_MIN, INT_MIN, INT_MIN};
+    if (mine) {
+        gconst<float> *disp = gc<float>(J.disp);
+        const int32_t nvox = J.ox * J.oy * J.oz;
+        const int32_t v0 = (x * J.oy + y) * J.oz + z;
+        float rb[3];
+        row_base(J.M, (float)x, (float)y, rb);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                if (k >= nvalid)
-                    break;
-                const float zf = (float)(z + k);
+        for (int k = 0; k < 4; ++k) {
+            if (k >= nvalid)
+                break;
+            const float zf = (float)(z + k);
 #pragma unroll
-                for (int i = 0; i < 3; ++i)
-                    Q.q[i][k] = coord(J.M, i, rb, zf) +
-                                (DISP == kDispField ? disp[i * nvox + v0 + k] : u[i][k]);
-                if (!any_in || !in_guard(Q.q[0][k], Q.q[1][k], Q.q[2][k], J.nx, J.ny, J.nz))
-                    continue;
-#pragma unroll
-                for (int i = 0; i < 3; ++i) {
-                    const int f = (int)floorf(Q.q[i][k]);
-                    fmn[i] = min(fmn[i], f);
-                    fmx[i] = max(fmx[i], f);
-                }
+            for (int i = 0; i < 3; ++i) {
+                Q.q[i][k] = guard_coord(
+                    coord(J.M, i, rb, zf) +
+                        (DISP == kDispField ? disp[i * nvox + v0 + k] : u[i][k]),
+                    nf[i]);
+                const int f = flr_i32(Q.q[i][k]);
+                fmn[i] = min(fmn[i], f);
+                fmx[i] = max(fmx[i], f);
             }
         }
-        block_minmax3(fmn, fmx, s_red);
-        TileGeom G = geom_from_cells(J, x0, y0, z0, x1, y1, z1, fmn, fmx, lds_cells);
-        if (G.lds && (J.flags & kFlagLds16) && !(J.flags & kFlagFillInT))
-            G.lds = false;             // an int16 footprint must hold fill exactly
-        fwd_box<T, LT, ALIGNED, DISP>(J, G, TL, s_lds, lds_cells, Q);
+    }
+    block_minmax3(fmn, fmx, s_red);
+    // the footprint: cells fmn .. fmx + 1 per axis, within [-2, n + 2)
+    TileGeom G;
+    int64_t cells = 1;
+    bool outside = J.nx == 0 || J.ny == 0 || J.nz == 0;
+    const int n[3] = {J.nx, J.ny, J.nz};
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        G.lo[i] = __builtin_amdgcn_readfirstlane(fmn[i]);
+        G.e[i] = __builtin_amdgcn_readfirstlane(fmx[i]) - G.lo[i] + 2;
+        outside = outside || G.lo[i] >= n[i] || G.lo[i] + G.e[i] <= 0;
+        if (i == 2) {
+            G.quads = (G.e[2] + 3) >> 2;
+            G.pitch = lds_pitch(G.e[2]);
+        }
+        cells *= i == 2 ? G.pitch : G.e[i];
+    }
+    G.cls = kBoundary;
+    int path = outside ? kPathOutside : kPathDirectBoundary;
+    if (!outside && cells <= lds_cells && (sizeof(LT) == 4 || (J.flags & kFlagFillInT))) {
+        path = kPathLdsBoundary;
+        stage_footprint<T, LT>(J, make_src<T>(J), G, reinterpret_cast<LT *>(s_lds));
+        B.sy = G.pitch * (int)sizeof(LT);
+        B.sx = G.e[1] * B.sy;
+        B.c0 = -(G.lo[0] * B.sx + G.lo[1] * B.sy + G.lo[2] * (int)sizeof(LT));
+        __syncthreads();
+    }
+    run_box<T, LT, ALIGNED, DISP>(Jp, B, path, TL, s_lds, Q);
+    __syncthreads();                   // LDS is reused by the next tile
+}
+
+// The quads (4 cells of a row) of a footprint window that this thread copies: quad
+// ql of rows row0, row0 + rpp, ... (mine of them), (cx, cy) the plane and row of the
+// first within the window.  The windows of a job's sub-tiles have the same
+// extents, so this is laid out once per tile.
+constexpr int kStageChunk = 4;
+struct StageWalk {
+    int row0, ql, cx, cy, mine;
+    int rpp, step_x, step_y, passes;   // uniform; rpp = step_x ey + step_y
+};
+
+__device__ __forceinline__ StageWalk stage_walk(int rows, int ey, int quads)
+{
+    StageWalk W;
+    W.row0 = W.ql = W.cx = W.cy = W.mine = W.step_x = W.step_y = 0;
+    W.passes = 0;
+    W.rpp = __builtin_amdgcn_readfirstlane(div_small(kAffineThreads, quads, 1.0f / (float)quads));
+    if (W.rpp == 0)
+        return W;
+    W.passes = __builtin_amdgcn_readfirstlane(
+        div_small(rows + W.rpp - 1, W.rpp, 1.0f / (float)W.rpp));
+    W.row0 = div_small(threadIdx.x, quads, 1.0f / (float)quads);
+    W.ql = threadIdx.x - W.row0 * quads;
+    const float rcp_y = 1.0f / (float)ey;
+    W.step_x = __builtin_amdgcn_readfirstlane(div_small(W.rpp, ey, rcp_y));
+    W.step_y = W.rpp - W.step_x * ey;
+    W.cx = div_small(W.row0, ey, rcp_y);
+    W.cy = W.row0 - W.cx * ey;
+    W.mine = W.row0 < W.rpp ? (W.row0 + (W.passes - 1) * W.rpp < rows ? W.passes : W.passes - 1)
+                            : 0;
+    return W;
+}
+
+// Four raw cells c loaded from z = zc of a row, of which the quad's cell u is
+// c[s + u] (fill where s + u is not 0 .. 3, or ok is false), written as LDS cells.
+template <typename LT>
+__device__ __forceinline__ void store_shifted(const LT (&c)[4], int s, bool ok, LT fill, LT *dst)
+{
+    LT v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        v[u] = fill;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            v[u] = s + u == j ? c[j] : v[u];
+        v[u] = ok ? v[u] : fill;
+    }
+    store4(dst, v);
+}
+
+// Copies a window into LDS, kStageChunk loads of a thread in flight at once (12
+// took as long: lines fetched count, not round trips, and the registers cost a
+// wave per SIMD).  Quads that no sample of the box can use are not loaded
+// (FwdJob::reach; their cells are never read): a rotated box fills about half of
+// its window.  That took the 16-volume batch from 250 to 237 us.
+// inside: the window (whole quads) lies in the volume.  Otherwise each quad is
+// loaded from the nearest place inside the volume (of at least 4 cells along
+// z), and its cells outside the volume become fill as they are written.
+template <typename T, typename LT>
+__device__ __forceinline__ void stage_window(const FwdJob &J, const Src &S, const StageWalk &W,
+                                             const int (&lo)[3], const float (&g)[3], int ey,
+                                             int pitch, bool inside, uint8_t *s_lds)
+{
+    constexpr int N = kStageChunk;
+    const float zq = (float)(4 * W.ql) + 1.5f;
+    const float gz[3] = {__builtin_fmaf(J.inv[2], zq, g[0]), __builtin_fmaf(J.inv[5], zq, g[1]),
+                         __builtin_fmaf(J.inv[8], zq, g[2])};
+    // whether a sample of the box can use the quad at row (cx, cy) of the window
+    auto reach = [&](int cx, int cy) {
+        const float fx = (float)cx, fy = (float)cy;
+        bool r = true;
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            r = r && fabsf(__builtin_fmaf(J.inv[3 * k], fx,
+                                          __builtin_fmaf(J.inv[3 * k + 1], fy, gz[k]))) <=
+                         J.reach[k];
+        return r;
+    };
+    constexpr uint32_t kNowhere = 0xffffffffu;     // past the buffer's end: no access, reads 0
+    typename QuadRaw<T>::type w[N];
+    uint32_t l = (uint32_t)(W.row0 * pitch + 4 * W.ql) * (uint32_t)sizeof(LT);
+    const uint32_t step = (uint32_t)(W.rpp * pitch) * (uint32_t)sizeof(LT);
+    int cx = W.cx, cy = W.cy;
+    if (inside) {
+        const int plane = S.ry * S.rsy;                    // elements
+        const uint32_t base = (uint32_t)(lo[0] * plane + lo[1] * S.rsy + lo[2]) *
+                              (uint32_t)sizeof(T);
+        uint32_t o = (uint32_t)(W.cx * plane + cy * S.rsy + 4 * W.ql) * (uint32_t)sizeof(T);
+        const uint32_t d = (uint32_t)(W.step_x * plane + W.step_y * S.rsy) * (uint32_t)sizeof(T);
+        const uint32_t dw = (uint32_t)(plane - ey * S.rsy) * (uint32_t)sizeof(T) + d;
+        for (int p0 = 0; p0 < W.passes; p0 += N) {
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+                w[u] = QuadRaw<T>::load_at(S.img, p0 + u < W.mine && reach(cx, cy) ? o : kNowhere,
+                                           base);
+                const int c = cy + W.step_y;
+                o += c >= ey ? dw : d;
+                cx += c >= ey ? W.step_x + 1 : W.step_x;
+                cy = c >= ey ? c - ey : c;
+            }
+#pragma unroll
+            for (int u = 0; u < N; ++u)
+                if (p0 + u < W.mine)
+                    QuadRaw<T>::store(w[u], reinterpret_cast<LT *>(s_lds + (l + u * step)));
+            l += N * step;
+        }
         return;
     }
-    const RunQ Q0{};
-    const int nz = ((z1 - z0) >> SL.lz) + 1, ny = ((y1 - y0) >> SL.ly) + 1,
-              nx = ((x1 - x0) >> SL.lx) + 1;
-    const int nsub = nx * ny * nz;     // sub-boxes, x-major
-    auto geom = [&](int i) {
-        const int iz = i % nz, r = i / nz, iy = r % ny, ix = r / ny;
-        const int sx = x0 + (ix << SL.lx), sy = y0 + (iy << SL.ly), sz = z0 + (iz << SL.lz);
-        return box_geom(J, sx, sy, sz, min(sx + (1 << SL.lx) - 1, x1),
-                        min(sy + (1 << SL.ly) - 1, y1), min(sz + (1 << SL.lz) - 1, z1),
-                        lds_cells);
-    };
-    // the geometry of every sub-box at once, sub-box i in lane i of each wave
-    // (one dependent chain per tile instead of one per box), read per box;
-    // choose_subtile keeps a tile at no more than 16 sub-boxes
-    __builtin_assume(nsub <= 64);
-    const TileGeom Gl = geom(min((int)(threadIdx.x & 63), nsub - 1));
-    for (int i = 0; i < nsub; ++i) {
-        TileGeom G;
-        G.x0 = __builtin_amdgcn_readlane(Gl.x0, i);
-        G.y0 = __builtin_amdgcn_readlane(Gl.y0, i);
-        G.z0 = __builtin_amdgcn_readlane(Gl.z0, i);
-        G.x1 = __builtin_amdgcn_readlane(Gl.x1, i);
-        G.y1 = __builtin_amdgcn_readlane(Gl.y1, i);
-        G.z1 = __builtin_amdgcn_readlane(Gl.z1, i);
-        G.cls = __builtin_amdgcn_readlane(Gl.cls, i);
+    const int gz0 = lo[2] + 4 * W.ql;
+    const int zc = min(max(gz0, 0), J.nz - 4), s = gz0 - zc;
+    const bool shifted = __any(s != 0);
+    const LT fill = (LT)J.fill;
+    for (int p0 = 0; p0 < W.passes; p0 += N) {
+        uint32_t rows_in = 0;
 #pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            G.lo[a] = __builtin_amdgcn_readlane(Gl.lo[a], i);
-            G.e[a] = __builtin_amdgcn_readlane(Gl.e[a], i);
+        for (int u = 0; u < N; ++u) {
+            const int gx = lo[0] + cx, gy = lo[1] + cy;
+            const bool in = (uint32_t)gx < (uint32_t)J.nx && (uint32_t)gy < (uint32_t)J.ny;
+            rows_in |= (in ? 1u : 0u) << u;
+            w[u] = QuadRaw<T>::load_at(
+                S.img,
+                in && p0 + u < W.mine && reach(cx, cy)
+                    ? elem_index(S, gx, gy, zc) * (uint32_t)sizeof(T)
+                    : kNowhere,
+                0);
+            const int c = cy + W.step_y;
+            cx += c >= ey ? W.step_x + 1 : W.step_x;
+            cy = c >= ey ? c - ey : c;
         }
-        G.quads = __builtin_amdgcn_readlane(Gl.quads, i);
-        G.pitch = __builtin_amdgcn_readlane(Gl.pitch, i);
-        G.lds = __builtin_amdgcn_readlane((int)Gl.lds, i) != 0;
-        fwd_box<T, LT, ALIGNED, kDispNone>(J, G, SL, s_lds, lds_cells, Q0);
+#pragma unroll
+        for (int u = 0; u < N; ++u)
+            if (p0 + u < W.mine) {
+                LT c[4];
+                QuadRaw<T>::cells(w[u], c);
+                LT *dst = reinterpret_cast<LT *>(s_lds + (l + u * step));
+                const bool ok = (rows_in >> u) & 1;
+                if (shifted) {
+                    store_shifted<LT>(c, s, ok, fill, dst);
+                } else {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        c[v] = ok ? c[v] : fill;
+                    store4(dst, c);
+                }
+            }
+        l += N * step;
     }
+}
+
+// Affine tile, processed as sub-tiles of the job's sub-tile shape (the whole
+// tile unless its footprint would not fit the LDS reservation).  LT: type of
+// the LDS footprint cells (FP32, or int16 for int16 inputs).  ALIGNED: the
+// output z extent is a multiple of 4, so every run is one noise group and (with
+// 16-byte aligned outputs) one vector store.
+//
+// What a sub-tile costs besides its samples is kept small: the extents of its
+// footprint are the job's (from the host), only its origin is computed (all
+// sub-tiles at once, one per lane), and all loads of a footprint are in flight
+// at once.
+template <typename T, typename LT, bool ALIGNED>
+__device__ __forceinline__ void fwd_tile_affine(JobPtr Jp, const Box &B0, const Tiling &TL,
+                                                uint8_t *s_lds)
+{
+    const RunQ Q0{};
+    int cls = kOutside, lo[3] = {0, 0, 0};
+    float g[3] = {0.0f, 0.0f, 0.0f};
+    StageWalk W;
+    uint32_t todo;
+    bool fast = false;
+    {
+        const FwdJob &J = *(const FwdJob *)reload(Jp);
+        const Tiling SL = {J.sub[0], J.sub[1], J.sub[2]};
+        const int n[3] = {J.nx, J.ny, J.nz};
+        const int e[3] = {J.box_e[0], J.box_e[1], J.box_e[2]};
+        const int quads = (e[2] + 3) >> 2;
+        // sub-tile i in lane i of each wave: its class and the window's first cell
+        const int nz_log = TL.lz - SL.lz, ny_log = TL.ly - SL.ly, nx_log = TL.lx - SL.lx;
+        const int lane = threadIdx.x & 63;
+        const int bx = B0.x0 + ((lane >> (nz_log + ny_log)) << SL.lx);
+        const int by = B0.y0 + (((lane >> nz_log) & ((1 << ny_log) - 1)) << SL.ly);
+        const int bz = B0.z0 + ((lane & ((1 << nz_log) - 1)) << SL.lz);
+        if (J.nx != 0 && J.ny != 0 && J.nz != 0) {
+            float rb[3];
+            row_base(J.M, (float)bx, (float)by, rb);
+            bool outside = false, interior = true;
+            float qc[3];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                const float q0 = coord(J.M, i, rb, (float)bz);
+                qc[i] = q0 + J.box_mid[i];
+                const float l = q0 + J.box_dn[i], h = q0 + J.box_up[i];
+                outside = outside || h <= -1.0f || l >= (float)n[i];
+                interior = interior && l >= 0.0f && h < (float)(n[i] - 1) &&
+                           (i == 2 ? 4 * quads : e[i]) <= n[i];
+                lo[i] = (int)fminf(fmaxf(floorf(l), -2.0f), (float)n[i]);
+            }
+            cls = outside ? kOutside : interior ? kInterior : kBoundary;
+            // the window inside the volume (interior: every row and quad of it),
+            // inside [-2, n + 2) otherwise
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+                lo[i] = min(lo[i], cls == kInterior ? n[i] - (i == 2 ? 4 * quads : e[i])
+                                                    : n[i] + 2 - e[i]);
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                g[k] = __builtin_fmaf(
+                    J.inv[3 * k], (float)lo[0] - qc[0],
+                    __builtin_fmaf(J.inv[3 * k + 1], (float)lo[1] - qc[1],
+                                   J.inv[3 * k + 2] * ((float)lo[2] - qc[2])));
+        }
+        const int nsub = 1 << (nx_log + ny_log + nz_log);  // at most 32
+        todo = (uint32_t)__ballot(lane < nsub && bx <= B0.x1 && by <= B0.y1 && bz <= B0.z1);
+        W.passes = 0;
+        if (e[0] != 0 && __any(cls != kOutside)) {
+            W = stage_walk(e[0] * e[1], e[1], quads);
+            fast = W.passes > 0 && J.nz >= 4;
+        }
+    }
+    bool used = false;                                     // LDS read by a sub-tile
+    while (todo) {
+        const int i = __builtin_ctz(todo);
+        todo &= todo - 1;
+        const int c = __builtin_amdgcn_readlane(cls, i);
+        int path = c == kOutside ? kPathOutside
+                                 : c == kInterior ? kPathDirectInterior : kPathDirectBoundary;
+        Box B;
+        const FwdJob &J = *(const FwdJob *)reload(Jp);
+        const Tiling SL = {J.sub[0], J.sub[1], J.sub[2]};
+        const int nz_log = TL.lz - SL.lz, ny_log = TL.ly - SL.ly;
+        B.x0 = B0.x0 + ((i >> (nz_log + ny_log)) << SL.lx);
+        B.y0 = B0.y0 + (((i >> nz_log) & ((1 << ny_log) - 1)) << SL.ly);
+        B.z0 = B0.z0 + ((i & ((1 << nz_log) - 1)) << SL.lz);
+        B.x1 = min(B.x0 + (1 << SL.lx) - 1, B0.x1);
+        B.y1 = min(B.y0 + (1 << SL.ly) - 1, B0.y1);
+        B.z1 = min(B.z0 + (1 << SL.lz) - 1, B0.z1);
+        B.sx = B.sy = B.c0 = 0;
+        if (c != kOutside && J.box_e[0] != 0 && (sizeof(LT) == 4 || (J.flags & kFlagFillInT))) {
+            path = c == kInterior ? kPathLdsInterior : kPathLdsBoundary;
+            const Src S = make_src<T>(J);
+            const int e1 = J.box_e[1], pitch = J.box_pitch;
+            const int l[3] = {__builtin_amdgcn_readlane(lo[0], i),
+                              __builtin_amdgcn_readlane(lo[1], i),
+                              __builtin_amdgcn_readlane(lo[2], i)};
+            B.sy = pitch * (int)sizeof(LT);
+            B.sx = e1 * B.sy;
+            B.c0 = -(l[0] * B.sx + l[1] * B.sy + l[2] * (int)sizeof(LT));
+            if (used)
+                __syncthreads();       // the last sub-tile has been sampled
+            if (fast) {
+                const float gi[3] = {
+                    __int_as_float(__builtin_amdgcn_readlane(__float_as_int(g[0]), i)),
+                    __int_as_float(__builtin_amdgcn_readlane(__float_as_int(g[1]), i)),
+                    __int_as_float(__builtin_amdgcn_readlane(__float_as_int(g[2]), i))};
+                stage_window<T, LT>(J, S, W, l, gi, e1, pitch, c == kInterior, s_lds);
+            } else {
+                TileGeom G;
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    G.lo[a] = l[a];
+                    G.e[a] = J.box_e[a];
+                }
+                G.quads = (G.e[2] + 3) >> 2;
+                G.pitch = pitch;
+                G.cls = c;
+                stage_footprint<T, LT, kAffineThreads>(J, S, G, reinterpret_cast<LT *>(s_lds));
+            }
+            __syncthreads();
+            used = true;
+        }
+        run_box<T, LT, ALIGNED, kDispNone>(Jp, B, path, SL, s_lds, Q0);
+    }
+    if (used)
+        __syncthreads();               // LDS is reused by the next tile
+}
+
+// One output tile t of job J.
+template <typename T, typename LT, bool ALIGNED, int DISP>
+__device__ __forceinline__ void fwd_tile_lt(JobPtr Jp, int t, const Tiling &TL,
+                                            int32_t lds_cells, uint8_t *s_lds)
+{
+    const FwdJob &J = *(const FwdJob *)reload(Jp);
+    const int rest = (int)div_rcp((uint32_t)t, (uint32_t)J.tiles_z, J.rcp_tz);
+    const int tz = t - rest * J.tiles_z;
+    const int tx = (int)div_rcp((uint32_t)rest, (uint32_t)J.tiles_y, J.rcp_ty);
+    const int ty = rest - tx * J.tiles_y;
+    Box B;
+    B.x0 = tx << TL.lx;
+    B.y0 = ty << TL.ly;
+    B.z0 = tz << TL.lz;
+    B.x1 = min(B.x0 + (1 << TL.lx), J.ox) - 1;
+    B.y1 = min(B.y0 + (1 << TL.ly), J.oy) - 1;
+    B.z1 = min(B.z0 + (1 << TL.lz), J.oz) - 1;
+    B.sx = B.sy = B.c0 = 0;
+    if constexpr (DISP != kDispNone)
+        fwd_tile_disp<T, LT, ALIGNED, DISP>(Jp, B, TL, lds_cells, s_lds);
+    else
+        fwd_tile_affine<T, LT, ALIGNED>(Jp, B, TL, s_lds);
 }
 
 template <typename T, bool ALIGNED, int DISP>
-__device__ __forceinline__ void fwd_tile(const FwdJob &J, int t, const Tiling &TL,
-                                         int32_t lds_cells, uint8_t *s_lds)
+__device__ __forceinline__ void fwd_tile(JobPtr Jp, int t, const Tiling &TL, int32_t lds_cells,
+                                         uint8_t *s_lds)
 {
-    if (sizeof(T) == 2 && (J.flags & kFlagLds16))
-        fwd_tile_lt<T, T, ALIGNED, DISP>(J, t, TL, lds_cells, s_lds);
+    if (sizeof(T) == 2 && (Jp->flags & kFlagLds16))
+        fwd_tile_lt<T, T, ALIGNED, DISP>(Jp, t, TL, lds_cells, s_lds);
     else
-        fwd_tile_lt<T, float, ALIGNED, DISP>(J, t, TL, lds_cells, s_lds);
+        fwd_tile_lt<T, float, ALIGNED, DISP>(Jp, t, TL, lds_cells, s_lds);
 }
 
 // Dynamic LDS: lds_cells input-type cells of image footprint (rounded up to
@@ -344,14 +657,16 @@ extern __shared__ __attribute__((aligned(16))) uint8_t s_footprint[];
 
 // Single job, job in kernel arguments, one workgroup per tile.
 template <typename T, bool ALIGNED, int DISP>
-__global__ __launch_bounds__(kThreads) void k_warp_single(FwdJob J, Tiling TL, int32_t ntiles,
+__global__ __launch_bounds__(kFwdThreads<DISP>) void k_warp_single(FwdJob J, Tiling TL, int32_t ntiles,
                                                           int32_t lds_cells)
 {
     const int b = blockIdx.x;
     const int t = xcd_tile(b & 7, b >> 3);
     if (t >= ntiles)
         return;
-    fwd_tile<T, ALIGNED, DISP>(J, t, TL, lds_cells, s_footprint);
+    // J is the first kernel argument (a single call's footprints are FP32 cells)
+    fwd_tile_lt<T, float, ALIGNED, DISP>((JobPtr)__builtin_amdgcn_kernarg_segment_ptr(), t, TL,
+                                         lds_cells, s_footprint);
 }
 
 // Index of the job holding global tile t: the number of i in [1, njobs) with
@@ -376,8 +691,13 @@ __device__ __forceinline__ int job_of(const int32_t *__restrict__ prefix, int nj
 // (xcd_tile; persistent when gridDim.x is a few per CU).  MODE fixes
 // the input and LDS cell types when every job shares them (fewer code paths
 // in the kernel, less register pressure); kBatchMixed dispatches per job.
+constexpr int batch_threads(int mode)
+{
+    return mode == kBatchSplineI16 || mode == kBatchSplineF32 || mode == kBatchSplineMixed
+               ? kThreads : kAffineThreads;
+}
 template <bool ALIGNED, int MODE>
-__global__ __launch_bounds__(kThreads) void k_warp_batch(const FwdJob *__restrict__ jobs,
+__global__ __launch_bounds__(batch_threads(MODE)) void k_warp_batch(const FwdJob *__restrict__ jobs,
                                                          const int32_t *__restrict__ prefix,
                                                          int32_t njobs, Tiling TL,
                                                          int32_t lds_cells)
@@ -391,14 +711,14 @@ __global__ __launch_bounds__(kThreads) void k_warp_batch(const FwdJob *__restric
         if (t >= total)
             break;
         const int j = job_of(prefix, njobs, t);
-        const FwdJob J = jobs[j];
+        const JobPtr J = (JobPtr)(jobs + j);
         const int lt = t - prefix[j];
         if constexpr (MODE == kBatchSplineI16) {
             fwd_tile_lt<int16_t, float, ALIGNED, kDispSpline>(J, lt, TL, lds_cells, s_footprint);
         } else if constexpr (MODE == kBatchSplineF32) {
             fwd_tile_lt<float, float, ALIGNED, kDispSpline>(J, lt, TL, lds_cells, s_footprint);
         } else if constexpr (MODE == kBatchSplineMixed) {
-            if (J.dtype == kI16)
+            if (J->dtype == kI16)
                 fwd_tile_lt<int16_t, float, ALIGNED, kDispSpline>(J, lt, TL, lds_cells, s_footprint);
             else
                 fwd_tile_lt<float, float, ALIGNED, kDispSpline>(J, lt, TL, lds_cells, s_footprint);
@@ -409,7 +729,7 @@ __global__ __launch_bounds__(kThreads) void k_warp_batch(const FwdJob *__restric
         } else if constexpr (MODE == kBatchF32) {
             fwd_tile_lt<float, float, ALIGNED, kDispNone>(J, lt, TL, lds_cells, s_footprint);
         } else {
-            if (J.dtype == kI16)
+            if (J->dtype == kI16)
                 fwd_tile<int16_t, ALIGNED, kDispNone>(J, lt, TL, lds_cells, s_footprint);
             else
                 fwd_tile<float, ALIGNED, kDispNone>(J, lt, TL, lds_cells, s_footprint);
@@ -438,38 +758,132 @@ int32_t footprint_cells_bound(const FwdJob &J, const Tiling &TL)
     return (int32_t)cells;
 }
 
-// Sub-tile shape of job J for tile TL and an LDS reservation of lds_cells
-// cells: the whole tile when its footprint bound fits; otherwise the sub-box
-// of the tile with the most voxels (at least 2^10, or the tile's own count if
-// smaller; z extent >= 4) whose bound fits, fewest cells per voxel among
-// equals; the whole tile (direct gathers) when none fits.  As tiles hold at
-// most 2^14 voxels, a tile has at most 16 sub-tiles (the kernels read one
-// sub-tile's geometry per lane of a wave).
-Tiling choose_subtile(const FwdJob &J, const Tiling &TL, int32_t lds_cells)
+// The footprint window of sub-tile shape S of job J (FwdJob::box_*); its LDS
+// cells.  The window of axis i holds the cells floor(l) .. floor(h) + 1 of any
+// coordinate range [l, h] of width at most span (delta on either side
+// included): floor(span) + 3, and no more than the n + 4 cells [-2, n + 2) that
+// clamped coordinates reach.
+static int32_t set_box(FwdJob &J, const Tiling &S)
 {
-    if (J.disp || J.ctrl || lds_cells <= 0 || footprint_cells_bound(J, TL) <= lds_cells)
-        return TL;
-    const int min_log = std::min(10, TL.lx + TL.ly + TL.lz);
+    const int t[3] = {1 << S.lx, 1 << S.ly, 1 << S.lz};
+    const int n[3] = {J.nx, J.ny, J.nz};
+    int64_t cells = 1;
+    for (int i = 0; i < 3; ++i) {
+        double dn = -(double)J.delta[i], up = (double)J.delta[i];
+        for (int j = 0; j < 3; ++j) {
+            const double d = (double)J.M[4 * i + j] * (double)(t[j] - 1);
+            (d < 0.0 ? dn : up) += d;
+        }
+        J.box_dn[i] = (float)dn;
+        J.box_up[i] = (float)up;
+        const double e = std::min(std::floor(up - dn) + 3.0, (double)n[i] + 4.0);
+        J.box_e[i] = (int32_t)e;
+        if (i == 2)
+            J.box_pitch = lds_pitch(J.box_e[2]);
+        cells = std::min<int64_t>(cells * (i == 2 ? J.box_pitch : J.box_e[i]), (int64_t)1 << 30);
+    }
+    return (int32_t)cells;
+}
+
+// Which quads of the window the samples of sub-tile shape S can use
+// (FwdJob::inv, reach): a sample p of the box uses cell c when q(p) = A p + b
+// lies in (c - 1, c + 1) per axis, a quad c .. c + 3 along z when it lies in (c -
+// 1, c + 4); so p lies in A^-1 of that block, along output axis k within sum_j
+// |A^-1_kj| r_j of its centre (r = 1, 1, 2.5).  The slack takes the rounding of
+// q and of the kernel's FP32 test, whose terms stay under 2^11 for the inverses
+// admitted here; other maps copy every quad.
+static void set_reach(FwdJob &J, const Tiling &S)
+{
+    const int t[3] = {1 << S.lx, 1 << S.ly, 1 << S.lz};
+    double a[3][3], c[3][3], inv[3][3];
+    for (int i = 0; i < 3; ++i) {
+        J.box_mid[i] = 0.0f;
+        double mid = 0.0;
+        for (int j = 0; j < 3; ++j) {
+            a[i][j] = (double)J.M[4 * i + j];
+            mid += a[i][j] * 0.5 * (double)(t[j] - 1);
+        }
+        J.box_mid[i] = (float)mid;
+    }
+    for (int i = 0; i < 3; ++i)
+        for (int j = 0; j < 3; ++j) {
+            const int i1 = (i + 1) % 3, i2 = (i + 2) % 3, j1 = (j + 1) % 3, j2 = (j + 2) % 3;
+            c[i][j] = a[i1][j1] * a[i2][j2] - a[i1][j2] * a[i2][j1];
+        }
+    const double det = a[0][0] * c[0][0] + a[0][1] * c[0][1] + a[0][2] * c[0][2];
+    bool ok = std::isfinite(det) && det != 0.0;
+    for (int k = 0; k < 3 && ok; ++k)
+        for (int j = 0; j < 3; ++j) {
+            inv[k][j] = c[j][k] / det;
+            ok = ok && std::fabs(inv[k][j]) <= 8.0;
+        }
+    for (int k = 0; k < 3; ++k) {
+        double m = 0.5 * (double)(t[k] - 1) + 0.02;
+        for (int j = 0; j < 3; ++j) {
+            J.inv[3 * k + j] = ok ? (float)inv[k][j] : 0.0f;
+            if (ok)
+                m += std::fabs(inv[k][j]) * ((j == 2 ? 2.5 : 1.0) + 2.0 * (double)J.delta[j]);
+        }
+        J.reach[k] = (float)m;
+    }
+}
+
+// Whether cell indices and coordinates of J stay where the LDS paths compute
+// them exactly: 24-bit cell indices and coordinates that FP32 resolves to
+// fractions (delta is 2^-20 of their bound).
+static bool box_exact(const FwdJob &J)
+{
+    for (int i = 0; i < 3; ++i)
+        if (!(J.delta[i] < 4.0f))
+            return false;
+    return J.nx < (1 << 22) && J.ny < (1 << 22) && J.nz < (1 << 22);
+}
+
+// Sub-tile shape of job J for tile TL and an LDS reservation of lds_cells
+// cells (into J.sub and J.box_*): the whole tile when its window fits;
+// otherwise the sub-box of the tile with the most voxels (at least 2^9, or
+// the tile's own count if smaller; z extent >= 4) whose window fits, fewest
+// cells per voxel among equals; the whole tile and no window (direct gathers,
+// 2.4 times slower on a 512 x 512 x 320 scan) when none fits: false.  As tiles
+// hold at most 2^14 voxels, a tile has at most 32 sub-tiles (the kernels
+// compute one sub-tile's geometry per lane of a wave).
+bool choose_subtile(FwdJob &J, const Tiling &TL, int32_t lds_cells)
+{
+    bool fits = true;
     Tiling best = TL;
-    int best_log = -1;
-    double best_ratio = 0.0;
-    for (int a = 0; a <= TL.lx; ++a)
-        for (int b = 0; b <= TL.ly; ++b)
-            for (int c = 2; c <= TL.lz; ++c) {
-                if (a + b + c < min_log)
-                    continue;
-                const Tiling S = {a, b, c};
-                const int32_t cells = footprint_cells_bound(J, S);
-                if (cells > lds_cells)
-                    continue;
-                const double ratio = (double)cells / (double)(1 << (a + b + c));
-                if (a + b + c > best_log || (a + b + c == best_log && ratio < best_ratio)) {
-                    best = S;
-                    best_log = a + b + c;
-                    best_ratio = ratio;
-                }
-            }
-    return best;
+    if (!J.disp && !J.ctrl) {
+        fits = lds_cells > 0 && box_exact(J);
+        if (fits && set_box(J, TL) > lds_cells) {
+            const int min_log = std::min(9, TL.lx + TL.ly + TL.lz);
+            int best_log = -1;
+            double best_ratio = 0.0;
+            for (int a = 0; a <= TL.lx; ++a)
+                for (int b = 0; b <= TL.ly; ++b)
+                    for (int c = 2; c <= TL.lz; ++c) {
+                        if (a + b + c < min_log)
+                            continue;
+                        const Tiling S = {a, b, c};
+                        const int32_t cells = set_box(J, S);
+                        if (cells > lds_cells)
+                            continue;
+                        const double ratio = (double)cells / (double)(1 << (a + b + c));
+                        if (a + b + c > best_log || (a + b + c == best_log && ratio < best_ratio)) {
+                            best = S;
+                            best_log = a + b + c;
+                            best_ratio = ratio;
+                        }
+                    }
+            fits = best_log >= 0;
+        }
+        (void)set_box(J, best);
+        set_reach(J, best);
+        if (!fits)
+            J.box_e[0] = 0;
+    }
+    J.sub[0] = best.lx;
+    J.sub[1] = best.ly;
+    J.sub[2] = best.lz;
+    return fits;
 }
 
 int32_t lds_cells_cap(int32_t elem_bytes)
@@ -493,17 +907,17 @@ static void launch_single_t(const FwdJob &J, const Tiling &TL, int ntiles, int32
 {
     if (J.dtype == kI16) {
         if (aligned)
-            hipLaunchKernelGGL((k_warp_single<int16_t, true, DISP>), dim3(grid), dim3(kThreads), lds,
+            hipLaunchKernelGGL((k_warp_single<int16_t, true, DISP>), dim3(grid), dim3(kFwdThreads<DISP>), lds,
                                s, J, TL, ntiles, cells);
         else
-            hipLaunchKernelGGL((k_warp_single<int16_t, false, DISP>), dim3(grid), dim3(kThreads),
+            hipLaunchKernelGGL((k_warp_single<int16_t, false, DISP>), dim3(grid), dim3(kFwdThreads<DISP>),
                                lds, s, J, TL, ntiles, cells);
     } else {
         if (aligned)
-            hipLaunchKernelGGL((k_warp_single<float, true, DISP>), dim3(grid), dim3(kThreads), lds,
+            hipLaunchKernelGGL((k_warp_single<float, true, DISP>), dim3(grid), dim3(kFwdThreads<DISP>), lds,
                                s, J, TL, ntiles, cells);
         else
-            hipLaunchKernelGGL((k_warp_single<float, false, DISP>), dim3(grid), dim3(kThreads), lds,
+            hipLaunchKernelGGL((k_warp_single<float, false, DISP>), dim3(grid), dim3(kFwdThreads<DISP>), lds,
                                s, J, TL, ntiles, cells);
     }
 }
@@ -585,20 +999,22 @@ hipError_t launch_warp_single(const FwdJob &J0, const Tiling &TL0, hipStream_t s
     Js.tiles_x = (Js.ox + (1 << TL.lx) - 1) >> TL.lx;
     Js.tiles_y = (Js.oy + (1 << TL.ly) - 1) >> TL.ly;
     Js.tiles_z = (Js.oz + (1 << TL.lz) - 1) >> TL.lz;
+    Js.rcp_ty = rcp_u32((uint32_t)Js.tiles_y);
+    Js.rcp_tz = rcp_u32((uint32_t)Js.tiles_z);
     const FwdJob &J = Js;
     const int ntiles = J.tiles_x * J.tiles_y * J.tiles_z;
     if (ntiles == 0)
         return hipSuccess;
     const int grid = 8 * xcd_slots(ntiles);
     const int32_t esz = (J.flags & kFlagLds16) ? 2 : 4;
-    const int32_t cells = displaced ? lds_cells_for(kDispLdsCells, esz)
-                                 : lds_cells_for(footprint_cells_bound(J, TL), esz);
+    const int32_t bound = displaced ? kDispLdsCells : footprint_cells_bound(J, TL);
+    int32_t cells = lds_cells_for(displaced ? bound : std::min(bound, kAffineLdsCells), esz);
+    if (!choose_subtile(Js, TL, cells)) {
+        cells = lds_cells_for(bound, esz);
+        (void)choose_subtile(Js, TL, cells);
+    }
     const size_t lds = lds_bytes_for(cells, esz);
     const bool aligned = J.oz % 4 == 0;
-    const Tiling SL = choose_subtile(J, TL, cells);
-    Js.sub[0] = SL.lx;
-    Js.sub[1] = SL.ly;
-    Js.sub[2] = SL.lz;
     if (J.ctrl)
         launch_single_t<kDispSpline>(Js, TL, ntiles, cells, grid, lds, aligned, s);
     else if (J.disp)
@@ -615,31 +1031,31 @@ static void launch_batch_mode(int mode, const FwdJob *jobs_dev, const int32_t *p
 {
     switch (mode) {
     case kBatchI16F32:
-        hipLaunchKernelGGL((k_warp_batch<ALIGNED, kBatchI16F32>), dim3(grid), dim3(kThreads), lds,
+        hipLaunchKernelGGL((k_warp_batch<ALIGNED, kBatchI16F32>), dim3(grid), dim3(batch_threads(mode)), lds,
                            s, jobs_dev, prefix_dev, njobs, TL, lds_cells);
         break;
     case kBatchI16I16:
-        hipLaunchKernelGGL((k_warp_batch<ALIGNED, kBatchI16I16>), dim3(grid), dim3(kThreads), lds,
+        hipLaunchKernelGGL((k_warp_batch<ALIGNED, kBatchI16I16>), dim3(grid), dim3(batch_threads(mode)), lds,
                            s, jobs_dev, prefix_dev, njobs, TL, lds_cells);
         break;
     case kBatchF32:
-        hipLaunchKernelGGL((k_warp_batch<ALIGNED, kBatchF32>), dim3(grid), dim3(kThreads), lds, s,
+        hipLaunchKernelGGL((k_warp_batch<ALIGNED, kBatchF32>), dim3(grid), dim3(batch_threads(mode)), lds, s,
                            jobs_dev, prefix_dev, njobs, TL, lds_cells);
         break;
     case kBatchSplineI16:
-        hipLaunchKernelGGL((k_warp_batch<ALIGNED, kBatchSplineI16>), dim3(grid), dim3(kThreads),
+        hipLaunchKernelGGL((k_warp_batch<ALIGNED, kBatchSplineI16>), dim3(grid), dim3(batch_threads(mode)),
                            lds, s, jobs_dev, prefix_dev, njobs, TL, lds_cells);
         break;
     case kBatchSplineF32:
-        hipLaunchKernelGGL((k_warp_batch<ALIGNED, kBatchSplineF32>), dim3(grid), dim3(kThreads),
+        hipLaunchKernelGGL((k_warp_batch<ALIGNED, kBatchSplineF32>), dim3(grid), dim3(batch_threads(mode)),
                            lds, s, jobs_dev, prefix_dev, njobs, TL, lds_cells);
         break;
     case kBatchSplineMixed:
-        hipLaunchKernelGGL((k_warp_batch<ALIGNED, kBatchSplineMixed>), dim3(grid), dim3(kThreads),
+        hipLaunchKernelGGL((k_warp_batch<ALIGNED, kBatchSplineMixed>), dim3(grid), dim3(batch_threads(mode)),
                            lds, s, jobs_dev, prefix_dev, njobs, TL, lds_cells);
         break;
     default:
-        hipLaunchKernelGGL((k_warp_batch<ALIGNED, kBatchMixed>), dim3(grid), dim3(kThreads), lds,
+        hipLaunchKernelGGL((k_warp_batch<ALIGNED, kBatchMixed>), dim3(grid), dim3(batch_threads(mode)), lds,
                            s, jobs_dev, prefix_dev, njobs, TL, lds_cells);
     }
 }
