@@ -49,6 +49,8 @@ __device__ __forceinline__ void bs_basis(float t, float B[4])
 }
 
 // Row profile P(x, y, gz) of component comp (control layout [3][gx][gy][gz]).
+// SLIM: four loads in flight instead of sixteen (registers).
+template <bool SLIM = false>
 __device__ __forceinline__ float bs_profile(const float *__restrict__ ctrl, const BsplineGeom &G,
                                             int comp, int32_t x, int32_t y, int32_t gz)
 {
@@ -69,121 +71,152 @@ __device__ __forceinline__ float bs_profile(const float *__restrict__ ctrl, cons
                                 ctrl[comp * gstride + ((int64_t)(ix + a) * G.gy + (iy + b)) * G.gz + gz],
                                 sa);
         s = __builtin_fmaf(Bx[a], sa, s);
+        if (SLIM)
+            __builtin_amdgcn_sched_barrier(0);
     }
     return s;
 }
 
-// Displacement of one thread's run of a tile of 2^lx x 2^ly rows (x, y) by
-// 2^lz voxels along z, evaluated from the control grid: the row profiles of
-// the tile's rows over its z-control window are computed into s_prof (LDS,
-// up to 64 rows; 64 * 3 * kSplineWindow floats, plus the control window and
-// the y contraction, 4 * 3 * 64 * kSplineWindow floats in all, when the tile
-// touches at most kSplineWindow controls along x and y), then each thread contracts z for its
-// own voxels z + k * zstep, k < nvalid, of row rr (x = x0 + (rr >> ly), y =
-// y0 + (rr & (2^ly - 1))).  A window of more than kSplineWindow controls (controls
-// closer than about 4 voxels along z) evaluates the profiles per voxel when
-// PER_VOXEL is set; without it the caller guarantees that every window fits.
-// Contains a workgroup barrier: every thread of the workgroup calls it.
+// Displacement of one thread's run of a tile of 8 x 8 rows (x, y) by 16 voxels
+// along z, evaluated from the control grid by a workgroup of 256 threads:
+// thread t has row t >> 2 (x = x0 + (row >> 3), y = y0 + (row & 7)) and the voxels z + k
+// zstep, k < nvalid, of the tile (z1 - z0 < 16).  With at most kSplineWindow
+// controls per axis in the tile's window, the sums of bs_profile are shared: the
+// window C[a][b][c] and the weights of the tile's 8 + 8 + 16 positions go to LDS,
+// then
+//   S[a][y][c] = sum_b B_b(y) C[a][b][c],  P[x][y][c] = sum_a B_a(x) S[a][y][c]
+// and each thread contracts c for its own voxels (the fmaf chains of bs_profile
+// in the same order, so the same bits).  Lane = 8 (b or y) + c throughout and a
+// wave takes one (a or x, component) at a time, so that every address is the
+// lane plus a scalar and no index is divided (most of the 322 VALU instructions
+// per voxel of the 256^3 warp were such divisions; it went from 185 to 160 us).  Wider windows along x or y take the profiles
+// one by one; along z (controls closer than about 4 voxels) every voxel its own when PER_VOXEL
+// is set; without it the caller guarantees that every z window fits.  s_prof:
+// kSplineTileLdsFloats floats of LDS, 16-byte aligned.  Contains workgroup
+// barriers: every thread of the workgroup calls it.
 constexpr int kSplineWindow = 8;
-constexpr int kSplineTileLdsFloats = 3 * 64 * kSplineWindow + 3 * kSplineWindow * kSplineWindow *
-                                     kSplineWindow + kSplineWindow * 8 * 3 * kSplineWindow;
+constexpr int kSplineTileLdsFloats = 3 * 3 * kSplineWindow * 64 + 32 * 4 + 32;
 
-template <int NT, bool PER_VOXEL = true>
+template <bool PER_VOXEL = true>
 __device__ __forceinline__ void spline_tile_u(const float *__restrict__ ctrl, const BsplineGeom &B,
-                                              int lx, int ly, int x0, int y0, int z0, int x1,
-                                              int y1, int z1, int rr, int x, int y, int z,
-                                              int zstep, int nvalid, bool mine, float *s_prof,
-                                              float (&u)[3][4])
+                                              int x0, int y0, int z0, int x1, int y1, int z1,
+                                              int x, int y, int z, int zstep, int nvalid,
+                                              bool mine, float *s_prof, float (&u)[3][4])
 {
-    const int izl = bs_index(z0, B.inv_hz, B.gz);
-    const int ncz = bs_index(z1, B.inv_hz, B.gz) - izl + 4;
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    float *Wc = s_prof;                            // [a][comp][b][c]
+    float *S = Wc + 3 * kSplineWindow * 64;        // [a][comp][y][c]
+    float *P = S + 3 * kSplineWindow * 64;         // [x][comp][y][c]
+    f32x4 *T = reinterpret_cast<f32x4 *>(P + 3 * 8 * 64);  // weights: 8 x, 8 y, 16 z
+    int *I = reinterpret_cast<int *>(T + 32);      // their cells, from the window's first
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+
+    // position pos of the 32: its cell in lane pos (and pos + 32) of every wave
+    const int pos = lane & 31;
+    const bool ax = pos < 8, ay = pos < 16;
+    const int p = min((ax ? x0 : ay ? y0 - 8 : z0 - 16) + pos, ax ? x1 : ay ? y1 : z1);
+    int32_t ci;
+    float ct;
+    bs_cell(p, ax ? B.inv_hx : ay ? B.inv_hy : B.inv_hz, ax ? B.gx : ay ? B.gy : B.gz, ci, ct);
+    const int ixl = __builtin_amdgcn_readlane(ci, 0), iyl = __builtin_amdgcn_readlane(ci, 8),
+              izl = __builtin_amdgcn_readlane(ci, 16);
+    const int ncx = __builtin_amdgcn_readlane(ci, 7) - ixl + 4,
+              ncy = __builtin_amdgcn_readlane(ci, 15) - iyl + 4,
+              ncz = __builtin_amdgcn_readlane(ci, 31) - izl + 4;
     if (!PER_VOXEL || ncz <= kSplineWindow) {
-        const int per_row = 3 * ncz;
-        const int nent = per_row << (lx + ly);
-        const int ixl = bs_index(x0, B.inv_hx, B.gx), iyl = bs_index(y0, B.inv_hy, B.gy);
-        const int ncx = bs_index(x1, B.inv_hx, B.gx) - ixl + 4;
-        const int ncy = bs_index(y1, B.inv_hy, B.gy) - iyl + 4;
+        if (wave == 0 && lane < 32) {
+            float Bw[4];
+            bs_basis(ct, Bw);
+            T[lane] = f32x4{Bw[0], Bw[1], Bw[2], Bw[3]};
+            I[lane] = ci - (ax ? ixl : ay ? iyl : izl);
+        }
+        const int64_t gstride = (int64_t)B.gx * B.gy * B.gz;
+        const int c = lane & 7, yr = lane >> 3;
         if (ncx <= kSplineWindow && ncy <= kSplineWindow) {
-            // separable, from the tile's control window staged in LDS: the same
-            // fmaf chains as bs_profile, sharing the y contraction of a control
-            // column among the rows of one y
-            float *Wc = s_prof + kSplineWindow * 3 * 64;                   // [3][ncx][ncy][ncz]
-            float *S = Wc + 3 * kSplineWindow * kSplineWindow * kSplineWindow;  // [ncx][ny][3][ncz]
-            const int ny = 1 << ly;
-            const int64_t gstride = (int64_t)B.gx * B.gy * B.gz;
-            const int nw = 3 * ncx * ncy * ncz;
-            for (int e = threadIdx.x; e < nw; e += NT) {
-                const int c = e % ncz, r1 = e / ncz;
-                const int b = r1 % ncy, r2 = r1 / ncy;
-                const int a = r2 % ncx, comp = r2 / ncx;
-                Wc[e] = ctrl[comp * gstride + ((int64_t)(ixl + a) * B.gy + (iyl + b)) * B.gz +
-                             izl + c];
+            if (c < ncz && yr < ncy) {
+                const int32_t e = (iyl + yr) * B.gz + izl + c;
+                for (int ac = wave; ac < 3 * ncx; ac += 4) {
+                    const int a = ac / 3, comp = ac - 3 * a;
+                    Wc[ac * 64 + lane] =
+                        ctrl[comp * gstride + (int64_t)(ixl + a) * B.gy * B.gz + e];
+                }
             }
             __syncthreads();
-            const int ns = ncx * ny * per_row;
-            for (int e = threadIdx.x; e < ns; e += NT) {
-                const int cc = e % per_row, r1 = e / per_row;
-                const int yr = r1 % ny, a = r1 / ny;
-                const int comp = cc / ncz, c = cc - comp * ncz;
-                int32_t iy;
-                float ty, By[4];
-                bs_cell(min(y0 + yr, y1), B.inv_hy, B.gy, iy, ty);
-                bs_basis(ty, By);
-                const float *w = Wc + ((comp * ncx + a) * ncy + (iy - iyl)) * ncz + c;
-                float sa = 0.0f;
+            {
+                const f32x4 By = T[8 + yr];
+                const float *w = Wc + I[8 + yr] * 8 + c;
+                for (int ac = wave; ac < 3 * ncx; ac += 4) {
+                    float sa = 0.0f;
 #pragma unroll
-                for (int bb = 0; bb < 4; ++bb)
-                    sa = __builtin_fmaf(By[bb], w[bb * ncz], sa);
-                S[e] = sa;
+                    for (int b = 0; b < 4; ++b)
+                        sa = __builtin_fmaf(By[b], w[ac * 64 + b * 8], sa);
+                    S[ac * 64 + lane] = sa;
+                }
             }
             __syncthreads();
-            for (int e = threadIdx.x; e < nent; e += NT) {
-                const int row = e / per_row;
-                const int cc = e - row * per_row;
-                const int yr = row & (ny - 1);
-                int32_t ix;
-                float tx, Bx[4];
-                bs_cell(min(x0 + (row >> ly), x1), B.inv_hx, B.gx, ix, tx);
-                bs_basis(tx, Bx);
-                const float *sp = S + ((ix - ixl) * ny + yr) * per_row + cc;
-                float sv = 0.0f;
 #pragma unroll
-                for (int a = 0; a < 4; ++a)
-                    sv = __builtin_fmaf(Bx[a], sp[a * ny * per_row], sv);
-                s_prof[e] = sv;
+            for (int xr = wave; xr < 8; xr += 4) {
+                const f32x4 Bx = T[xr];
+                const float *sp = S + I[xr] * (3 * 64) + lane;
+#pragma unroll
+                for (int comp = 0; comp < 3; ++comp) {
+                    float sv = 0.0f;
+#pragma unroll
+                    for (int a = 0; a < 4; ++a)
+                        sv = __builtin_fmaf(Bx[a], sp[(3 * a + comp) * 64], sv);
+                    P[(xr * 3 + comp) * 64 + lane] = sv;
+                }
             }
-        } else {
-            for (int e = threadIdx.x; e < nent; e += NT) {
-                const int row = e / per_row;
-                const int rem = e - row * per_row;
-                const int comp = rem / ncz, c = rem - comp * ncz;
-                const int px = min(x0 + (row >> ly), x1);
-                const int py = min(y0 + (row & ((1 << ly) - 1)), y1);
-                s_prof[e] = bs_profile(ctrl, B, comp, px, py, izl + c);
-            }
+        } else if (c < ncz) {
+#pragma unroll 1
+            for (int xc = wave; xc < 24; xc += 4)
+                P[xc * 64 + lane] = bs_profile<true>(ctrl, B, xc % 3, min(x0 + xc / 3, x1),
+                                               min(y0 + yr, y1), izl + c);
         }
         __syncthreads();
         if (!mine)
             return;
-        const float *P = s_prof + rr * per_row - izl;
+        const int row = threadIdx.x >> 2;
+        const float *pr = P + (row >> 3) * (3 * 64) + (row & 7) * 8;
+        f32x4 Bz[4];
+        int iz[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            if (k >= nvalid)
-                break;
-            int32_t iz;
-            float tz, Bz[4];
-            bs_cell(z + k * zstep, B.inv_hz, B.gz, iz, tz);
-            bs_basis(tz, Bz);
+            const int e = 16 + min(z - z0 + k * zstep, 15);
+            Bz[k] = T[e];
+            iz[k] = I[e];
+        }
+        if (__all(iz[0] == iz[3])) {   // cells do not decrease along z: one for all four
 #pragma unroll
             for (int comp = 0; comp < 3; ++comp) {
-                float s = 0.0f;
+                float v[4];
 #pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    s = __builtin_fmaf(Bz[c], P[comp * ncz + iz + c], s);
-                u[comp][k] = s;
+                for (int cc = 0; cc < 4; ++cc)
+                    v[cc] = pr[comp * 64 + iz[0] + cc];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    float s = 0.0f;
+#pragma unroll
+                    for (int cc = 0; cc < 4; ++cc)
+                        s = __builtin_fmaf(Bz[k][cc], v[cc], s);
+                    u[comp][k] = s;
+                }
             }
+        } else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int comp = 0; comp < 3; ++comp) {
+                    float s = 0.0f;
+#pragma unroll
+                    for (int cc = 0; cc < 4; ++cc)
+                        s = __builtin_fmaf(Bz[k][cc], pr[comp * 64 + iz[k] + cc], s);
+                    u[comp][k] = s;
+                }
         }
     } else if (PER_VOXEL && mine) {
+#pragma unroll 1
         for (int k = 0; k < nvalid; ++k) {
             int32_t iz;
             float tz, Bz[4];
@@ -195,7 +228,7 @@ __device__ __forceinline__ void spline_tile_u(const float *__restrict__ ctrl, co
 #pragma unroll 1
                 for (int c = 0; c < 4; ++c) {
                     const float bz = c == 0 ? Bz[0] : c == 1 ? Bz[1] : c == 2 ? Bz[2] : Bz[3];
-                    s = __builtin_fmaf(bz, bs_profile(ctrl, B, comp, x, y, iz + c), s);
+                    s = __builtin_fmaf(bz, bs_profile<true>(ctrl, B, comp, x, y, iz + c), s);
                 }
                 u[comp][k] = s;
             }

@@ -363,36 +363,45 @@ __device__ __forceinline__ void stage_footprint(const FwdJob &J, const Src &S, c
     }
 }
 
-// Workgroup-wide min of mn[] and max of mx[] (3 ints each); every thread gets
-// the result.  s_red: 4 x 6 ints of LDS.  Ends with a barrier.
-__device__ __forceinline__ void block_minmax3(int mn[3], int mx[3], int (*s_red)[6])
+// Minimum over the wave, as a scalar: DPP row shifts and broadcasts (one VALU
+// instruction a step; a shuffle goes through LDS), lane 63 holds the result.
+__device__ __forceinline__ int wave_min(int v)
 {
+#define CTAUG_DPP_MIN(ctrl, rows)                                                                 \
+    v = min(v, __builtin_amdgcn_update_dpp(v, v, ctrl, rows, 0xF, false))
+    CTAUG_DPP_MIN(0x111, 0xF);         // row_shr:1, 2, 4, 8: lane 15 of each row of 16
+    CTAUG_DPP_MIN(0x112, 0xF);
+    CTAUG_DPP_MIN(0x114, 0xF);
+    CTAUG_DPP_MIN(0x118, 0xF);
+    CTAUG_DPP_MIN(0x142, 0xA);         // row_bcast:15 into rows 1 and 3
+    CTAUG_DPP_MIN(0x143, 0xC);         // row_bcast:31 into rows 2 and 3
+#undef CTAUG_DPP_MIN
+    return __builtin_amdgcn_readlane(v, 63);
+}
+
+// Workgroup-wide min of mn[] and max of mx[] (3 ints each); every thread gets
+// the result, as scalars.  s_red: 6 x 4 ints of LDS, 16-byte aligned.  Contains
+// one barrier; the caller passes another before it calls again.
+__device__ __forceinline__ void block_minmax3(int mn[3], int mx[3], int (*s_red)[kThreads / 64])
+{
+    static_assert(kThreads == 256, "four waves");
+    typedef int i32x4 __attribute__((ext_vector_type(4)));
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int v = 0;
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1)
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            mn[i] = min(mn[i], __shfl_xor(mn[i], off, 64));
-            mx[i] = max(mx[i], __shfl_xor(mx[i], off, 64));
-        }
-    if (lane == 0)
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            s_red[wave][i] = mn[i];
-            s_red[wave][3 + i] = mx[i];
-        }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        mn[i] = s_red[0][i];
-        mx[i] = s_red[0][3 + i];
-#pragma unroll
-        for (int w = 1; w < kThreads / 64; ++w) {
-            mn[i] = min(mn[i], s_red[w][i]);
-            mx[i] = max(mx[i], s_red[w][3 + i]);
-        }
+    for (int i = 0; i < 6; ++i) {      // max as the minimum of the complement
+        const int m = wave_min(i < 3 ? mn[i] : ~mx[i - 3]);
+        v = lane == i ? m : v;
     }
+    if (lane < 6)
+        s_red[lane][wave] = v;
     __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+        const i32x4 r = *reinterpret_cast<const i32x4 *>(s_red[i]);
+        const int m = __builtin_amdgcn_readfirstlane(min(min(r.x, r.y), min(r.z, r.w)));
+        (i < 3 ? mn[i] : mx[i - 3]) = i < 3 ? m : ~m;
+    }
 }
 
 // Footprint of an output box from the range [fmn, fmx] of floor(q) over its

@@ -93,6 +93,8 @@ constexpr int32_t kCtrlMaxEntries = 2048;
 constexpr int32_t kSplineBwdCells = kBwdLdsCells - kCtrlMaxEntries;
 constexpr int32_t kCtrlRowGroups = 64;
 static_assert(kSplineTileLdsFloats <= kSplineBwdCells, "the B-spline scratch fits the reservation");
+static_assert(kBwdTiling.lx == 3 && kBwdTiling.ly == 3 && kBwdTiling.lz == 4 && kThreads == 256,
+              "the tile of spline_tile_u");
 
 // v + (v of the lane at quad position q ^ 1), then ^ 2: sum over the 4 lanes
 // of a quad, in the same order on every lane (DPP quad permutes, no LDS).
@@ -310,7 +312,7 @@ __device__ __forceinline__ void bwd_tile(const FwdJob &J, int t, const Src &src,
                                          const float *__restrict__ gn, int tn, float (&gnext)[4],
                                          float *__restrict__ g_img, float *__restrict__ g_disp,
                                          float *s_ctrl, int32_t lds_cells, int fix_bits, int zr,
-                                         int yr, int xr, double (&acc)[12], int (*s_red)[6],
+                                         int yr, int xr, double (&acc)[12], int (*s_red)[kThreads / 64],
                                          float *s_gmax)
 {
     const Tiling TL = kBwdTiling;
@@ -329,9 +331,8 @@ __device__ __forceinline__ void bwd_tile(const FwdJob &J, int t, const Src &src,
     bool gd[4];
     float u[3][4];
     if (DISP == kDispSpline)
-        spline_tile_u<kThreads, false>(J.ctrl, J.bs, TL.lx, TL.ly, x0, y0, z0, x1, y1, z1,
-                                       threadIdx.x >> 2, x, y, z, 4, nvalid, run_ok,
-                                       s_cells, u);
+        spline_tile_u<false>(J.ctrl, J.bs, x0, y0, z0, x1, y1, z1, x, y, z, 4, nvalid, run_ok,
+                             s_cells, u);
     {
         float rb[3];
         row_base(J.M, (float)x, (float)y, rb);
@@ -386,6 +387,7 @@ __device__ __forceinline__ void bwd_tile(const FwdJob &J, int t, const Src &src,
                     fmx[i] = max(fmx[i], f);
                 }
         block_minmax3(fmn, fmx, s_red);
+        __syncthreads();               // a tile without a footprint passes no other
         G = geom_from_cells(J, x0, y0, z0, x1, y1, z1, fmn, fmx, lds_cells);
     } else {
         G = box_geom(J, x0, y0, z0, x1, y1, z1, lds_cells);
@@ -717,7 +719,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
         __syncthreads();
     }
 
-    __shared__ int s_red[kThreads / 64][6];
+    __shared__ __attribute__((aligned(16))) int s_red[6][kThreads / 64];
     __shared__ float s_gmax[kThreads / 64];
 
     // this thread's run inside every tile: voxels z0 + zr + 4k, k = 0..3, of row
@@ -776,7 +778,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
     const int total = B.prefix[B.njobs];
     const int b = blockIdx.x;
     const int per_xcd_wg = gridDim.x >> 3;
-    __shared__ int s_red[kThreads / 64][6];
+    __shared__ __attribute__((aligned(16))) int s_red[6][kThreads / 64];
     __shared__ float s_gmax[kThreads / 64];
     __shared__ double red[kThreads / 64][12];
     const int zr = threadIdx.x & 3;

@@ -149,7 +149,7 @@ __device__ __forceinline__ void run_box(JobPtr Jp, const Box &B, int path, const
                                  (float)c10[0], (float)c10[1], (float)c11[0], (float)c11[1]};
             return tri(kk, tx, ty, tz);
         };
-        if (DISP == kDispNone && path == kPathLdsInterior) {
+        if (path == kPathLdsInterior) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 if (ALIGNED || k < nvalid)
@@ -266,99 +266,22 @@ __device__ __forceinline__ void run_box(JobPtr Jp, const Box &B, int path, const
     }
 }
 
-// Displacement tile (ALIGNED, LT: see fwd_tile_affine).  A displacement has no
-// a-priori footprint bound: the tile (one run of 4 z voxels per thread)
-// computes its coordinates once, reduces their cells, and stages that
-// footprint when it fits the reservation.
-template <typename T, typename LT, bool ALIGNED, int DISP>
-__device__ __forceinline__ void fwd_tile_disp(JobPtr Jp, const Box &B0, const Tiling &TL,
-                                              int32_t lds_cells, uint8_t *s_lds)
-{
-    const FwdJob &J = *(const FwdJob *)reload(Jp);
-    Box B = B0;
-    __shared__ int s_red[kThreads / 64][6];
-    const int zr = threadIdx.x & ((1 << (TL.lz - 2)) - 1);
-    const int rr = threadIdx.x >> (TL.lz - 2);
-    const int x = B.x0 + (rr >> TL.ly), y = B.y0 + (rr & ((1 << TL.ly) - 1)), z = B.z0 + 4 * zr;
-    const bool mine = x <= B.x1 && y <= B.y1 && z <= B.z1;
-    const int nvalid = min(4, J.oz - z);
-    float u[3][4];
-    if (DISP == kDispSpline)
-        spline_tile_u<kThreads>(J.ctrl, J.bs, TL.lx, TL.ly, B.x0, B.y0, B.z0, B.x1, B.y1, B.z1, rr,
-                                x, y, z, 1, nvalid, mine, reinterpret_cast<float *>(s_lds), u);
-    const float nf[3] = {(float)J.nx, (float)J.ny, (float)J.nz};
-    RunQ Q;
-    int fmn[3] = {INT_MAX, INT_MAX, INT_MAX}, fmx[3] = {INT_MIN, INT_MIN, INT_MIN};
-    if (mine) {
-        gconst<float> *disp = gc<float>(J.disp);
-        const int32_t nvox = J.ox * J.oy * J.oz;
-        const int32_t v0 = (x * J.oy + y) * J.oz + z;
-        float rb[3];
-        row_base(J.M, (float)x, (float)y, rb);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            if (k >= nvalid)
-                break;
-            const float zf = (float)(z + k);
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                Q.q[i][k] = guard_coord(
-                    coord(J.M, i, rb, zf) +
-                        (DISP == kDispField ? disp[i * nvox + v0 + k] : u[i][k]),
-                    nf[i]);
-                const int f = flr_i32(Q.q[i][k]);
-                fmn[i] = min(fmn[i], f);
-                fmx[i] = max(fmx[i], f);
-            }
-        }
-    }
-    block_minmax3(fmn, fmx, s_red);
-    // the footprint: cells fmn .. fmx + 1 per axis, within [-2, n + 2)
-    TileGeom G;
-    int64_t cells = 1;
-    bool outside = J.nx == 0 || J.ny == 0 || J.nz == 0;
-    const int n[3] = {J.nx, J.ny, J.nz};
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        G.lo[i] = __builtin_amdgcn_readfirstlane(fmn[i]);
-        G.e[i] = __builtin_amdgcn_readfirstlane(fmx[i]) - G.lo[i] + 2;
-        outside = outside || G.lo[i] >= n[i] || G.lo[i] + G.e[i] <= 0;
-        if (i == 2) {
-            G.quads = (G.e[2] + 3) >> 2;
-            G.pitch = lds_pitch(G.e[2]);
-        }
-        cells *= i == 2 ? G.pitch : G.e[i];
-    }
-    G.cls = kBoundary;
-    int path = outside ? kPathOutside : kPathDirectBoundary;
-    if (!outside && cells <= lds_cells && (sizeof(LT) == 4 || (J.flags & kFlagFillInT))) {
-        path = kPathLdsBoundary;
-        stage_footprint<T, LT>(J, make_src<T>(J), G, reinterpret_cast<LT *>(s_lds));
-        B.sy = G.pitch * (int)sizeof(LT);
-        B.sx = G.e[1] * B.sy;
-        B.c0 = -(G.lo[0] * B.sx + G.lo[1] * B.sy + G.lo[2] * (int)sizeof(LT));
-        __syncthreads();
-    }
-    run_box<T, LT, ALIGNED, DISP>(Jp, B, path, TL, s_lds, Q);
-    __syncthreads();                   // LDS is reused by the next tile
-}
-
 // The quads (4 cells of a row) of a footprint window that this thread copies: quad
 // ql of rows row0, row0 + rpp, ... (mine of them), (cx, cy) the plane and row of the
 // first within the window.  The windows of a job's sub-tiles have the same
-// extents, so this is laid out once per tile.
+// extents, so this is laid out once per tile.  NT threads take part.
 constexpr int kStageChunk = 4;
 struct StageWalk {
     int row0, ql, cx, cy, mine;
     int rpp, step_x, step_y, passes;   // uniform; rpp = step_x ey + step_y
 };
 
-__device__ __forceinline__ StageWalk stage_walk(int rows, int ey, int quads)
+template <int NT> __device__ __forceinline__ StageWalk stage_walk(int rows, int ey, int quads)
 {
     StageWalk W;
     W.row0 = W.ql = W.cx = W.cy = W.mine = W.step_x = W.step_y = 0;
     W.passes = 0;
-    W.rpp = __builtin_amdgcn_readfirstlane(div_small(kAffineThreads, quads, 1.0f / (float)quads));
+    W.rpp = __builtin_amdgcn_readfirstlane(div_small(NT, quads, 1.0f / (float)quads));
     if (W.rpp == 0)
         return W;
     W.passes = __builtin_amdgcn_readfirstlane(
@@ -396,21 +319,26 @@ __device__ __forceinline__ void store_shifted(const LT (&c)[4], int s, bool ok, 
 // took as long: lines fetched count, not round trips, and the registers cost a
 // wave per SIMD).  Quads that no sample of the box can use are not loaded
 // (FwdJob::reach; their cells are never read): a rotated box fills about half of
-// its window.  That took the 16-volume batch from 250 to 237 us.
+// its window (CLIP; displaced boxes copy every quad).  That took the 16-volume
+// batch from 250 to 237 us.
 // inside: the window (whole quads) lies in the volume.  Otherwise each quad is
 // loaded from the nearest place inside the volume (of at least 4 cells along
 // z), and its cells outside the volume become fill as they are written.
-template <typename T, typename LT>
+template <typename T, typename LT, bool CLIP>
 __device__ __forceinline__ void stage_window(const FwdJob &J, const Src &S, const StageWalk &W,
                                              const int (&lo)[3], const float (&g)[3], int ey,
                                              int pitch, bool inside, uint8_t *s_lds)
 {
     constexpr int N = kStageChunk;
     const float zq = (float)(4 * W.ql) + 1.5f;
-    const float gz[3] = {__builtin_fmaf(J.inv[2], zq, g[0]), __builtin_fmaf(J.inv[5], zq, g[1]),
-                         __builtin_fmaf(J.inv[8], zq, g[2])};
+    float gz[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+        gz[k] = CLIP ? __builtin_fmaf(J.inv[3 * k + 2], zq, g[k]) : 0.0f;
     // whether a sample of the box can use the quad at row (cx, cy) of the window
     auto reach = [&](int cx, int cy) {
+        if (!CLIP)
+            return true;
         const float fx = (float)cx, fy = (float)cy;
         bool r = true;
 #pragma unroll
@@ -491,6 +419,99 @@ __device__ __forceinline__ void stage_window(const FwdJob &J, const Src &S, cons
     }
 }
 
+// Displacement tile (ALIGNED, LT: see fwd_tile_affine).  A displacement has no
+// a-priori footprint bound: the tile (one run of 4 z voxels per thread)
+// computes its coordinates once, reduces their cells, and stages that
+// footprint when it fits the reservation, as affine windows are (bulk loads;
+// row by row with tests the 256^3 B-spline warp took 160 us, so 139).
+template <typename T, typename LT, bool ALIGNED, int DISP>
+__device__ __forceinline__ void fwd_tile_disp(JobPtr Jp, const Box &B0, const Tiling &TL,
+                                              int32_t lds_cells, uint8_t *s_lds)
+{
+    const FwdJob &J = *(const FwdJob *)reload(Jp);
+    Box B = B0;
+    __shared__ __attribute__((aligned(16))) int s_red[6][kThreads / 64];
+    const int zr = threadIdx.x & ((1 << (TL.lz - 2)) - 1);
+    const int rr = threadIdx.x >> (TL.lz - 2);
+    const int x = B.x0 + (rr >> TL.ly), y = B.y0 + (rr & ((1 << TL.ly) - 1)), z = B.z0 + 4 * zr;
+    const bool mine = x <= B.x1 && y <= B.y1 && z <= B.z1;
+    const int nvalid = min(4, J.oz - z);
+    float u[3][4];
+    if (DISP == kDispSpline)
+        spline_tile_u(J.ctrl, J.bs, B.x0, B.y0, B.z0, B.x1, B.y1, B.z1, x, y, z, 1, nvalid, mine,
+                      reinterpret_cast<float *>(s_lds), u);
+    const float nf[3] = {(float)J.nx, (float)J.ny, (float)J.nz};
+    RunQ Q;
+    int fmn[3] = {INT_MAX, INT_MAX, INT_MAX}, fmx[3] = {INT_MIN, INT_MIN, INT_MIN};
+    if (mine) {
+        gconst<float> *disp = gc<float>(J.disp);
+        const int32_t nvox = J.ox * J.oy * J.oz;
+        const int32_t v0 = (x * J.oy + y) * J.oz + z;
+        float rb[3];
+        row_base(J.M, (float)x, (float)y, rb);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (k >= nvalid)
+                break;
+            const float zf = (float)(z + k);
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                Q.q[i][k] = guard_coord(
+                    coord(J.M, i, rb, zf) +
+                        (DISP == kDispField ? disp[i * nvox + v0 + k] : u[i][k]),
+                    nf[i]);
+                const int f = flr_i32(Q.q[i][k]);
+                fmn[i] = min(fmn[i], f);
+                fmx[i] = max(fmx[i], f);
+            }
+        }
+    }
+    block_minmax3(fmn, fmx, s_red);
+    // the footprint: cells fmn .. fmx + 1 per axis, within [-2, n + 2)
+    const int n[3] = {J.nx, J.ny, J.nz};
+    int lo[3], e[3];
+    bool outside = J.nx == 0 || J.ny == 0 || J.nz == 0, inside = true;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        lo[i] = fmn[i];
+        e[i] = fmx[i] - fmn[i] + 2;
+        outside = outside || lo[i] >= n[i] || lo[i] + e[i] <= 0;
+        inside = inside && lo[i] >= 0 && lo[i] + e[i] <= n[i];
+    }
+    const int quads = (e[2] + 3) >> 2, pitch = lds_pitch(e[2]);
+    const int64_t cells = (int64_t)e[0] * e[1] * pitch;
+    int path = outside ? kPathOutside : kPathDirectBoundary;
+    if (!outside && cells <= lds_cells && (sizeof(LT) == 4 || (J.flags & kFlagFillInT))) {
+        path = inside ? kPathLdsInterior : kPathLdsBoundary;
+        const Src S = make_src<T>(J);
+        // whole quads inside the volume: the window of an inside tile may start earlier
+        const bool whole = inside && 4 * quads <= J.nz;
+        lo[2] = whole ? min(lo[2], J.nz - 4 * quads) : lo[2];
+        const StageWalk W = stage_walk<kThreads>(e[0] * e[1], e[1], quads);
+        if (W.passes > 0 && J.nz >= 4) {
+            const float g[3] = {0.0f, 0.0f, 0.0f};
+            stage_window<T, LT, false>(J, S, W, lo, g, e[1], pitch, whole, s_lds);
+        } else {
+            TileGeom G;
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                G.lo[i] = lo[i];
+                G.e[i] = e[i];
+            }
+            G.quads = quads;
+            G.pitch = pitch;
+            G.cls = kBoundary;
+            stage_footprint<T, LT>(J, S, G, reinterpret_cast<LT *>(s_lds));
+        }
+        B.sy = pitch * (int)sizeof(LT);
+        B.sx = e[1] * B.sy;
+        B.c0 = -(lo[0] * B.sx + lo[1] * B.sy + lo[2] * (int)sizeof(LT));
+        __syncthreads();
+    }
+    run_box<T, LT, ALIGNED, DISP>(Jp, B, path, TL, s_lds, Q);
+    __syncthreads();                   // LDS is reused by the next tile
+}
+
 // Affine tile, processed as sub-tiles of the job's sub-tile shape (the whole
 // tile unless its footprint would not fit the LDS reservation).  LT: type of
 // the LDS footprint cells (FP32, or int16 for int16 inputs).  ALIGNED: the
@@ -556,7 +577,7 @@ __device__ __forceinline__ void fwd_tile_affine(JobPtr Jp, const Box &B0, const 
         todo = (uint32_t)__ballot(lane < nsub && bx <= B0.x1 && by <= B0.y1 && bz <= B0.z1);
         W.passes = 0;
         if (e[0] != 0 && __any(cls != kOutside)) {
-            W = stage_walk(e[0] * e[1], e[1], quads);
+            W = stage_walk<kAffineThreads>(e[0] * e[1], e[1], quads);
             fast = W.passes > 0 && J.nz >= 4;
         }
     }
@@ -595,7 +616,7 @@ __device__ __forceinline__ void fwd_tile_affine(JobPtr Jp, const Box &B0, const 
                     __int_as_float(__builtin_amdgcn_readlane(__float_as_int(g[0]), i)),
                     __int_as_float(__builtin_amdgcn_readlane(__float_as_int(g[1]), i)),
                     __int_as_float(__builtin_amdgcn_readlane(__float_as_int(g[2]), i))};
-                stage_window<T, LT>(J, S, W, l, gi, e1, pitch, c == kInterior, s_lds);
+                stage_window<T, LT, true>(J, S, W, l, gi, e1, pitch, c == kInterior, s_lds);
             } else {
                 TileGeom G;
 #pragma unroll
@@ -923,8 +944,10 @@ static void launch_single_t(const FwdJob &J, const Tiling &TL, int ntiles, int32
 }
 
 static_assert(1 << (3 + 3 + 4 - 2) == kThreads, "one run of a displacement tile per thread");
-static_assert(2 * kDispLdsCells >= kSplineTileLdsFloats * (int32_t)sizeof(float),
-              "the B-spline scratch of a tile fits its smallest footprint reservation");
+static_assert(kDispTiling.lx == 3 && kDispTiling.ly == 3 && kDispTiling.lz == 4 && kThreads == 256,
+              "the tile of spline_tile_u");
+static_assert(kDispLdsCells >= kSplineTileLdsFloats,
+              "the B-spline scratch of a tile fits its footprint reservation");
 
 // Labels alone: one thread per run of 4 output voxels along z (one packed
 // 4-byte store with kFlagVec), the coordinate and the nearest-neighbour gather
@@ -991,6 +1014,26 @@ hipError_t launch_warp_labels(const FwdJob &J, hipStream_t s)
     return hipGetLastError();
 }
 
+// LDS cells for a displacement warp: the window of a tile under the affine part
+// alone with two more cells per axis for the field's own variation, between the
+// B-spline scratch and kDispLdsCells.  Tiles past it gather from memory; a gentle
+// map leaves room for more workgroups (256^3 B-spline warps: 106 to 137 us at
+// 7152 cells by the draw, 137 to 140 at 10224).
+static int32_t disp_cells(const FwdJob &J)
+{
+    const int t[3] = {1 << kDispTiling.lx, 1 << kDispTiling.ly, 1 << kDispTiling.lz};
+    double cells = 1.0;
+    for (int i = 0; i < 3; ++i) {
+        double span = 2.0 * (double)J.delta[i];
+        for (int j = 0; j < 3; ++j)
+            span += std::fabs((double)J.M[4 * i + j]) * (double)(t[j] - 1);
+        const double e = std::min(std::floor(span) + 5.0, 16384.0);
+        cells *= i == 2 ? (double)lds_pitch((int32_t)e) : e;
+    }
+    const int32_t least = (kSplineTileLdsFloats + 15) & ~15;
+    return (int32_t)std::min(std::max(cells, (double)least), (double)kDispLdsCells);
+}
+
 hipError_t launch_warp_single(const FwdJob &J0, const Tiling &TL0, hipStream_t s)
 {
     FwdJob Js = J0;
@@ -1007,7 +1050,7 @@ hipError_t launch_warp_single(const FwdJob &J0, const Tiling &TL0, hipStream_t s
         return hipSuccess;
     const int grid = 8 * xcd_slots(ntiles);
     const int32_t esz = (J.flags & kFlagLds16) ? 2 : 4;
-    const int32_t bound = displaced ? kDispLdsCells : footprint_cells_bound(J, TL);
+    const int32_t bound = displaced ? disp_cells(J) : footprint_cells_bound(J, TL);
     int32_t cells = lds_cells_for(displaced ? bound : std::min(bound, kAffineLdsCells), esz);
     if (!choose_subtile(Js, TL, cells)) {
         cells = lds_cells_for(bound, esz);
