@@ -224,6 +224,12 @@ __device__ __forceinline__ int32_t mad_i24(int32_t a, int32_t s, int32_t c)
     return r;
 }
 
+// at byte offset off + base (base uniform)
+__device__ __forceinline__ int8_t load_i8_at(rsrc_t r, uint32_t off, uint32_t base)
+{
+    return (int8_t)__builtin_amdgcn_raw_buffer_load_b8(r, off, base, 0);
+}
+
 // 24-bit multiply (full rate); operands and product must stay below 2^24 / 2^32.
 __device__ __forceinline__ uint32_t mul24(uint32_t a, uint32_t b) { return __umul24(a, b); }
 
