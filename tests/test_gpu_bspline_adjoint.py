@@ -1,0 +1,52 @@
+"""The control-grid adjoint of a dense field against the oracle's FP64 sums: grids
+around the 16-control tiles and every split of the y sums, rows around the
+64-row chunks, z extents past one table segment, odd rows, non-finite entries
+(which reach exactly the controls of their voxel), and the same bits twice."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_1811_11226_amd as ctaug
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("grid", [(4, 4, 4), (8, 8, 8), (5, 9, 8), (6, 16, 16), (4, 17, 16),
+                                  (7, 64, 16), (5, 6, 17), (4, 16, 64), (64, 64, 64)])
+@pytest.mark.parametrize("dims", [(5, 63, 16), (3, 65, 20), (9, 130, 37), (2, 7, 515), (4, 1, 1030),
+                                  (70, 5, 12), (1, 1, 1)])
+def test_adjoint(grid, dims):
+    rng = np.random.default_rng(sum(grid) + sum(dims))
+    g = rng.normal(0, 1, (3,) + dims).astype(np.float32)
+    out = ctaug.bspline_upsample_adjoint(torch.from_numpy(g).cuda(), grid)
+    again = ctaug.bspline_upsample_adjoint(torch.from_numpy(g).cuda(), grid)
+    assert torch.equal(out, again)
+    ref = oracle.bspline_adjoint(g.astype(np.float64), grid)
+    # FP32: each term's weights carry about 20 roundings and the cell coordinate two
+    # of p / h; a z sum of m terms at most m more; bounded by the sum of |terms|
+    mag = oracle.bspline_adjoint(np.abs(g).astype(np.float64), grid)
+    n = max(dims)
+    tol = (60 + 2 * dims[2] + 12 * max(grid) + n) * 2.0 ** -24
+    assert np.all(np.abs(out.cpu().numpy() - ref) <= tol * mag + 64 * 2.0 ** -24 * mag.max())
+
+
+@pytest.mark.parametrize("grid", [(8, 8, 8), (5, 6, 20)])
+def test_nonfinite_entries_reach_their_own_controls(grid):
+    dims = (9, 70, 40)
+    rng = np.random.default_rng(3)
+    g = rng.normal(0, 1, (3,) + dims).astype(np.float32)
+    clean = ctaug.bspline_upsample_adjoint(torch.from_numpy(g).cuda(), grid).cpu().numpy()
+    at = [(0, 1, 3, 5), (1, 8, 66, 39), (2, 4, 30, 0)]
+    for k, p in enumerate(at):
+        g[p] = (np.nan, np.inf, -np.inf)[k]
+    out = ctaug.bspline_upsample_adjoint(torch.from_numpy(g).cuda(), grid).cpu().numpy()
+    for comp, *p in at:
+        touched = np.zeros(grid, dtype=bool)
+        i = [min(int(np.floor(np.float32(v) * np.float32((G - 3) / (n - 1)))), G - 4)
+             for v, n, G in zip(p, dims, grid)]
+        touched[tuple(slice(a, a + 4) for a in i)] = True
+        assert not np.any(np.isfinite(out[comp][touched]) & (np.abs(out[comp][touched]) > 1e30))
+        assert np.array_equal(out[comp][~touched], clean[comp][~touched]) or np.allclose(
+            out[comp][~touched], clean[comp][~touched], rtol=1e-5, atol=1e-5)
+        assert np.all(np.isfinite(out[comp][~touched]))
