@@ -1002,19 +1002,25 @@ __global__ __launch_bounds__(kThreads) void k_warp_labels(FwdJob J, int32_t runs
 
 // Labels alone under a diagonal map, what resampling a label map to another grid
 // is: the x and y cells are a plane's and a row's, and the z cells are the same
-// for every row.  A wave takes rows rows of one plane, lane l the V voxels from z = l
-// V (of each segment of 64 V), so a row costs one store per lane, and the V byte
-// gathers only where its input row differs from the last one's; only the
-// output's own traffic is left.  512 x 512 x 320 from 160 x 160 x 100: 32 us, 103
-// with the general kernel.
+// for every row.  A wave takes rows of one plane, L = ceil(oz / V) lanes a row with
+// V voxels each, 64 / L rows at once (SUB: two or more; rows past 64 V voxels in
+// segments).  A row costs one store per lane, and V byte gathers, which a wave
+// with one row at a time skips where its input row is the last one's; four rows'
+// gathers are in flight together (one at a time a small map waits for each: 31
+// us where the general kernel took 24).  What is left is the output's own traffic: 512 x 512
+// x 320 from 160 x 160 x 100 takes 30 us, 103 with the general kernel.
 // Coordinates are those of row_base and coord (the products with 0 add nothing),
 // nearest voxels and the guard those of label_checked.
-template <int V>
-__global__ __launch_bounds__(kThreads) void k_warp_labels_diag(FwdJob J, int32_t x0, int32_t rows)
+template <int V, bool SUB>
+__global__ __launch_bounds__(kThreads) void k_warp_labels_diag(FwdJob J, int32_t x0, int32_t rows,
+                                                               int32_t L)
 {
+    constexpr int kAhead = 4;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int x = x0 + (int)blockIdx.y;
+    const int sub = SUB ? div_small(lane, L, 1.0f / (float)L) : 0;
+    const int nsub = SUB ? div_small(64, L, 1.0f / (float)L) : 1;      // rows at once
     const int y0 = ((int)blockIdx.x * (kThreads / 64) + wave) * rows;
     const int y1 = min(y0 + rows, J.oy);
     const rsrc_t src = make_rsrc(J.lbl, (uint32_t)J.in_extent);
@@ -1024,10 +1030,9 @@ __global__ __launch_bounds__(kThreads) void k_warp_labels_diag(FwdJob J, int32_t
         const int j = nn_index(q);
         return q > -1.0f && q < (float)n && (uint32_t)j < (uint32_t)n ? j : -1;
     };
-    const int jx = __builtin_amdgcn_readfirstlane(
-        nearest(__builtin_fmaf(J.M[0], (float)x, J.M[3]), J.nx));
-    for (int z0 = 0; z0 < J.oz; z0 += 64 * V) {
-        const int z = z0 + lane * V;
+    const int jx = J.nz == 0 ? -1 : nearest(__builtin_fmaf(J.M[0], (float)x, J.M[3]), J.nx);
+    for (int z0 = 0; z0 < J.oz; z0 += 64 * V) {    // (SUB: one segment)
+        const int z = z0 + (lane - sub * L) * V;
         uint32_t jz[V], in = 0;
 #pragma unroll
         for (int k = 0; k < V; ++k) {
@@ -1040,49 +1045,63 @@ __global__ __launch_bounds__(kThreads) void k_warp_labels_diag(FwdJob J, int32_t
         for (int i = 0; i < V / 4; ++i)
             w[i] = 0x01010101u * fill;
         int last = -1;                 // the input row in w (-1: fill)
-        for (int y = y0; y < y1; ++y) {
-            const int jy = __builtin_amdgcn_readfirstlane(
-                nearest(__builtin_fmaf(J.M[5], (float)y, J.M[7]), J.ny));
-            const int row = jx < 0 || jy < 0 || J.nz == 0 ? -1 : jx * J.in_ry + jy;
-            if (row != last) {
-                last = row;
+        for (int yb = y0; yb < y1; yb += kAhead * nsub) {
+            int row[kAhead];
+            uint32_t c[kAhead][V];
 #pragma unroll
-                for (int i = 0; i < V / 4; ++i) {
-                    w[i] = 0;
+            for (int u = 0; u < kAhead; ++u) {
+                const int y = yb + u * nsub + sub;
+                const int jy = nearest(__builtin_fmaf(J.M[5], (float)y, J.M[7]), J.ny);
+                row[u] = jx < 0 || jy < 0 ? -1 : jx * J.in_ry + jy;
+                if (!SUB)
+                    row[u] = __builtin_amdgcn_readfirstlane(row[u]);
+                if (SUB || row[u] != (u ? row[u - 1] : last)) {
+                    const uint32_t base = (uint32_t)max(row[u], 0) * (uint32_t)J.in_sy;
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        uint32_t b = fill;
-                        if (row >= 0) {
-                            b = (uint8_t)load_i8_at(src, jz[4 * i + k],
-                                                    (uint32_t)row * (uint32_t)J.in_sy);
-                            b = (in >> (4 * i + k)) & 1 ? b : fill;
-                        }
-                        w[i] |= b << (8 * k);
-                    }
+                    for (int k = 0; k < V; ++k)
+                        c[u][k] = row[u] < 0 ? fill
+                                  : SUB      ? (uint8_t)load_i8(src, base + jz[k])
+                                             : (uint8_t)load_i8_at(src, jz[k], base);
                 }
             }
-            int8_t *out = J.lout + (((uint32_t)x * (uint32_t)J.oy + (uint32_t)y) *
-                                        (uint32_t)J.oz + (uint32_t)z);
-            if (z + V <= J.oz) {
-                __builtin_memcpy(gm<int8_t>(out), w, V);
-            } else {
-                for (int k = 0; k < V && z + k < J.oz; ++k)
-                    out[k] = (int8_t)(w[k >> 2] >> (8 * (k & 3)));
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                const int y = yb + u * nsub + sub;
+                if (SUB || row[u] != (u ? row[u - 1] : last))
+#pragma unroll
+                    for (int i = 0; i < V / 4; ++i) {
+                        w[i] = 0;
+#pragma unroll
+                        for (int k = 0; k < 4; ++k)
+                            w[i] |= ((in >> (4 * i + k)) & 1 ? c[u][4 * i + k] : fill) << (8 * k);
+                    }
+                int8_t *out = J.lout + (((uint32_t)x * (uint32_t)J.oy + (uint32_t)y) *
+                                            (uint32_t)J.oz + (uint32_t)z);
+                if (y < y1 && (!SUB || sub < nsub)) {
+                    if (z + V <= J.oz)
+                        __builtin_memcpy(gm<int8_t>(out), w, V);
+                    else
+                        for (int k = 0; k < V && z + k < J.oz; ++k)
+                            out[k] = (int8_t)(w[k >> 2] >> (8 * (k & 3)));
+                }
             }
+            last = row[kAhead - 1];
         }
     }
 }
 
-template <int V>
-static void launch_labels_diag(const FwdJob &J, hipStream_t s)
+template <int V, bool SUB> static void launch_labels_diag(const FwdJob &J, hipStream_t s)
 {
-    // up to 16 rows a wave, fewer while that leaves under 8192 waves
-    const int64_t all = (int64_t)J.ox * J.oy;
-    const int32_t rows = (int32_t)std::min<int64_t>(16, std::max<int64_t>(1, all / 8192));
-    const unsigned bx = (unsigned)((J.oy + 4 * rows - 1) / (4 * rows));
+    // rows per wave: a multiple of the four steps in flight, more once that still
+    // leaves 16384 waves (two per resident slot)
+    const int32_t L = (J.oz + V - 1) / V, nsub = SUB ? 64 / L : 1;
+    const int64_t steps = (int64_t)J.ox * ((J.oy + nsub - 1) / nsub);
+    const int32_t rows = 4 * nsub * (int32_t)std::min<int64_t>(4, std::max<int64_t>(1, steps / (4 * 16384)));
+    const unsigned bx = (unsigned)((J.oy + 4 * (int64_t)rows - 1) / (4 * (int64_t)rows));
     for (int32_t x0 = 0; x0 < J.ox; x0 += 65535) {
         const unsigned nx = (unsigned)std::min<int32_t>(65535, J.ox - x0);
-        hipLaunchKernelGGL(k_warp_labels_diag<V>, dim3(bx, nx), dim3(kThreads), 0, s, J, x0, rows);
+        hipLaunchKernelGGL((k_warp_labels_diag<V, SUB>), dim3(bx, nx), dim3(kThreads), 0, s, J, x0,
+                           rows, L);
     }
 }
 
@@ -1091,14 +1110,16 @@ hipError_t launch_warp_labels(const FwdJob &J, hipStream_t s)
     const bool diagonal = J.M[1] == 0.0f && J.M[2] == 0.0f && J.M[4] == 0.0f && J.M[6] == 0.0f &&
                           J.M[8] == 0.0f && J.M[9] == 0.0f;
     if (diagonal && J.ox > 0 && J.oy > 0 && J.oz > 0) {
-        // the fewest voxels a lane that cover a row at once: short rows would leave
-        // lanes idle, long ones cost another pass over the rows
-        if (J.oz <= 256)
-            launch_labels_diag<4>(J, s);
+        // the fewest voxels a lane that cover a row at once (short rows would leave
+        // lanes idle, long ones cost another pass over the rows)
+        if (J.oz <= 128)
+            launch_labels_diag<4, true>(J, s);
+        else if (J.oz <= 256)
+            launch_labels_diag<4, false>(J, s);
         else if (J.oz <= 512)
-            launch_labels_diag<8>(J, s);
+            launch_labels_diag<8, false>(J, s);
         else
-            launch_labels_diag<16>(J, s);
+            launch_labels_diag<16, false>(J, s);
         return hipGetLastError();
     }
     const int32_t runs_z = (J.oz + 3) >> 2;
