@@ -79,7 +79,7 @@ __device__ __forceinline__ float bs_profile(const float *__restrict__ ctrl, cons
 
 // Displacement of one thread's run of a tile of 8 x 8 rows (x, y) by 16 voxels
 // along z, evaluated from the control grid by a workgroup of 256 threads:
-// thread t has row t >> 2 (x = x0 + (row >> 3), y = y0 + (row & 7)) and the voxels z + k
+// thread tid has row tid >> 2 (x = x0 + (row >> 3), y = y0 + (row & 7)) and the voxels z + k
 // zstep, k < nvalid, of the tile (z1 - z0 < 16).  With at most kSplineWindow
 // controls per axis in the tile's window, the sums of bs_profile are shared: the
 // window C[a][b][c] and the weights of the tile's 8 + 8 + 16 positions go to LDS,
@@ -101,7 +101,7 @@ template <bool PER_VOXEL = true>
 __device__ __forceinline__ void spline_tile_u(const float *__restrict__ ctrl, const BsplineGeom &B,
                                               int x0, int y0, int z0, int x1, int y1, int z1,
                                               int x, int y, int z, int zstep, int nvalid,
-                                              bool mine, float *s_prof, float (&u)[3][4])
+                                              bool mine, int tid, float *s_prof, float (&u)[3][4])
 {
     typedef float f32x4 __attribute__((ext_vector_type(4)));
     float *Wc = s_prof;                            // [a][comp][b][c]
@@ -109,8 +109,8 @@ __device__ __forceinline__ void spline_tile_u(const float *__restrict__ ctrl, co
     float *P = S + 3 * kSplineWindow * 64;         // [x][comp][y][c]
     f32x4 *T = reinterpret_cast<f32x4 *>(P + 3 * 8 * 64);  // weights: 8 x, 8 y, 16 z
     int *I = reinterpret_cast<int *>(T + 32);      // their cells, from the window's first
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
     // position pos of the 32: its cell in lane pos (and pos + 32) of every wave
     const int pos = lane & 31;
@@ -155,7 +155,6 @@ __device__ __forceinline__ void spline_tile_u(const float *__restrict__ ctrl, co
                 }
             }
             __syncthreads();
-#pragma unroll
             for (int xr = wave; xr < 8; xr += 4) {
                 const f32x4 Bx = T[xr];
                 const float *sp = S + I[xr] * (3 * 64) + lane;
@@ -177,7 +176,7 @@ __device__ __forceinline__ void spline_tile_u(const float *__restrict__ ctrl, co
         __syncthreads();
         if (!mine)
             return;
-        const int row = threadIdx.x >> 2;
+        const int row = tid >> 2;
         const float *pr = P + (row >> 3) * (3 * 64) + (row & 7) * 8;
         f32x4 Bz[4];
         int iz[4];

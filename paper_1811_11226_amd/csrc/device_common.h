@@ -20,20 +20,23 @@ constexpr int kMaxLdsBytes = 61440;    // LDS footprint reservation per workgrou
 
 // XCD-aware tile order.  Consecutive workgroup ids are dispatched round-robin
 // over the 8 XCDs, so workgroup b runs on XCD b % 8.  Tiles are dealt to the
-// XCDs in chunks of 2^kXcdChunkLog consecutive tiles, round-robin, and the
+// XCDs in chunks of 2^kXcdChunkLog consecutive tiles, eight chunks a round, and the
 // workgroups of an XCD take its tiles in increasing order: each XCD (and its
 // L2) gets spatially coherent runs of tiles from every part of the grid, so
-// that jobs of uneven cost spread over all XCDs.  Slot i of XCD x holds tile
-// xcd_tile(x, i); tiles increase with i, and xcd_slots(n) slots per XCD cover
-// n tiles.
-constexpr int kXcdChunkLog = 6;
-__host__ __device__ __forceinline__ int xcd_tile(int xcd, int i)
+// that jobs of uneven cost spread over all XCDs.  Round r starts at XCD 3 r: where
+// eight chunks make up a plane of tiles, every XCD would else get the same band
+// of every plane (256^3 B-spline adjoint 385 -> 371 us).  Slot i of XCD x holds
+// tile xcd_tile(x, i); tiles increase with i, and xcd_slots(n) slots per XCD
+// cover n tiles.  LOG: of a chunk, also of items that hold several tiles.
+constexpr int kXcdChunkLog = 5;
+template <int LOG = kXcdChunkLog> __host__ __device__ __forceinline__ int xcd_tile(int xcd, int i)
 {
-    return ((((i >> kXcdChunkLog) << 3) + xcd) << kXcdChunkLog) + (i & ((1 << kXcdChunkLog) - 1));
+    const int r = i >> LOG;
+    return (((r << 3) + ((xcd + 3 * r) & 7)) << LOG) + (i & ((1 << LOG) - 1));
 }
-__host__ __device__ __forceinline__ int xcd_slots(int n)
+template <int LOG = kXcdChunkLog> __host__ __device__ __forceinline__ int xcd_slots(int n)
 {
-    return ((n + (8 << kXcdChunkLog) - 1) >> (kXcdChunkLog + 3)) << kXcdChunkLog;
+    return ((n + (8 << LOG) - 1) >> (LOG + 3)) << LOG;
 }
 
 // Slots of one persistent workgroup w of an XCD with W workgroups: in round k

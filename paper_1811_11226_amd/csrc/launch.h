@@ -38,6 +38,9 @@ int32_t lds_cells_cap(int32_t elem_bytes);
 int32_t lds_cells_for(int32_t bound, int32_t elem_bytes);
 size_t lds_bytes_for(int32_t cells, int32_t elem_bytes);
 bool choose_subtile(FwdJob &J, const Tiling &TL, int32_t lds_cells);
+// The footprint window of tiles of shape S (FwdJob::box_*, reach; box_e[0] = 0
+// where coordinates are too large for one): its LDS cells.
+int32_t set_window(FwdJob &J, const Tiling &S);
 hipError_t launch_photometric(float *data, int64_t n, int64_t nz, const Photo &P, float occ_lo,
                               float occ_hi, uint32_t vol, uint32_t k0, uint32_t k1, bool vec,
                               hipStream_t s);
@@ -73,7 +76,8 @@ struct BwdJob {
 constexpr int32_t kBwdBatchMax = 8;    // jobs per launch (the table travels in the kernel arguments)
 struct BwdBatch {
     BwdJob jobs[kBwdBatchMax];
-    int32_t prefix[kBwdBatchMax + 1];
+    int32_t prefix[kBwdBatchMax + 1];  // groups of tiles before job j
+    int32_t group_tiles[kBwdBatchMax];
     int32_t fix_bits[kBwdBatchMax];    // per job: 32-bit fixed-point exponent, or -1
     int32_t njobs;
 };

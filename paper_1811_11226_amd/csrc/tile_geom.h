@@ -26,82 +26,13 @@ __device__ __host__ __forceinline__ int lds_pitch(int e)
     return (p & 4) ? p : p + 4;
 }
 
-// Geometry of one output tile, uniform over the workgroup.
+// A footprint window, uniform over the workgroup.
 struct TileGeom {
-    int x0, y0, z0, x1, y1, z1;        // output voxels covered (inclusive)
     int cls;                           // kOutside / kInterior / kBoundary
-    int lo[3], e[3];                   // input cells [lo, lo + e) the tile can touch
+    int lo[3], e[3];                   // input cells [lo, lo + e)
     int quads;                         // 4-cell quads staged per row: ceil(e[2] / 4)
     int pitch;                         // LDS row pitch: 4 * quads, padded to 4 mod 8 cells
-    bool lds;                          // footprint staged in LDS
 };
-
-// Geometry of the output box [x0, x1] x [y0, y1] x [z0, z1] (inclusive).
-__device__ __forceinline__ TileGeom box_geom(const FwdJob &J, int x0, int y0, int z0, int x1,
-                                             int y1, int z1, int32_t lds_cells)
-{
-    TileGeom G;
-    G.x0 = x0;
-    G.y0 = y0;
-    G.z0 = z0;
-    G.x1 = x1;
-    G.y1 = y1;
-    G.z1 = z1;
-    G.lds = false;
-    G.quads = 0;
-    G.pitch = 0;
-    if (J.nx == 0 || J.ny == 0 || J.nz == 0) {
-        G.cls = kOutside;              // empty input: every sample is fill
-        return G;
-    }
-    if (J.disp) {
-        G.cls = kBoundary;             // displacement: per-sample checks, direct gathers
-        return G;
-    }
-    // The coordinate is affine in p: its extremes over the box are the value at
-    // the origin plus the negative / positive parts of A_ij * span_j.  The
-    // margin delta covers FP32 rounding of both this bound and of q itself.
-    const float span[3] = {(float)(G.x1 - G.x0), (float)(G.y1 - G.y0), (float)(G.z1 - G.z0)};
-    float rb[3];
-    row_base(J.M, (float)G.x0, (float)G.y0, rb);
-    const int n[3] = {J.nx, J.ny, J.nz};
-    bool outside = false, interior = true;
-    int cells = 1;
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        const float q0 = coord(J.M, i, rb, (float)G.z0);
-        float dn = 0.0f, up = 0.0f;
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            const float d = J.M[4 * i + j] * span[j];
-            dn += fminf(d, 0.0f);
-            up += fmaxf(d, 0.0f);
-        }
-        const float l = q0 + dn - J.delta[i], h = q0 + up + J.delta[i];
-        outside = outside || (h <= -1.0f) || (l >= (float)n[i]);
-        interior = interior && (l >= 0.0f) && (h < (float)(n[i] - 1));
-        // cells floor(q) .. floor(q) + 1 of every guarded sample, clamped to [-1, n]
-        const int a = (int)fmaxf(floorf(l), -1.0f);
-        const int b = min((int)fminf(floorf(h), (float)n[i]) + 1, n[i]);
-        G.lo[i] = a;
-        G.e[i] = max(b - a + 1, 1);
-    }
-    G.quads = (G.e[2] + 3) >> 2;
-    G.pitch = lds_pitch(G.e[2]);
-    cells = G.e[0] * G.e[1] * G.pitch;
-    G.cls = outside ? kOutside : (interior ? kInterior : kBoundary);
-    // an interior footprint whose last quad would reach past z = nz - 1 starts
-    // its z window earlier (the extra cells are in the volume), so that every
-    // staged quad of an interior tile lies inside the volume
-    if (G.cls == kInterior && 4 * G.quads <= J.nz && G.lo[2] + 4 * G.quads > J.nz) {
-        const int shift = G.lo[2] + 4 * G.quads - J.nz;
-        G.lo[2] -= shift;
-        G.e[2] += shift;
-    }
-    // an int16 footprint must hold fill exactly
-    G.lds = !outside && cells <= lds_cells && (!(J.flags & kFlagLds16) || (J.flags & kFlagFillInT));
-    return G;
-}
 
 __device__ __forceinline__ void store4(float *dst, const float v[4])
 {
@@ -363,6 +294,216 @@ __device__ __forceinline__ void stage_footprint(const FwdJob &J, const Src &S, c
     }
 }
 
+// A job in constant memory (kernel arguments or the batch's table, which no
+// kernel writes): its fields are scalar loads.  reload() hides the pointer's
+// origin, so that a phase's fields are loaded anew there rather than kept in
+// scalar registers through the phases before it (all of them together spill).
+typedef __attribute__((address_space(4))) const FwdJob *JobPtr;
+__device__ __forceinline__ JobPtr reload(JobPtr p)
+{
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
+// A coordinate moved into [-2, n] without changing its sample: at or below -1
+// (and NaN) it goes to -2, at or above n to n.  There every corner is outside the volume,
+// so the trilinear value is fill and the nearest voxel is outside, which is what
+// the guard (-1, n) gives; a footprint of cells within [-2, n + 2), fill where
+// outside the volume, then needs no test per sample.
+__device__ __forceinline__ float guard_coord(float q, float n)
+{
+    return fminf(q > -1.0f ? q : -2.0f, n);
+}
+
+// The quads (4 cells of a row) of a footprint window that this thread copies: quad
+// ql of rows row0, row0 + rpp, ... (mine of them), (cx, cy) the plane and row of the
+// first within the window.  The windows of a job's sub-tiles have the same
+// extents, so this is laid out once per tile.  NT threads take part.
+constexpr int kStageChunk = 4;
+struct StageWalk {
+    int row0, ql, cx, cy, mine;
+    int rpp, step_x, step_y, passes;   // uniform; rpp = step_x ey + step_y
+};
+
+template <int NT> __device__ __forceinline__ StageWalk stage_walk(int rows, int ey, int quads,
+                                                                       int tid)
+{
+    StageWalk W;
+    W.row0 = W.ql = W.cx = W.cy = W.mine = W.step_x = W.step_y = 0;
+    W.passes = 0;
+    W.rpp = __builtin_amdgcn_readfirstlane(div_small(NT, quads, 1.0f / (float)quads));
+    if (W.rpp == 0)
+        return W;
+    W.passes = __builtin_amdgcn_readfirstlane(
+        div_small(rows + W.rpp - 1, W.rpp, 1.0f / (float)W.rpp));
+    W.row0 = div_small(tid, quads, 1.0f / (float)quads);
+    W.ql = tid - W.row0 * quads;
+    const float rcp_y = 1.0f / (float)ey;
+    W.step_x = __builtin_amdgcn_readfirstlane(div_small(W.rpp, ey, rcp_y));
+    W.step_y = W.rpp - W.step_x * ey;
+    W.cx = div_small(W.row0, ey, rcp_y);
+    W.cy = W.row0 - W.cx * ey;
+    W.mine = W.row0 < W.rpp ? (W.row0 + (W.passes - 1) * W.rpp < rows ? W.passes : W.passes - 1)
+                            : 0;
+    return W;
+}
+
+// Four raw cells c loaded from z = zc of a row, of which the quad's cell u is
+// c[s + u] (fill where s + u is not 0 .. 3, or ok is false), written as LDS cells.
+template <typename LT>
+__device__ __forceinline__ void store_shifted(const LT (&c)[4], int s, bool ok, LT fill, LT *dst)
+{
+    LT v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        v[u] = fill;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            v[u] = s + u == j ? c[j] : v[u];
+        v[u] = ok ? v[u] : fill;
+    }
+    store4(dst, v);
+}
+
+// Copies a window into LDS, kStageChunk loads of a thread in flight at once (12
+// took as long: lines fetched count, not round trips, and the registers cost a
+// wave per SIMD).  Quads that no sample of the box can use are not loaded
+// (FwdJob::reach; their cells are never read): a rotated box fills about half of
+// its window (CLIP; displaced boxes copy every quad).  That took the 16-volume
+// batch from 250 to 237 us.
+// inside: the window (whole quads) lies in the volume.  Otherwise each quad is
+// loaded from the nearest place inside the volume (of at least 4 cells along
+// z), and its cells outside the volume become fill as they are written.
+template <typename T, typename LT, bool CLIP>
+__device__ __forceinline__ void stage_window(const FwdJob &J, const Src &S, const StageWalk &W,
+                                             const int (&lo)[3], const float (&g)[3], int ey,
+                                             int pitch, bool inside, uint8_t *s_lds)
+{
+    constexpr int N = kStageChunk;
+    const float zq = (float)(4 * W.ql) + 1.5f;
+    float gz[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+        gz[k] = CLIP ? __builtin_fmaf(J.inv[3 * k + 2], zq, g[k]) : 0.0f;
+    // whether a sample of the box can use the quad at row (cx, cy) of the window
+    auto reach = [&](int cx, int cy) {
+        if (!CLIP)
+            return true;
+        const float fx = (float)cx, fy = (float)cy;
+        bool r = true;
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            r = r && fabsf(__builtin_fmaf(J.inv[3 * k], fx,
+                                          __builtin_fmaf(J.inv[3 * k + 1], fy, gz[k]))) <=
+                         J.reach[k];
+        return r;
+    };
+    constexpr uint32_t kNowhere = 0xffffffffu;     // past the buffer's end: no access, reads 0
+    typename QuadRaw<T>::type w[N];
+    uint32_t l = (uint32_t)(W.row0 * pitch + 4 * W.ql) * (uint32_t)sizeof(LT);
+    const uint32_t step = (uint32_t)(W.rpp * pitch) * (uint32_t)sizeof(LT);
+    int cx = W.cx, cy = W.cy;
+    if (inside) {
+        const int plane = S.ry * S.rsy;                    // elements
+        const uint32_t base = (uint32_t)(lo[0] * plane + lo[1] * S.rsy + lo[2]) *
+                              (uint32_t)sizeof(T);
+        uint32_t o = (uint32_t)(W.cx * plane + cy * S.rsy + 4 * W.ql) * (uint32_t)sizeof(T);
+        const uint32_t d = (uint32_t)(W.step_x * plane + W.step_y * S.rsy) * (uint32_t)sizeof(T);
+        const uint32_t dw = (uint32_t)(plane - ey * S.rsy) * (uint32_t)sizeof(T) + d;
+        for (int p0 = 0; p0 < W.passes; p0 += N) {
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+                w[u] = QuadRaw<T>::load_at(S.img, p0 + u < W.mine && reach(cx, cy) ? o : kNowhere,
+                                           base);
+                const int c = cy + W.step_y;
+                o += c >= ey ? dw : d;
+                cx += c >= ey ? W.step_x + 1 : W.step_x;
+                cy = c >= ey ? c - ey : c;
+            }
+#pragma unroll
+            for (int u = 0; u < N; ++u)
+                if (p0 + u < W.mine)
+                    QuadRaw<T>::store(w[u], reinterpret_cast<LT *>(s_lds + (l + u * step)));
+            l += N * step;
+        }
+        return;
+    }
+    const int gz0 = lo[2] + 4 * W.ql;
+    const int zc = min(max(gz0, 0), J.nz - 4), s = gz0 - zc;
+    const bool shifted = __any(s != 0);
+    const LT fill = (LT)J.fill;
+    for (int p0 = 0; p0 < W.passes; p0 += N) {
+        uint32_t rows_in = 0;
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const int gx = lo[0] + cx, gy = lo[1] + cy;
+            const bool in = (uint32_t)gx < (uint32_t)J.nx && (uint32_t)gy < (uint32_t)J.ny;
+            rows_in |= (in ? 1u : 0u) << u;
+            w[u] = QuadRaw<T>::load_at(
+                S.img,
+                in && p0 + u < W.mine && reach(cx, cy)
+                    ? elem_index(S, gx, gy, zc) * (uint32_t)sizeof(T)
+                    : kNowhere,
+                0);
+            const int c = cy + W.step_y;
+            cx += c >= ey ? W.step_x + 1 : W.step_x;
+            cy = c >= ey ? c - ey : c;
+        }
+#pragma unroll
+        for (int u = 0; u < N; ++u)
+            if (p0 + u < W.mine) {
+                LT c[4];
+                QuadRaw<T>::cells(w[u], c);
+                LT *dst = reinterpret_cast<LT *>(s_lds + (l + u * step));
+                const bool ok = (rows_in >> u) & 1;
+                if (shifted) {
+                    store_shifted<LT>(c, s, ok, fill, dst);
+                } else {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        c[v] = ok ? c[v] : fill;
+                    store4(dst, c);
+                }
+            }
+        l += N * step;
+    }
+}
+
+// Class of the sub-tile of an affine job whose first voxel is (x, y, z), the first
+// cell lo of its window (FwdJob::box_*; inside the volume for an interior one,
+// inside [-2, n + 2) otherwise) and the constants gr of its quad test
+// (stage_window).  Any lane's or a uniform voxel.
+__device__ __forceinline__ int box_window(const FwdJob &J, float x, float y, float z, int (&lo)[3],
+                                          float (&gr)[3])
+{
+    if (J.nx == 0 || J.ny == 0 || J.nz == 0)
+        return kOutside;               // empty input: every sample is fill
+    const int n[3] = {J.nx, J.ny, J.nz};
+    const int e[3] = {J.box_e[0], J.box_e[1], (J.box_e[2] + 3) & ~3};
+    float rb[3], qc[3];
+    row_base(J.M, x, y, rb);
+    bool outside = false, interior = true;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const float q0 = coord(J.M, i, rb, z);
+        qc[i] = q0 + J.box_mid[i];
+        const float l = q0 + J.box_dn[i], h = q0 + J.box_up[i];
+        outside = outside || h <= -1.0f || l >= (float)n[i];
+        interior = interior && l >= 0.0f && h < (float)(n[i] - 1) && e[i] <= n[i];
+        lo[i] = (int)fminf(fmaxf(floorf(l), -2.0f), (float)n[i]);
+    }
+    const int cls = outside ? kOutside : interior ? kInterior : kBoundary;
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+        lo[i] = min(lo[i], cls == kInterior ? n[i] - e[i] : n[i] + 2 - J.box_e[i]);
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+        gr[k] = __builtin_fmaf(J.inv[3 * k], (float)lo[0] - qc[0],
+                               __builtin_fmaf(J.inv[3 * k + 1], (float)lo[1] - qc[1],
+                                              J.inv[3 * k + 2] * ((float)lo[2] - qc[2])));
+    return cls;
+}
+
 // Minimum over the wave, as a scalar: DPP row shifts and broadcasts (one VALU
 // instruction a step; a shuffle goes through LDS), lane 63 holds the result.
 __device__ __forceinline__ int wave_min(int v)
@@ -402,42 +543,6 @@ __device__ __forceinline__ void block_minmax3(int mn[3], int mx[3], int (*s_red)
         const int m = __builtin_amdgcn_readfirstlane(min(min(r.x, r.y), min(r.z, r.w)));
         (i < 3 ? mn[i] : mx[i - 3]) = i < 3 ? m : ~m;
     }
-}
-
-// Footprint of an output box from the range [fmn, fmx] of floor(q) over its
-// guarded samples (fmn > fmx: no guarded sample): cells floor(q) .. floor(q) + 1,
-// clamped to [-1, n].
-__device__ __forceinline__ TileGeom geom_from_cells(const FwdJob &J, int x0, int y0, int z0,
-                                                    int x1, int y1, int z1, const int fmn[3],
-                                                    const int fmx[3], int32_t lds_cells)
-{
-    TileGeom G;
-    G.x0 = x0;
-    G.y0 = y0;
-    G.z0 = z0;
-    G.x1 = x1;
-    G.y1 = y1;
-    G.z1 = z1;
-    G.lds = false;
-    G.quads = 0;
-    G.pitch = 0;
-    if (fmn[0] > fmx[0]) {
-        G.cls = kOutside;
-        return G;
-    }
-    const int n[3] = {J.nx, J.ny, J.nz};
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        const int a = max(fmn[i], -1), b = min(fmx[i] + 1, n[i]);
-        G.lo[i] = a;
-        G.e[i] = b - a + 1;
-    }
-    G.quads = (G.e[2] + 3) >> 2;
-    G.pitch = lds_pitch(G.e[2]);
-    // samples outside the guard may remain: always the per-sample checked path
-    G.cls = kBoundary;
-    G.lds = (int64_t)G.e[0] * G.e[1] * G.pitch <= lds_cells;
-    return G;
 }
 
 }  // namespace ctaug

@@ -45,6 +45,9 @@ namespace ctaug {
 // adjoint accumulators of the same cells.
 constexpr Tiling kBwdTiling = {3, 3, 4};
 constexpr int32_t kBwdLdsCells = 12288;
+// An affine job whose windows need more takes up to this (60 KB, two workgroups
+// per CU) before its tiles fall back to per-corner atomics.
+constexpr int32_t kBwdLdsMax = 15360;
 constexpr int64_t kBwdMaxGrid = kBwdMaxRows;
 
 static int64_t bwd_tiles(int64_t ox, int64_t oy, int64_t oz)
@@ -62,11 +65,21 @@ int64_t bwd_partial_rows(int64_t ox, int64_t oy, int64_t oz)
     return bwd_grid(bwd_tiles(ox, oy, oz));
 }
 
+// Sum over the wave in a fixed order, in lane 63: DPP row shifts and broadcasts (a
+// shuffle goes through LDS; twelve sums of six took about 7000 cycles).
 __device__ __forceinline__ double wave_sum(double v)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1)
-        v += __shfl_xor(v, off, 64);
+#define CTAUG_DPP_ADD(ctrl, rows)                                                                 \
+    v += __hiloint2double(                                                                        \
+        __builtin_amdgcn_update_dpp(0, __double2hiint(v), ctrl, rows, 0xF, true),                 \
+        __builtin_amdgcn_update_dpp(0, __double2loint(v), ctrl, rows, 0xF, true))
+    CTAUG_DPP_ADD(0x111, 0xF);         // row_shr:1, 2, 4, 8: lane 15 of each row of 16
+    CTAUG_DPP_ADD(0x112, 0xF);
+    CTAUG_DPP_ADD(0x114, 0xF);
+    CTAUG_DPP_ADD(0x118, 0xF);
+    CTAUG_DPP_ADD(0x142, 0xA);         // row_bcast:15 into rows 1 and 3
+    CTAUG_DPP_ADD(0x143, 0xC);         // row_bcast:31 into rows 2 and 3
+#undef CTAUG_DPP_ADD
     return v;
 }
 
@@ -168,7 +181,7 @@ __device__ __forceinline__ void spline_weight_entry(int e, int p0, int p1, float
 // guarantees that no thread reads the scratch LDS on entry; ends with a
 // barrier.
 __device__ __forceinline__ void ctrl_adjoint_tile(const BsplineGeom &B, int x0, int y0, int z0,
-                                                  int x1, int y1, int z1, int rr, int zr,
+                                                  int x1, int y1, int z1, int t,
                                                   const float (&gu)[4][3], float *lds, float *acc)
 {
     constexpr int NW = kSplineWindow;
@@ -182,7 +195,7 @@ __device__ __forceinline__ void ctrl_adjoint_tile(const BsplineGeom &B, int x0, 
     static_assert(16 * NW + 16 * NW + 64 * 3 * NW + 8 * 3 * NW * NW + 3 * NW * NW * NW <=
                       kSplineBwdCells,
                   "the tile's contraction scratch fits the footprint reservation");
-    const int t = threadIdx.x;
+    const int rr = t >> 2, zr = t & 3;
     // controls of the tile's window per axis (at most NW): contractions stop
     // there, as every weight beyond is zero and no later stage reads beyond
     const int ixl = bs_index(x0, B.inv_hx, B.gx), iyl = bs_index(y0, B.inv_hy, B.gy),
@@ -266,7 +279,7 @@ __device__ __forceinline__ void write_partial_row(const double (&acc)[12],
 #pragma unroll
     for (int i = 0; i < 12; ++i) {
         const double sum = wave_sum(acc[i]);
-        if (lane == 0)
+        if (lane == 63)
             red[wave][i] = sum;
     }
     __syncthreads();
@@ -279,14 +292,25 @@ __device__ __forceinline__ void write_partial_row(const double (&acc)[12],
     __syncthreads();                   // red is reused by the next row
 }
 
+// Place of tile t in job J's grid of tiles.
+__device__ __forceinline__ void tile_place(const FwdJob &J, int t, int &tx, int &ty, int &tz)
+{
+    const int rest = (int)div_rcp((uint32_t)t, (uint32_t)J.tiles_z, J.rcp_tz);
+    tz = t - rest * J.tiles_z;
+    tx = (int)div_rcp((uint32_t)rest, (uint32_t)J.tiles_y, J.rcp_ty);
+    ty = rest - tx * J.tiles_y;
+}
+
 // The upstream gradient of the calling thread's run in tile t of job J
 // (voxels z0 + zr + 4k of row (x0 + xr, y0 + yr)); 0 past the output.
-__device__ __forceinline__ void load_run_g(const FwdJob &J, const float *__restrict__ g, int t,
-                                           int zr, int yr, int xr, float (&gv)[4])
+__device__ __forceinline__ void load_run_g(JobPtr Jp, const float *__restrict__ g, int t, int tid,
+                                           float (&gv)[4])
 {
+    const int zr = tid & 3, yr = (tid >> 2) & 7, xr = tid >> 5;
+    const FwdJob &J = *(const FwdJob *)reload(Jp);
     const Tiling TL = kBwdTiling;
-    const int tz = t % J.tiles_z, rest = t / J.tiles_z;
-    const int ty = rest % J.tiles_y, tx = rest / J.tiles_y;
+    int tx, ty, tz;
+    tile_place(J, t, tx, ty, tz);
     const int x = (tx << TL.lx) + xr, y = (ty << TL.ly) + yr, z = (tz << TL.lz) + zr;
     const bool row_ok = x < J.ox && y < J.oy;
     const int32_t v0 = row_ok ? (x * J.oy + y) * J.oz + z : 0;
@@ -295,8 +319,79 @@ __device__ __forceinline__ void load_run_g(const FwdJob &J, const float *__restr
         gv[k] = row_ok && z + 4 * k < J.oz ? g[v0 + 4 * k] : 0.0f;
 }
 
+// Largest of the wave's values, as a scalar (DPP, as wave_min).
+__device__ __forceinline__ uint32_t wave_max(uint32_t v)
+{
+#define CTAUG_DPP_MAX(ctrl, rows)                                                                 \
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, ctrl, rows, 0xF, false))
+    CTAUG_DPP_MAX(0x111, 0xF);
+    CTAUG_DPP_MAX(0x112, 0xF);
+    CTAUG_DPP_MAX(0x114, 0xF);
+    CTAUG_DPP_MAX(0x118, 0xF);
+    CTAUG_DPP_MAX(0x142, 0xA);
+    CTAUG_DPP_MAX(0x143, 0xC);
+#undef CTAUG_DPP_MAX
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// Adds the touched accumulators of `planes` window planes from lox (rows of ez
+// cells, ey rows per plane, pitch cells apart in s_acc) to the in-volume cells of
+// g_img, one FP32 global atomic each; conv converts an accumulator.  A row is
+// taken by neighbouring lanes, one cell each (atomics of an instruction on
+// consecutive cells coalesce; lanes 16 bytes apart took twice as long), and rows
+// advance by additions: two divisions per cell were 34 instructions of the 1480 a
+// thread spent on a tile, 19 times.  inside: the window lies in the volume.
+template <typename A, typename F>
+__device__ __forceinline__ void flush_cells(const A *s_acc, int planes, int ey, int ez, int pitch,
+                                            int lox, int loy, int loz, const FwdJob &J,
+                                            bool inside, int tid, float *__restrict__ g_img,
+                                            F conv)
+{
+    const int lpr = min(ez, kThreads);
+    const float rcp_l = 1.0f / (float)lpr, rcp_y = 1.0f / (float)ey;
+    const int rpp = __builtin_amdgcn_readfirstlane(div_small(kThreads, lpr, rcp_l));
+    const int step_x = __builtin_amdgcn_readfirstlane(div_small(rpp, ey, rcp_y));
+    const int step_y = rpp - step_x * ey;
+    int row = div_small(tid, lpr, rcp_l);
+    const int z0 = tid - row * lpr;
+    int cx = div_small(row, ey, rcp_y), cy = row - cx * ey;
+    const int rows = row < rpp ? planes * ey : 0;          // the lanes past the last whole row idle
+    const int d = (step_x * J.ny + step_y) * J.nz, dw = (J.ny - ey) * J.nz + d;
+    int o = ((lox + cx) * J.ny + loy + cy) * J.nz + loz + z0;
+    const A *s = s_acc + (row * pitch + z0);
+    const int step = rpp * pitch;
+    const bool z_in = z0 < ez && (inside || (uint32_t)(loz + z0) < (uint32_t)J.nz);
+    constexpr int kAhead = 4;          // rows whose accumulators are read together
+    for (; row < rows; row += kAhead * rpp) {
+        A v[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+            v[u] = row + u * rpp < rows ? s[u * step] : A(0);
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const bool row_in = inside || ((uint32_t)(lox + cx) < (uint32_t)J.nx &&
+                                           (uint32_t)(loy + cy) < (uint32_t)J.ny);
+            if (v[u] != 0 && row_in && z_in)
+                unsafeAtomicAdd(g_img + o, conv(v[u]));
+            if (ez > kThreads)         // (a window that long has few rows)
+                for (int z = kThreads; z + z0 < ez; z += kThreads)
+                    if (row + u * rpp < rows && row_in &&
+                        (uint32_t)(loz + z0 + z) < (uint32_t)J.nz && s[u * step + z] != 0)
+                        unsafeAtomicAdd(g_img + (o + z), conv(s[u * step + z]));
+            const int c = cy + step_y;
+            const bool wrap = c >= ey;
+            cy = wrap ? c - ey : c;
+            cx += wrap ? step_x + 1 : step_x;
+            o += wrap ? dw : d;
+        }
+        s += kAhead * step;
+    }
+}
+
 // The adjoint of one 8 x 8 x 16 output tile t of job J, for the calling
-// thread's run (voxels z0 + zr + 4k of row (xr, yr)): coordinates, the
+// thread's run (voxels z0 + zr + 4k, k = 0..3, of row (xr, yr): lanes next to each
+// other take neighbouring z, so that the LDS accumulator updates of one
+// instruction fall in different banks): coordinates, the
 // staged footprint, dV/dq and its FP64 parameter sums (into acc), the image
 // adjoint (fixed-point tile sums, flushed with FP32 atomics), the
 // displacement gradient and the control-grid contraction.  gin holds the
@@ -304,62 +399,93 @@ __device__ __forceinline__ void load_run_g(const FwdJob &J, const float *__restr
 // has_next) is loaded into gnext once the image scatter is done, so that its
 // latency hides behind the flush.  Uniform over the workgroup; ends with
 // every LDS read and write of the tile done.
+//
+// Footprints are the forward warps' windows (fill where outside the volume,
+// coordinates through guard_coord): a sample outside the guard reads only fill,
+// so its dV/dq is exactly 0, and voxels past the output take the coordinates of the
+// last one inside it, so no sample branches.
 template <typename T, int DISP, bool NARROW>
-__device__ __forceinline__ void bwd_tile(const FwdJob &J, int t, const Src &src,
-                                         gconst<float> *disp, int32_t nvox, bool empty_in,
-                                         bool want_ctrl, bool need_dv, const float (&gin)[4],
-                                         bool has_next, const FwdJob &Jn,
+__device__ __forceinline__ void bwd_tile(JobPtr Jp, int t, bool want_ctrl, bool need_dv,
+                                         const float (&gin)[4], bool has_next, JobPtr Jn,
                                          const float *__restrict__ gn, int tn, float (&gnext)[4],
                                          float *__restrict__ g_img, float *__restrict__ g_disp,
-                                         float *s_ctrl, int32_t lds_cells, int fix_bits, int zr,
-                                         int yr, int xr, double (&acc)[12], int (*s_red)[kThreads / 64],
-                                         float *s_gmax)
+                                         float *s_ctrl, int32_t lds_cells, int fix_bits,
+                                         double (&acc)[12],
+                                         int (*s_red)[kThreads / 64], uint32_t *s_gmax)
 {
     const Tiling TL = kBwdTiling;
-    const int tz = t % J.tiles_z, rest = t / J.tiles_z;
-    const int ty = rest % J.tiles_y, tx = rest / J.tiles_y;
-    const int x0 = tx << TL.lx, y0 = ty << TL.ly, z0 = tz << TL.lz;
-    const int x1 = min(x0 + (1 << TL.lx), J.ox) - 1, y1 = min(y0 + (1 << TL.ly), J.oy) - 1,
-              z1 = min(z0 + (1 << TL.lz), J.oz) - 1;
-    const int x = x0 + xr, y = y0 + yr, z = z0 + zr;
-    const bool run_ok = x <= x1 && y <= y1 && z <= z1;
+    // the thread's index anew for each tile: what follows from it is then computed where
+    // it is used, not kept (and spilled) across the tiles
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int zr = tid & 3, yr = (tid >> 2) & 7, xr = tid >> 5;
     bool fetched = false;              // gnext loaded (uniform)
-    const int nvalid = run_ok ? min(4, (z1 - z) / 4 + 1) : 0;
-    const int32_t v0 = run_ok ? (x * J.oy + y) * J.oz + z : 0;
-    // coordinates, guard and upstream gradient of the run's voxels
+    int x0, y0, z0, x1, y1, z1;
     float qv[4][3], gpk[4];
-    bool gd[4];
-    float u[3][4];
-    if (DISP == kDispSpline)
-        spline_tile_u<false>(J.ctrl, J.bs, x0, y0, z0, x1, y1, z1, x, y, z, 4, nvalid, run_ok,
-                             s_cells, u);
+    uint32_t live = 0;                 // voxel k of the run is in the output and guarded
+    int cls, lo[3], e[3], pitch;
+    bool lds;
     {
+        const FwdJob &J = *(const FwdJob *)reload(Jp);
+        int tx, ty, tz;
+        tile_place(J, t, tx, ty, tz);
+        x0 = tx << TL.lx;
+        y0 = ty << TL.ly;
+        z0 = tz << TL.lz;
+        x1 = min(x0 + (1 << TL.lx), J.ox) - 1;
+        y1 = min(y0 + (1 << TL.ly), J.oy) - 1;
+        z1 = min(z0 + (1 << TL.lz), J.oz) - 1;
+        float gr[3] = {0.0f, 0.0f, 0.0f};
+        if (DISP == kDispNone) {
+            const int c = box_window(J, (float)x0, (float)y0, (float)z0, lo, gr);
+            cls = __builtin_amdgcn_readfirstlane(c);
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                lo[i] = __builtin_amdgcn_readfirstlane(lo[i]);
+                e[i] = J.box_e[i];
+            }
+            if (cls == kInterior)      // whole quads, of which the last ones may be needed
+                e[2] = (e[2] + 3) & ~3;
+            pitch = J.box_pitch;
+            lds = cls != kOutside && e[0] != 0;
+        }
+        const int x = x0 + xr, y = y0 + yr, z = z0 + zr;
+        const bool row_ok = x <= x1 && y <= y1;
+        const int xc = min(x, x1), yc = min(y, y1);
+        const float nf[3] = {(float)J.nx, (float)J.ny, (float)J.nz};
+        float u[3][4];
+        if (DISP == kDispSpline)
+            spline_tile_u<false>(J.ctrl, J.bs, x0, y0, z0, x1, y1, z1, x, y, z, 4, 4, true, tid,
+                                 s_cells, u);
         float rb[3];
-        row_base(J.M, (float)x, (float)y, rb);
+        row_base(J.M, (float)xc, (float)yc, rb);
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            gd[k] = false;
-            gpk[k] = 0.0f;
-            qv[k][0] = qv[k][1] = qv[k][2] = 0.0f;
-            if (k >= nvalid)
-                continue;
-            const int32_t v = v0 + 4 * k;
-            const float zf = (float)(z + 4 * k);
-            float qx = coord(J.M, 0, rb, zf), qy = coord(J.M, 1, rb, zf),
-                  qz = coord(J.M, 2, rb, zf);
+            const int zc = min(z + 4 * k, z1);
+            const bool valid = row_ok && z + 4 * k <= z1;
+            const float zf = (float)zc;
+            float q[3];
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+                q[i] = coord(J.M, i, rb, zf);
             if (DISP == kDispField) {
-                qx = qx + disp[v];
-                qy = qy + disp[nvox + v];
-                qz = qz + disp[2 * nvox + v];
+                gconst<float> *disp = gc<float>(J.disp);
+                const int32_t nvox = J.ox * J.oy * J.oz;
+                const int32_t v = (xc * J.oy + yc) * J.oz + zc;
+#pragma unroll
+                for (int i = 0; i < 3; ++i)
+                    q[i] = q[i] + disp[i * nvox + v];
             } else if (DISP == kDispSpline) {
-                qx = qx + u[0][k];
-                qy = qy + u[1][k];
-                qz = qz + u[2][k];
+#pragma unroll
+                for (int i = 0; i < 3; ++i)
+                    q[i] = q[i] + u[i][k];
             }
-            qv[k][0] = qx;
-            qv[k][1] = qy;
-            qv[k][2] = qz;
-            gd[k] = !empty_in && in_guard(qx, qy, qz, J.nx, J.ny, J.nz);
+            const bool interior = DISP == kDispNone && cls == kInterior;
+            const bool gd = valid && (interior || in_guard(q[0], q[1], q[2], J.nx, J.ny, J.nz));
+            live |= (gd ? 1u : 0u) << k;
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+                qv[k][i] = interior ? q[i] : guard_coord(q[i], nf[i]);
             // adjoint of the photometric chain without window: the output
             // is gain * V + offset + sigma * n off the occluded slab and
             // does not depend on V on it
@@ -371,306 +497,301 @@ __device__ __forceinline__ void bwd_tile(const FwdJob &J, int t, const Src &src,
             }
             gpk[k] = gv;
         }
-    }
-    TileGeom G;
-    if (DISP != kDispNone) {
-        // no a-priori bound with a displacement field: the footprint is the
-        // range of floor(q) over the tile's guarded samples (block reduction)
-        int fmn[3] = {INT_MAX, INT_MAX, INT_MAX}, fmx[3] = {INT_MIN, INT_MIN, INT_MIN};
+        if (DISP != kDispNone) {
+            // no a-priori bound with a displacement field: the footprint is the
+            // range of the cells of the tile's samples (block reduction)
+            int fmn[3], fmx[3];
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-            if (gd[k])
+            for (int i = 0; i < 3; ++i) {
+                fmn[i] = fmx[i] = flr_i32(qv[0][i]);
 #pragma unroll
-                for (int i = 0; i < 3; ++i) {
-                    const int f = (int)floorf(qv[k][i]);
+                for (int k = 1; k < 4; ++k) {
+                    const int f = flr_i32(qv[k][i]);
                     fmn[i] = min(fmn[i], f);
                     fmx[i] = max(fmx[i], f);
                 }
-        block_minmax3(fmn, fmx, s_red);
-        __syncthreads();               // a tile without a footprint passes no other
-        G = geom_from_cells(J, x0, y0, z0, x1, y1, z1, fmn, fmx, lds_cells);
-    } else {
-        G = box_geom(J, x0, y0, z0, x1, y1, z1, lds_cells);
-    }
-    const bool lds = G.lds;
-    const int ey = G.e[1], pitch = G.pitch, sxy = G.e[1] * G.pitch;
-    if (lds && g_img) {
-        // the tile's largest |g| over its guarded samples: reduced in each
-        // wave here, across the waves after the barrier that ends the corner
-        // reads; +inf when any g is not finite (NaN included, which fmaxf
-        // alone would drop), which sends the tile to the per-corner FP32 path
-        float gw = 0.0f;
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-            if (gd[k]) {
-                const float a = fabsf(gpk[k]);
-                gw = a <= 3.40282347e38f ? fmaxf(gw, a) : __builtin_inff();
             }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1)
-            gw = fmaxf(gw, __shfl_xor(gw, off, 64));
-        if ((threadIdx.x & 63) == 0)
-            s_gmax[threadIdx.x >> 6] = gw;
-    }
-    if (lds && need_dv) {              // the image adjoint alone needs no corner values
-        stage_footprint<T, float>(J, src, G, s_cells);
-        __syncthreads();
-    }
-    // per voxel of the run: LDS cell of corner (0,0,0), fractions, upstream gradient
-    int base[4], cx0[4];
-    float tw[4][3], gk[4];
-    bool live[4] = {false, false, false, false};
-    float S[3] = {0.0f, 0.0f, 0.0f}, Sz[3] = {0.0f, 0.0f, 0.0f};
-    float gu[4][3];
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-        gu[k][0] = gu[k][1] = gu[k][2] = 0.0f;
-    if (run_ok) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            if (k >= nvalid)
-                continue;
-            const int32_t v = v0 + 4 * k;
-            const float zf = (float)(z + 4 * k);
-            const float qx = qv[k][0], qy = qv[k][1], qz = qv[k][2];
-            const float gp = gpk[k];
-            float dV[3] = {0.0f, 0.0f, 0.0f};
-            if (gd[k]) {
-                float K[8], tt[3];
-                if (lds) {
-                    const float fx = floorf(qx), fy = floorf(qy), fz = floorf(qz);
-                    // LDS cell (i - lo) . (sxy, pitch, 1) in exact FP32 (integers < 2^24)
-                    const int bs = (int)__builtin_fmaf(
-                        fx - (float)G.lo[0], (float)sxy,
-                        __builtin_fmaf(fy - (float)G.lo[1], (float)pitch, fz - (float)G.lo[2]));
-                    tt[0] = qx - fx;
-                    tt[1] = qy - fy;
-                    tt[2] = qz - fz;
-                    if (need_dv) {
-                        K[0] = s_cells[bs];
-                        K[1] = s_cells[bs + 1];
-                        K[2] = s_cells[bs + pitch];
-                        K[3] = s_cells[bs + pitch + 1];
-                        K[4] = s_cells[bs + sxy];
-                        K[5] = s_cells[bs + sxy + 1];
-                        K[6] = s_cells[bs + sxy + pitch];
-                        K[7] = s_cells[bs + sxy + pitch + 1];
-                        cell_gradient(K, tt, dV);
-                    }
-                    if (g_img) {
-                        live[k] = true;
-                        base[k] = bs;
-                        cx0[k] = (int)fx - G.lo[0];
-                        tw[k][0] = tt[0];
-                        tw[k][1] = tt[1];
-                        tw[k][2] = tt[2];
-                        gk[k] = gp;
-                    }
-                } else {
-                    int32_t i0[3];
-                    corners_checked<T>(src, qx, qy, qz, J.fill, K, tt, i0);
-                    cell_gradient(K, tt, dV);
-                    if (g_img && gp != 0.0f) {
-                        const float wx[2] = {1.0f - tt[0], tt[0]};
-                        const float wy[2] = {1.0f - tt[1], tt[1]};
-                        const float wz[2] = {1.0f - tt[2], tt[2]};
-#pragma unroll
-                        for (int a = 0; a < 2; ++a)
-#pragma unroll
-                            for (int bb = 0; bb < 2; ++bb)
-#pragma unroll
-                                for (int c = 0; c < 2; ++c) {
-                                    const int32_t cx = i0[0] + a, cy = i0[1] + bb,
-                                                  cz = i0[2] + c;
-                                    // zero contributions are skipped; a non-finite
-                                    // g reaches every in-volume corner (0 * inf and
-                                    // 0 * NaN are NaN), as in the per-corner path
-                                    const float cw = wx[a] * wy[bb] * wz[c] * gp;
-                                    const bool ok = cx >= 0 && cx < J.nx && cy >= 0 &&
-                                                    cy < J.ny && cz >= 0 && cz < J.nz &&
-                                                    cw != 0.0f;
-                                    if (ok)
-                                        unsafeAtomicAdd(g_img + (cx * J.ny + cy) * J.nz + cz,
-                                                        cw);
-                                }
-                    }
-                }
-            }
-            if (DISP != kDispNone && g_disp) {
-                g_disp[v] = gp * dV[0];
-                g_disp[nvox + v] = gp * dV[1];
-                g_disp[2 * nvox + v] = gp * dV[2];
-            }
+            block_minmax3(fmn, fmx, s_red);
+            __syncthreads();           // a tile without a footprint passes no other
+            const int n[3] = {J.nx, J.ny, J.nz};
+            bool outside = J.nx == 0 || J.ny == 0 || J.nz == 0, inside = true;
 #pragma unroll
             for (int i = 0; i < 3; ++i) {
-                const float c = gp * dV[i];
-                gu[k][i] = c;
-                S[i] += c;
-                Sz[i] = __builtin_fmaf(c, zf, Sz[i]);
+                lo[i] = fmn[i];
+                e[i] = fmx[i] - fmn[i] + 2;
+                outside = outside || lo[i] >= n[i] || lo[i] + e[i] <= 0;
+                inside = inside && lo[i] >= 0 && lo[i] + e[i] <= n[i];
+            }
+            // whole quads inside the volume: an inside window may start earlier
+            inside = inside && ((e[2] + 3) & ~3) <= J.nz;
+            if (inside) {
+                const int zl = min(lo[2], J.nz - ((e[2] + 3) & ~3));
+                e[2] += lo[2] - zl;
+                lo[2] = zl;
+            }
+            pitch = lds_pitch(e[2]);
+            cls = outside ? kOutside : inside ? kInterior : kBoundary;
+            lds = !outside && (int64_t)e[0] * e[1] * pitch <= lds_cells;
+        }
+        if (lds && g_img) {
+            // the tile's largest |g| over its guarded samples, as bits: reduced
+            // in each wave here, across the waves after the barrier that ends
+            // the corner reads
+            uint32_t gw = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                gw = max(gw, (live >> k) & 1 ? __float_as_uint(gpk[k]) & 0x7fffffffu : 0u);
+            gw = wave_max(gw);
+            if ((tid & 63) == 0)
+                s_gmax[tid >> 6] = gw;
+        }
+        if (lds && need_dv) {          // the image adjoint alone needs no corner values
+            const Src S = make_src<T>(J);
+            const int quads = (e[2] + 3) >> 2;
+            const StageWalk W = stage_walk<kThreads>(e[0] * e[1], e[1], quads, tid);
+            if (W.passes > 0 && J.nz >= 4) {
+                stage_window<T, float, DISP == kDispNone>(J, S, W, lo, gr, e[1], pitch,
+                                                          cls == kInterior,
+                                                          reinterpret_cast<uint8_t *>(s_cells));
+            } else {
+                TileGeom G;
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    G.lo[i] = lo[i];
+                    G.e[i] = e[i];
+                }
+                G.quads = quads;
+                G.pitch = pitch;
+                G.cls = kBoundary;
+                stage_footprint<T, float>(J, S, G, s_cells);
+            }
+            __syncthreads();
+        }
+    }
+    const int ey = e[1], sxy = e[1] * pitch;
+    // per voxel of the run: LDS cell of corner (0,0,0), fractions
+    int base[4], cx0[4];
+    float tw[4][3];
+    float S[3] = {0.0f, 0.0f, 0.0f}, Sz[3] = {0.0f, 0.0f, 0.0f};
+    float gu[4][3];
+    const FwdJob &J = *(const FwdJob *)reload(Jp);
+    const int x = x0 + xr, y = y0 + yr, z = z0 + zr;
+    const bool row_ok = x <= x1 && y <= y1;
+    const int sy = 4 * pitch, sx = 4 * sxy;                // bytes
+    const int c0 = -(lo[0] * sx + lo[1] * sy + lo[2] * 4);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const bool valid = row_ok && z + 4 * k <= z1;
+        float dV[3] = {0.0f, 0.0f, 0.0f};
+        if (lds) {
+            int ix, iy, iz;
+            if (cls == kInterior) {
+                ix = flr_i32(qv[k][0]);
+                iy = flr_i32(qv[k][1]);
+                iz = flr_i32(qv[k][2]);
+#pragma unroll
+                for (int i = 0; i < 3; ++i)
+                    tw[k][i] = __builtin_amdgcn_fractf(qv[k][i]);
+            } else {
+                const float fx = floorf(qv[k][0]), fy = floorf(qv[k][1]), fz = floorf(qv[k][2]);
+                ix = (int)fx;
+                iy = (int)fy;
+                iz = (int)fz;
+                tw[k][0] = qv[k][0] - fx;
+                tw[k][1] = qv[k][1] - fy;
+                tw[k][2] = qv[k][2] - fz;
+            }
+            const int a = mad_i24(ix, sx, mad_i24(iy, sy, iz * 4 + c0));
+            base[k] = a;
+            cx0[k] = ix - lo[0];
+            if (need_dv) {
+                const char *s = reinterpret_cast<const char *>(s_cells);
+                const float *c00 = reinterpret_cast<const float *>(s + a);
+                const float *c01 = reinterpret_cast<const float *>(s + (a + sy));
+                const float *c10 = reinterpret_cast<const float *>(s + (a + sx));
+                const float *c11 = reinterpret_cast<const float *>(s + (a + sx + sy));
+                const float K[8] = {c00[0], c00[1], c01[0], c01[1], c10[0], c10[1], c11[0], c11[1]};
+                cell_gradient(K, tw[k], dV);
+            }
+        } else if (cls != kOutside && (live >> k) & 1) {
+            const Src src = make_src<T>(J);
+            const float gp = gpk[k];
+            float K[8], tt[3];
+            int32_t i0[3];
+            corners_checked<T>(src, qv[k][0], qv[k][1], qv[k][2], J.fill, K, tt, i0);
+            cell_gradient(K, tt, dV);
+            if (g_img && gp != 0.0f) {
+                const float wx[2] = {1.0f - tt[0], tt[0]};
+                const float wy[2] = {1.0f - tt[1], tt[1]};
+                const float wz[2] = {1.0f - tt[2], tt[2]};
+#pragma unroll 1
+                for (int c = 0; c < 8; ++c) {
+                    const int32_t cx = i0[0] + (c >> 2), cy = i0[1] + ((c >> 1) & 1),
+                                  cz = i0[2] + (c & 1);
+                    // zero contributions are skipped; a non-finite
+                    // g reaches every in-volume corner (0 * inf and
+                    // 0 * NaN are NaN), as in the per-corner path
+                    const float cw = (c & 4 ? wx[1] : wx[0]) * (c & 2 ? wy[1] : wy[0]) *
+                                     (c & 1 ? wz[1] : wz[0]) * gp;
+                    const bool ok = cx >= 0 && cx < J.nx && cy >= 0 && cy < J.ny && cz >= 0 &&
+                                    cz < J.nz && cw != 0.0f;
+                    if (ok)
+                        unsafeAtomicAdd(g_img + (cx * J.ny + cy) * J.nz + cz, cw);
+                }
             }
         }
+        if (DISP != kDispNone && g_disp && valid) {
+            const int32_t nvox = J.ox * J.oy * J.oz;
+            const int32_t v = (x * J.oy + y) * J.oz + z + 4 * k;
+            g_disp[v] = gpk[k] * dV[0];
+            g_disp[nvox + v] = gpk[k] * dV[1];
+            g_disp[2 * nvox + v] = gpk[k] * dV[2];
+        }
+        const float zf = (float)(z + 4 * k);
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
-            acc[4 * i + 0] += (double)x * (double)S[i];
-            acc[4 * i + 1] += (double)y * (double)S[i];
-            acc[4 * i + 2] += (double)Sz[i];
-            acc[4 * i + 3] += (double)S[i];
+            const float c = valid ? gpk[k] * dV[i] : 0.0f;
+            gu[k][i] = c;
+            S[i] += c;
+            Sz[i] = __builtin_fmaf(c, zf, Sz[i]);
         }
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        acc[4 * i + 0] += (double)x * (double)S[i];
+        acc[4 * i + 1] += (double)y * (double)S[i];
+        acc[4 * i + 2] += (double)Sz[i];
+        acc[4 * i + 3] += (double)S[i];
     }
     if (lds)                           // uniform: no barrier is skipped by part of the group
         __syncthreads();               // every corner read of the staged image is done
     if (want_ctrl)                     // before the image scatter: gu dies here
-        ctrl_adjoint_tile(J.bs, x0, y0, z0, x1, y1, z1, threadIdx.x >> 2, zr, gu, s_cells,
-                          s_ctrl);
-    if (lds) {
-        if (g_img) {
-            // the tile's largest |g| (the waves' maxima, written before the
-            // barrier that ended the corner reads); every wave reads it before
-            // any wave goes on to the next tile, which writes s_gmax again:
-            // each branch below passes a barrier before the tile ends
-            float gm = s_gmax[0];
+        ctrl_adjoint_tile(J.bs, x0, y0, z0, x1, y1, z1, tid, gu, s_cells, s_ctrl);
+    if (lds && g_img) {
+        // the tile's largest |g| (the waves' maxima, written before the
+        // barrier that ended the corner reads); every wave reads it before
+        // any wave goes on to the next tile, which writes s_gmax again:
+        // each branch below passes a barrier before the tile ends
+        typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+        const u4 gw = *reinterpret_cast<const u4 *>(s_gmax);
+        const float gm = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane(
+            (int)max(max(gw.x, gw.y), max(gw.z, gw.w))));
+        const bool inside = cls == kInterior;
+        // x-planes of 64-bit accumulators that fit the footprint reservation
+        const int planes = (lds_cells >> 1) / sxy;
+        if (NARROW && gm >= 0x1p-96f && gm <= 3.40282347e38f) {
+            // one pass, 32-bit accumulators (gmax >= 2^-96 keeps every
+            // scaled value and every flushed sum in the normal range)
+            const int sc = 30 - fix_bits - (ilogbf(gm) + 1);
+            const float S32 = __builtin_ldexpf(1.0f, sc);    // normal: sc in [-105, 125]
+            const float r32 = __builtin_ldexpf(1.0f, -sc);
+            int *s_acc = reinterpret_cast<int *>(s_cells);
+            const int n = e[0] * sxy;                        // a multiple of 4
+            for (int c = 4 * tid; c < n; c += 4 * kThreads)
+                *reinterpret_cast<f32x4 *>(s_acc + c) = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            __syncthreads();
 #pragma unroll
-            for (int w = 1; w < kThreads / 64; ++w)
-                gm = fmaxf(gm, s_gmax[w]);
-            // x-planes of 64-bit accumulators that fit the footprint reservation
-            const int planes = (lds_cells >> 1) / sxy;
-            const float rcp_pitch = 1.0f / (float)pitch, rcp_ey = 1.0f / (float)ey;
-            if (NARROW && gm >= 0x1p-96f && gm <= 3.40282347e38f) {
-                // one pass, 32-bit accumulators (gmax >= 2^-96 keeps every
-                // scaled value and every flushed sum in the normal range)
-                const int sc = 30 - fix_bits - (ilogbf(gm) + 1);
-                const float S32 = __builtin_ldexpf(1.0f, sc);    // normal: sc in [-105, 125]
-                int *s_acc = reinterpret_cast<int *>(s_cells);
-                const int n = G.e[0] * sxy;                      // a multiple of 4
-                for (int c = 4 * threadIdx.x; c < n; c += 4 * kThreads)
+            for (int k = 0; k < 4; ++k) {
+                if (!((live >> k) & 1))
+                    continue;
+                const float wx[2] = {1.0f - tw[k][0], tw[k][0]};
+                const float wy[2] = {1.0f - tw[k][1], tw[k][1]};
+                const float gks = gpk[k] * S32;
+                const float gz0 = (1.0f - tw[k][2]) * gks, gz1 = tw[k][2] * gks;
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+#pragma unroll
+                    for (int bb = 0; bb < 2; ++bb) {
+                        const float wxy = wx[a] * wy[bb];
+                        int *row = reinterpret_cast<int *>(reinterpret_cast<char *>(s_acc) +
+                                                           (base[k] + a * sx + bb * sy));
+                        atomicAdd(row, (int)__builtin_rintf(wxy * gz0));
+                        atomicAdd(row + 1, (int)__builtin_rintf(wxy * gz1));
+                    }
+                __builtin_amdgcn_sched_barrier(0);       // one voxel at a time
+            }
+            __syncthreads();
+            if (has_next) {            // waited for here: after the flush the wait would be
+                                       // for its atomics too (memory operations return in order)
+                load_run_g(Jn, gn, tn, tid, gnext);
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    asm volatile("" : "+v"(gnext[k]));
+                fetched = true;
+            }
+            flush_cells(s_acc, e[0], ey, e[2], pitch, lo[0], lo[1], lo[2], J, inside, tid, g_img,
+                        [=](int v) { return (float)v * r32; });
+            __syncthreads();           // LDS is reused next
+        } else if (!NARROW && gm > 0.0f && gm <= 3.40282347e38f && planes > 0) {
+            const int ex = ilogbf(gm) + 1;         // gm < 2^ex
+            const double S64 = ldexp(1.0, 50 - ex);
+            const double rS = ldexp(1.0, ex - 50);
+            long long *s_acc = reinterpret_cast<long long *>(s_cells);
+            for (int sx0 = 0; sx0 < e[0]; sx0 += planes) {     // uniform
+                const int np = min(planes, e[0] - sx0);
+                const int n = np * sxy;                        // a multiple of 4
+                for (int c = 2 * tid; c < n; c += 2 * kThreads)
                     *reinterpret_cast<f32x4 *>(s_acc + c) = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
                 __syncthreads();
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
-                    if (!live[k])
+                    if (!((live >> k) & 1))
                         continue;
                     const float wx[2] = {1.0f - tw[k][0], tw[k][0]};
                     const float wy[2] = {1.0f - tw[k][1], tw[k][1]};
-                    const float gks = gk[k] * S32;
-                    const float gz0 = (1.0f - tw[k][2]) * gks, gz1 = tw[k][2] * gks;
+                    const float gz0 = (1.0f - tw[k][2]) * gpk[k], gz1 = tw[k][2] * gpk[k];
 #pragma unroll
-                    for (int a = 0; a < 2; ++a)
+                    for (int a = 0; a < 2; ++a) {
+                        const int px = cx0[k] + a - sx0;
+                        if ((unsigned)px >= (unsigned)np)
+                            continue;
 #pragma unroll
                         for (int bb = 0; bb < 2; ++bb) {
                             const float wxy = wx[a] * wy[bb];
-                            int *row = s_acc + base[k] + a * sxy + bb * pitch;
-                            atomicAdd(row, (int)__builtin_rintf(wxy * gz0));
-                            atomicAdd(row + 1, (int)__builtin_rintf(wxy * gz1));
+                            unsigned long long *row = reinterpret_cast<unsigned long long *>(
+                                s_acc + (base[k] >> 2) + (a - sx0) * sxy + bb * pitch);
+                            atomicAdd(row, (unsigned long long)to_fixed(wxy * gz0, S64));
+                            atomicAdd(row + 1, (unsigned long long)to_fixed(wxy * gz1, S64));
                         }
-                    __builtin_amdgcn_sched_barrier(0);       // one voxel at a time
+                    }
+                    // one voxel's conversions at a time (register pressure)
+                    __builtin_amdgcn_sched_barrier(0);
                 }
                 __syncthreads();
-                if (has_next && !fetched) {
-                    load_run_g(Jn, gn, tn, zr, yr, xr, gnext);
-                    fetched = true;
-                }
-                // flush: one global atomic per touched in-volume footprint cell
-                for (int c = threadIdx.x; c < n; c += kThreads) {
-                    const int v = s_acc[c];
-                    if (v == 0)
-                        continue;
-                    const int row = div_small(c, pitch, rcp_pitch);
-                    const int cz = c - row * pitch;
-                    const int cx = div_small(row, ey, rcp_ey);
-                    const int cy = row - cx * ey;
-                    const int gx = G.lo[0] + cx, gy = G.lo[1] + cy, gz = G.lo[2] + cz;
-                    if (cz < G.e[2] && (unsigned)gx < (unsigned)J.nx &&
-                        (unsigned)gy < (unsigned)J.ny && (unsigned)gz < (unsigned)J.nz)
-                        unsafeAtomicAdd(g_img + (gx * J.ny + gy) * J.nz + gz,
-                                        __builtin_ldexpf((float)v, -sc));
-                }
+                flush_cells(s_acc, np, ey, e[2], pitch, lo[0] + sx0, lo[1], lo[2], J, inside, tid, g_img,
+                            [=](long long v) { return (float)((double)v * rS); });
                 __syncthreads();       // LDS is reused next
-            } else if (!NARROW && gm > 0.0f && gm <= 3.40282347e38f && planes > 0) {
-                const int e = ilogbf(gm) + 1;          // gm < 2^e
-                const double S = ldexp(1.0, 50 - e);
-                const double rS = ldexp(1.0, e - 50);
-                long long *s_acc = reinterpret_cast<long long *>(s_cells);
-                for (int sx0 = 0; sx0 < G.e[0]; sx0 += planes) {   // uniform
-                    const int np = min(planes, G.e[0] - sx0);
-                    const int n = np * sxy;                        // a multiple of 4
-                    for (int c = 2 * threadIdx.x; c < n; c += 2 * kThreads)
-                        *reinterpret_cast<f32x4 *>(s_acc + c) = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-                    __syncthreads();
+            }
+        } else {
+            __syncthreads();           // every wave has read s_gmax
+            // non-finite gradients, a footprint too large for one x-plane
+            // of 64-bit accumulators, or a 32-bit tile with gmax < 2^-96:
+            // FP32 global atomics per corner (none when gmax = 0)
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        if (!live[k])
-                            continue;
-                        const float wx[2] = {1.0f - tw[k][0], tw[k][0]};
-                        const float wy[2] = {1.0f - tw[k][1], tw[k][1]};
-                        const float gz0 = (1.0f - tw[k][2]) * gk[k], gz1 = tw[k][2] * gk[k];
-#pragma unroll
-                        for (int a = 0; a < 2; ++a) {
-                            const int px = cx0[k] + a - sx0;
-                            if ((unsigned)px >= (unsigned)np)
-                                continue;
-#pragma unroll
-                            for (int bb = 0; bb < 2; ++bb) {
-                                const float wxy = wx[a] * wy[bb];
-                                unsigned long long *row = reinterpret_cast<unsigned long long *>(
-                                    s_acc + base[k] - cx0[k] * sxy + px * sxy + bb * pitch);
-                                atomicAdd(row, (unsigned long long)to_fixed(wxy * gz0, S));
-                                atomicAdd(row + 1, (unsigned long long)to_fixed(wxy * gz1, S));
-                            }
-                        }
-                        // one voxel's conversions at a time (register pressure)
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                    __syncthreads();
-                    // flush: one global atomic per touched in-volume footprint cell
-                    for (int c = threadIdx.x; c < n; c += kThreads) {
-                        const long long v = s_acc[c];
-                        if (v == 0)
-                            continue;
-                        const int row = div_small(c, pitch, rcp_pitch);
-                        const int cz = c - row * pitch;
-                        const int cx = div_small(row, ey, rcp_ey);
-                        const int cy = row - cx * ey;
-                        const int gx = G.lo[0] + sx0 + cx, gy = G.lo[1] + cy,
-                                  gz = G.lo[2] + cz;
-                        if (cz < G.e[2] && (unsigned)gx < (unsigned)J.nx &&
-                            (unsigned)gy < (unsigned)J.ny && (unsigned)gz < (unsigned)J.nz)
-                            unsafeAtomicAdd(g_img + (gx * J.ny + gy) * J.nz + gz,
-                                            (float)((double)v * rS));
-                    }
-                    __syncthreads();   // LDS is reused next
-                }
-            } else {
-                __syncthreads();       // every wave has read s_gmax
-                // non-finite gradients, a footprint too large for one x-plane
-                // of 64-bit accumulators, or a 32-bit tile with gmax < 2^-96:
-                // FP32 global atomics per corner (none when gmax = 0)
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    if (!live[k] || gm == 0.0f)
-                        continue;
-                    const int rel = base[k] - cx0[k] * sxy;
-                    const int cy0 = rel / pitch, cz0 = rel - cy0 * pitch;
-                    const float wx[2] = {1.0f - tw[k][0], tw[k][0]};
-                    const float wy[2] = {1.0f - tw[k][1], tw[k][1]};
-                    const float gz[2] = {(1.0f - tw[k][2]) * gk[k], tw[k][2] * gk[k]};
-                    for (int a = 0; a < 2; ++a)
-                        for (int bb = 0; bb < 2; ++bb)
-                            for (int c = 0; c < 2; ++c) {
-                                const int gx = G.lo[0] + cx0[k] + a, gy = G.lo[1] + cy0 + bb,
-                                          gz2 = G.lo[2] + cz0 + c;
-                                if ((unsigned)gx < (unsigned)J.nx &&
-                                    (unsigned)gy < (unsigned)J.ny &&
-                                    (unsigned)gz2 < (unsigned)J.nz)
-                                    unsafeAtomicAdd(g_img + (gx * J.ny + gy) * J.nz + gz2,
-                                                    wx[a] * wy[bb] * gz[c]);
-                            }
+            for (int k = 0; k < 4; ++k) {
+                if (!((live >> k) & 1) || gm == 0.0f)
+                    continue;
+                const int rel = (base[k] >> 2) - cx0[k] * sxy;
+                const int cy0 = rel / pitch, cz0 = rel - cy0 * pitch;
+                const float wx[2] = {1.0f - tw[k][0], tw[k][0]};
+                const float wy[2] = {1.0f - tw[k][1], tw[k][1]};
+                const float gz[2] = {(1.0f - tw[k][2]) * gpk[k], tw[k][2] * gpk[k]};
+#pragma unroll 1
+                for (int c = 0; c < 8; ++c) {
+                    const int gx = lo[0] + cx0[k] + (c >> 2), gy = lo[1] + cy0 + ((c >> 1) & 1),
+                              gz2 = lo[2] + cz0 + (c & 1);
+                    if ((unsigned)gx < (unsigned)J.nx && (unsigned)gy < (unsigned)J.ny &&
+                        (unsigned)gz2 < (unsigned)J.nz)
+                        unsafeAtomicAdd(g_img + (gx * J.ny + gy) * J.nz + gz2,
+                                        (c & 4 ? wx[1] : wx[0]) * (c & 2 ? wy[1] : wy[0]) *
+                                            (c & 1 ? gz[1] : gz[0]));
                 }
             }
         }
     }
     if (!fetched) {
         if (has_next)
-            load_run_g(Jn, gn, tn, zr, yr, xr, gnext);
+            load_run_g(Jn, gn, tn, tid, gnext);
         else
 #pragma unroll
             for (int k = 0; k < 4; ++k)
@@ -678,28 +799,37 @@ __device__ __forceinline__ void bwd_tile(const FwdJob &J, int t, const Src &src,
     }
 }
 
+// An affine adjoint's tiles come in groups of consecutive ones, a workgroup each,
+// which the hardware hands out as workgroups end: tiles cost from nothing (outside
+// the volume) to a full footprint, and with one wave of workgroups striding over
+// all tiles the last ended 35 % after the mean on 8 x 128^3.  The group's FP64 sums
+// of grad_M are one row, so they do not depend on who ran it when.  That took 8 x
+// 128^3 from 257 to 229 us (2 tiles a group 228, 8 tiles 241).
+constexpr int32_t kGroupTiles = 4;     // at most, but for the limit of kBwdMaxRows groups
+constexpr int64_t kGroupFill = 4096;   // groups wanted: four per resident workgroup
+constexpr int kGroupLog = 3;           // groups of a chunk of the XCD order (32 tiles)
+
 // Register budgets follow the LDS: a displacement takes the whole 48 KB
 // reservation (3 workgroups per CU), so at most 168 VGPRs (3 waves per SIMD);
 // an affine job's footprint bound usually keeps a workgroup within 40 KB
-// (4 per CU), so at most 128 VGPRs, a few of them spilled.  NARROW (affine
-// jobs with a bound fix_bits >= 0) takes the 32-bit image adjoint: a kernel
-// of its own, as register allocation over both fixed-point paths spills.
+// (4 per CU), so at most 128 VGPRs; its 64-bit variant would spill at that and
+// takes 168 (spilled registers cost far more than a wave: scratch loads wait for
+// every load before them).  NARROW (affine jobs with a bound fix_bits >= 0) takes
+// the 32-bit image adjoint: a kernel of its own, as register allocation over
+// both fixed-point paths spills.
 template <typename T, int DISP, bool NARROW>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
-    DISP == kDispNone ? 4 : 3))) void k_warp_bwd(FwdJob J, const float *__restrict__ g,
+    NARROW ? 4 : 3))) void k_warp_bwd(FwdJob J, const float *__restrict__ g,
                                                        float *__restrict__ g_img,
                                                        float *__restrict__ g_disp,
                                                        double *__restrict__ partials,
                                                        double *__restrict__ ctrl_part,
                                                        int32_t ntiles, int32_t lds_cells,
-                                                       int32_t fix_bits)
+                                                       int32_t fix_bits, int32_t group_tiles)
 {
     const int b = blockIdx.x;
-    const int per_xcd_wg = gridDim.x >> 3;
-    const Src src = make_src<T>(J);
-    gconst<float> *disp = gc<float>(J.disp);
-    const int32_t nvox = J.ox * J.oy * J.oz;
-    const bool empty_in = J.nx == 0 || J.ny == 0 || J.nz == 0;   // every sample is fill
+    // J is the first kernel argument
+    const JobPtr Jp = (JobPtr)__builtin_amdgcn_kernarg_segment_ptr();
 
     double acc[12];
 #pragma unroll
@@ -720,35 +850,38 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
     }
 
     __shared__ __attribute__((aligned(16))) int s_red[6][kThreads / 64];
-    __shared__ float s_gmax[kThreads / 64];
+    __shared__ __attribute__((aligned(16))) uint32_t s_gmax[kThreads / 64];
 
-    // this thread's run inside every tile: voxels z0 + zr + 4k, k = 0..3, of row
-    // (xr, yr).  Lanes next to each other take neighbouring z, so that the LDS
-    // accumulator updates of one instruction fall in different banks.
-    const int zr = threadIdx.x & 3;
-    const int yr = (threadIdx.x >> 2) & 7;
-    const int xr = threadIdx.x >> 5;
-
-    XcdSlots slots(b >> 3, per_xcd_wg);
-    int t = xcd_tile(b & 7, slots.slot());
-    float gcur[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (t < ntiles)
-        load_run_g(J, g, t, zr, yr, xr, gcur);
-    while (t < ntiles) {
-        slots.next();
-        const int tn = xcd_tile(b & 7, slots.slot());
-        float gnext[4];
-        // affine: the next tile's gradient is loaded during this tile's flush;
-        // a displacement's tiles load their own at the start
-        bwd_tile<T, DISP, NARROW>(J, t, src, disp, nvox, empty_in, want_ctrl, need_dv, gcur,
-                                  DISP == kDispNone && tn < ntiles, J, g, tn, gnext, g_img, g_disp,
-                                  s_ctrl, lds_cells, fix_bits, zr, yr, xr, acc, s_red, s_gmax);
-        if (DISP != kDispNone && tn < ntiles)
-            load_run_g(J, g, tn, zr, yr, xr, gnext);
+    if constexpr (DISP == kDispNone) {
+        // group g of group_tiles tiles; its row of partials is g
+        const int g0 = xcd_tile<kGroupLog>(b & 7, b >> 3);
+        const int t1 = min((g0 + 1) * group_tiles, ntiles);
+        if (g0 * group_tiles >= ntiles)
+            return;
+        float gcur[4];
+        load_run_g(Jp, g, g0 * group_tiles, (int)threadIdx.x, gcur);
+        for (int t = g0 * group_tiles; t < t1; ++t) {
+            float gnext[4];
+            bwd_tile<T, DISP, NARROW>(Jp, t, false, need_dv, gcur, t + 1 < t1, Jp, g, t + 1, gnext,
+                                      g_img, g_disp, s_ctrl, lds_cells, fix_bits, acc, s_red,
+                                      s_gmax);
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-            gcur[k] = gnext[k];
-        t = tn;
+            for (int k = 0; k < 4; ++k)
+                gcur[k] = gnext[k];
+        }
+        if (partials) {
+            __shared__ double red[kThreads / 64][12];
+            write_partial_row(acc, red, partials + (int64_t)g0 * 12);
+        }
+        return;
+    }
+    XcdSlots slots(b >> 3, gridDim.x >> 3);
+    for (int t = xcd_tile(b & 7, slots.slot()); t < ntiles;
+         slots.next(), t = xcd_tile(b & 7, slots.slot())) {
+        float gcur[4], gnext[4];
+        load_run_g(Jp, g, t, (int)threadIdx.x, gcur);
+        bwd_tile<T, DISP, NARROW>(Jp, t, want_ctrl, need_dv, gcur, false, Jp, g, t, gnext, g_img,
+                                  g_disp, s_ctrl, lds_cells, fix_bits, acc, s_red, s_gmax);
     }
 
     if (want_ctrl)                         // the last tile ended with a barrier
@@ -761,100 +894,61 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
     write_partial_row(acc, red, partials + (int64_t)blockIdx.x * 12);
 }
 
-// Batched adjoint: the tiles of up to kBwdBatchMax jobs in one persistent
-// launch, the job table passed by value in the kernel arguments (no upload,
-// nothing to allocate).  prefix[j] = first global tile of job j,
-// prefix[njobs] = total; workgroups stride over their XCD's tiles in
-// increasing order (xcd_tile), so the jobs a workgroup meets come in
-// increasing order.  The
-// workgroup's FP64 parameter sums of job j go to partials row
-// j * gridDim.x + b; it writes zeros to the rows of the jobs it never meets
-// (no zeroing launch before).
+// Batched adjoint: the groups of up to kBwdBatchMax jobs in one launch, the job
+// table passed by value in the kernel arguments (no upload, nothing to
+// allocate).  prefix[j] = first group of job j, prefix[njobs] = total;
+// group_tiles[j] tiles each.  The FP64 parameter sums of group g of job j go to
+// partials row j * kBwdMaxRows + g.
 template <typename T, bool NARROW>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_warp_bwd_batch(const BwdBatch B,
-                                                             double *__restrict__ partials,
-                                                             int32_t lds_cells)
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NARROW ? 4 : 3))) void
+k_warp_bwd_batch(const BwdBatch B, double *__restrict__ partials, int32_t lds_cells)
 {
-    const int total = B.prefix[B.njobs];
     const int b = blockIdx.x;
-    const int per_xcd_wg = gridDim.x >> 3;
+    const int gi = xcd_tile<kGroupLog>(b & 7, b >> 3);
+    if (gi >= B.prefix[B.njobs])
+        return;
+    int j = 0;                         // the job holding group gi (uniform)
+    for (int i = 1; i < B.njobs; ++i)
+        j += B.prefix[i] <= gi;
     __shared__ __attribute__((aligned(16))) int s_red[6][kThreads / 64];
-    __shared__ float s_gmax[kThreads / 64];
+    __shared__ __attribute__((aligned(16))) uint32_t s_gmax[kThreads / 64];
     __shared__ double red[kThreads / 64][12];
-    const int zr = threadIdx.x & 3;
-    const int yr = (threadIdx.x >> 2) & 7;
-    const int xr = threadIdx.x >> 5;
     double acc[12];
 #pragma unroll
     for (int i = 0; i < 12; ++i)
         acc[i] = 0.0;
-    // rows of jobs jlo .. jhi - 1, which this workgroup does not meet: zeros
-    // (only jobs with grad_M have rows: without any, partials may be null)
-    auto zero_rows = [&](int jlo, int jhi) {
-        for (int e = threadIdx.x; e < (jhi - jlo) * 12; e += kThreads) {
-            const int jj = jlo + e / 12;
-            if (B.jobs[jj].g_M)
-                partials[((int64_t)jj * gridDim.x + b) * 12 + e % 12] = 0.0;
-        }
-    };
-    auto job_of = [&](int t) {         // the job holding tile t (uniform)
-        int j = 0;
-        for (int i = 1; i < B.njobs; ++i)
-            j += B.prefix[i] <= t;
-        return j;
-    };
-    int jcur = -1;
-    XcdSlots slots(b >> 3, per_xcd_wg);
-    int t = xcd_tile(b & 7, slots.slot());
-    int j = t < total ? job_of(t) : 0;
-    float gcur[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (t < total)
-        load_run_g(B.jobs[j].J, B.jobs[j].g, t - B.prefix[j], zr, yr, xr, gcur);
-    while (t < total) {
-        if (j != jcur) {               // the whole workgroup switches jobs (j > jcur)
-            if (jcur >= 0 && B.jobs[jcur].g_M) {
-                write_partial_row(acc, red, partials + ((int64_t)jcur * gridDim.x + b) * 12);
-#pragma unroll
-                for (int i = 0; i < 12; ++i)
-                    acc[i] = 0.0;
-            }
-            zero_rows(jcur + 1, j);
-            jcur = j;
-        }
-        slots.next();
-        const int tn = xcd_tile(b & 7, slots.slot());
-        const int jn = tn < total ? job_of(tn) : j;
-        const BwdJob &BJ = B.jobs[j];
-        const BwdJob &BN = B.jobs[jn];
-        const Src src = make_src<T>(BJ.J);
-        const bool empty_in = BJ.J.nx == 0 || BJ.J.ny == 0 || BJ.J.nz == 0;
+    const BwdJob &BJ = B.jobs[j];
+    // B is the first kernel argument
+    const JobPtr Jp = (JobPtr)((__attribute__((address_space(4))) const char *)
+                                   __builtin_amdgcn_kernarg_segment_ptr() +
+                               offsetof(BwdBatch, jobs) + j * sizeof(BwdJob) + offsetof(BwdJob, J));
+    const int g = gi - B.prefix[j], nt = B.group_tiles[j];
+    const int t1 = min((g + 1) * nt, Jp->tiles_x * Jp->tiles_y * Jp->tiles_z);
+    float gcur[4];
+    load_run_g(Jp, BJ.g, g * nt, (int)threadIdx.x, gcur);
+    for (int t = g * nt; t < t1; ++t) {
         float gnext[4];
-        bwd_tile<T, kDispNone, NARROW>(BJ.J, t - B.prefix[j], src, nullptr,
-                                       BJ.J.ox * BJ.J.oy * BJ.J.oz, empty_in, false,
-                                       BJ.g_M != nullptr, gcur, tn < total, BN.J, BN.g,
-                                       tn - B.prefix[jn], gnext, BJ.g_img, nullptr, nullptr,
-                                       lds_cells, B.fix_bits[j], zr, yr, xr, acc, s_red, s_gmax);
+        bwd_tile<T, kDispNone, NARROW>(Jp, t, false, BJ.g_M != nullptr, gcur, t + 1 < t1, Jp, BJ.g,
+                                       t + 1, gnext, BJ.g_img, nullptr, nullptr, lds_cells,
+                                       B.fix_bits[j], acc, s_red, s_gmax);
 #pragma unroll
         for (int k = 0; k < 4; ++k)
             gcur[k] = gnext[k];
-        t = tn;
-        j = jn;
     }
-    if (jcur >= 0 && B.jobs[jcur].g_M)
-        write_partial_row(acc, red, partials + ((int64_t)jcur * gridDim.x + b) * 12);
-    zero_rows(jcur + 1, B.njobs);
+    if (BJ.g_M)
+        write_partial_row(acc, red, partials + ((int64_t)j * kBwdMaxRows + g) * 12);
 }
 
-// grad_M of job blockIdx.x: its rows j * nrows .. (j + 1) * nrows - 1 summed
-// in a fixed order (jobs without grad_M are skipped).
+// grad_M of job blockIdx.x: the rows of its groups summed in a fixed order (jobs
+// without grad_M are skipped).
 __global__ __launch_bounds__(kThreads) void k_reduce12_batch(const BwdBatch B,
-                                                             const double *__restrict__ partials,
-                                                             int32_t nrows)
+                                                             const double *__restrict__ partials)
 {
     double *out = B.jobs[blockIdx.x].g_M;
     if (!out)
         return;
-    const double *rows = partials + (int64_t)blockIdx.x * nrows * 12;
+    const int32_t nrows = B.prefix[blockIdx.x + 1] - B.prefix[blockIdx.x];
+    const double *rows = partials + (int64_t)blockIdx.x * kBwdMaxRows * 12;
     double acc[12];
 #pragma unroll
     for (int i = 0; i < 12; ++i)
@@ -869,7 +963,7 @@ __global__ __launch_bounds__(kThreads) void k_reduce12_batch(const BwdBatch B,
 #pragma unroll
     for (int i = 0; i < 12; ++i) {
         const double sum = wave_sum(acc[i]);
-        if (lane == 0)
+        if (lane == 63)
             red[wave][i] = sum;
     }
     __syncthreads();
@@ -879,14 +973,6 @@ __global__ __launch_bounds__(kThreads) void k_reduce12_batch(const BwdBatch B,
             sum += red[w][threadIdx.x];
         out[threadIdx.x] = sum;
     }
-}
-
-// Zero n doubles (rows of partials that a batched adjoint may leave unwritten).
-__global__ __launch_bounds__(kThreads) void k_zero_f64(double *__restrict__ p, int64_t n)
-{
-    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (i < n)
-        p[i] = 0.0;
 }
 
 // Sum n rows of 12 doubles in a fixed order into out[12].
@@ -908,7 +994,7 @@ __global__ __launch_bounds__(kThreads) void k_reduce12(const double *__restrict_
 #pragma unroll
     for (int i = 0; i < 12; ++i) {
         const double s = wave_sum(acc[i]);
-        if (lane == 0)
+        if (lane == 63)
             red[wave][i] = s;
     }
     __syncthreads();
@@ -1087,6 +1173,15 @@ static int bwd_launch_grid(const void *fn, size_t lds, int64_t ntiles)
     return (int)(resident >= 8 ? std::min<int64_t>(rows, resident) : rows);
 }
 
+// Tiles of a group of an affine job of ntiles tiles, in a launch of total: fewer where
+// the launch would not fill the device.
+static int32_t group_size(int64_t ntiles, int64_t total)
+{
+    const int64_t want = std::min<int64_t>(kGroupTiles, std::max<int64_t>(1, total / kGroupFill));
+    return (int32_t)std::max<int64_t>(want, (ntiles + kBwdMaxRows - 1) / kBwdMaxRows);
+}
+
+// Launches the adjoint of J; the rows of partials it writes.
 template <int DISP>
 static int launch_bwd_t(const FwdJob &J, int64_t ntiles, size_t lds, hipStream_t s,
                         const float *g, float *g_img, float *g_disp, double *part,
@@ -1094,11 +1189,18 @@ static int launch_bwd_t(const FwdJob &J, int64_t ntiles, size_t lds, hipStream_t
 {
     const int32_t fix_bits = DISP == kDispNone ? fixed32_bits(J) : -1;
     const int nt = (int)ntiles;
-    int grid = 0;
+    const int32_t gt = group_size(ntiles, ntiles);
+    int rows = 0;
     auto launch = [&](auto kern) {
-        grid = bwd_launch_grid(reinterpret_cast<const void *>(kern), lds, ntiles);
+        int grid;
+        if (DISP == kDispNone) {
+            rows = (int)((ntiles + gt - 1) / gt);
+            grid = 8 * xcd_slots<kGroupLog>(rows);
+        } else {
+            grid = rows = bwd_launch_grid(reinterpret_cast<const void *>(kern), lds, ntiles);
+        }
         hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), lds, s, J, g, g_img, g_disp, part,
-                           ctrl_part, nt, cells, fix_bits);
+                           ctrl_part, nt, cells, fix_bits, gt);
     };
     if constexpr (DISP == kDispNone) {
         if (fix_bits >= 0) {
@@ -1106,14 +1208,24 @@ static int launch_bwd_t(const FwdJob &J, int64_t ntiles, size_t lds, hipStream_t
                 launch(&k_warp_bwd<int16_t, DISP, true>);
             else
                 launch(&k_warp_bwd<float, DISP, true>);
-            return grid;
+            return rows;
         }
     }
     if (J.dtype == kI16)
         launch(&k_warp_bwd<int16_t, DISP, false>);
     else
         launch(&k_warp_bwd<float, DISP, false>);
-    return grid;
+    return rows;
+}
+
+// LDS cells of an affine job's tiles (their window, set here); jobs whose window
+// exceeds kBwdLdsMax, or has coordinates too large for one, take none and gather.
+static int32_t affine_cells(FwdJob &J)
+{
+    const int32_t cells = set_window(J, kBwdTiling);
+    if (cells > kBwdLdsMax)
+        J.box_e[0] = 0;
+    return J.box_e[0] != 0 ? cells : 64;
 }
 
 hipError_t launch_warp_bwd(const FwdJob &J0, const float *g, float *g_img, float *g_disp,
@@ -1124,6 +1236,8 @@ hipError_t launch_warp_bwd(const FwdJob &J0, const float *g, float *g_img, float
     J.tiles_x = (J.ox + 7) >> 3;
     J.tiles_y = (J.oy + 7) >> 3;
     J.tiles_z = (J.oz + 15) >> 4;
+    J.rcp_ty = rcp_u32((uint32_t)J.tiles_y);
+    J.rcp_tz = rcp_u32((uint32_t)J.tiles_z);
     const int64_t ntiles = (int64_t)J.tiles_x * J.tiles_y * J.tiles_z;
     const int32_t nctrl = 3 * J.bs.gx * J.bs.gy * J.bs.gz;
     if (ntiles == 0) {
@@ -1141,10 +1255,9 @@ hipError_t launch_warp_bwd(const FwdJob &J0, const float *g, float *g_img, float
     // LDS cells sized for the largest footprint of any tile (a displacement has
     // no a-priori bound: the full reservation, used when a tile fits it)
     const bool displaced = J.disp || J.ctrl;
-    const int32_t cells =
-        J.ctrl ? kSplineBwdCells
-               : displaced ? kBwdLdsCells
-                           : std::min(footprint_cells_bound(J, kBwdTiling), kBwdLdsCells);
+    const int32_t cells = J.ctrl      ? kSplineBwdCells
+                          : displaced ? kBwdLdsCells
+                                      : affine_cells(J);
     const size_t lds = (size_t)(J.ctrl ? kBwdLdsCells : cells) * sizeof(float);
     double *part = g_M ? partials : nullptr;
     double *cpart = g_ctrl ? ctrl_part : nullptr;
@@ -1169,18 +1282,20 @@ hipError_t launch_warp_bwd(const FwdJob &J0, const float *g, float *g_img, float
     return hipGetLastError();
 }
 
-// Batched affine adjoint: chunks of up to kBwdBatchMax jobs, each one
-// persistent launch (its job table in the kernel arguments; every workgroup
-// writes its partial row of every job, zeros where it met none of the job's
-// tiles) and one reduction launch; a chunk with no tiles zeroes its rows in
-// a launch of its own.  partials: kBwdMaxRows * 12 doubles per job.
+// Batched affine adjoint: chunks of up to kBwdBatchMax jobs, each one launch (its
+// job table in the kernel arguments; every group of tiles writes its row) and
+// one reduction launch.  partials: kBwdMaxRows * 12 doubles per job.
 hipError_t launch_warp_bwd_batch(const BwdJob *jobs, int32_t n, double *partials, hipStream_t s)
 {
     for (int32_t c0 = 0; c0 < n; c0 += kBwdBatchMax) {
         BwdBatch B;
         std::memset(&B, 0, sizeof B);
         B.njobs = std::min<int32_t>(kBwdBatchMax, n - c0);
-        int64_t total = 0;
+        int64_t total = 0, all_tiles = 0;
+        for (int i = 0; i < B.njobs; ++i) {
+            const FwdJob &J = jobs[c0 + i].J;
+            all_tiles += bwd_tiles(J.ox, J.oy, J.oz);
+        }
         int32_t cells = 64;
         bool any_M = false;
         for (int i = 0; i < B.njobs; ++i) {
@@ -1189,11 +1304,15 @@ hipError_t launch_warp_bwd_batch(const BwdJob *jobs, int32_t n, double *partials
             J.tiles_x = (J.ox + 7) >> 3;
             J.tiles_y = (J.oy + 7) >> 3;
             J.tiles_z = (J.oz + 15) >> 4;
-            B.prefix[i] = (int32_t)total;
+            J.rcp_ty = rcp_u32((uint32_t)J.tiles_y);
+            J.rcp_tz = rcp_u32((uint32_t)J.tiles_z);
             B.fix_bits[i] = fixed32_bits(J);
-            total += (int64_t)J.tiles_x * J.tiles_y * J.tiles_z;
+            const int64_t tiles = (int64_t)J.tiles_x * J.tiles_y * J.tiles_z;
+            B.group_tiles[i] = group_size(tiles, all_tiles);
+            B.prefix[i] = (int32_t)total;
+            total += (tiles + B.group_tiles[i] - 1) / B.group_tiles[i];
             if (J.nx > 0 && J.ny > 0 && J.nz > 0 && J.ox > 0 && J.oy > 0 && J.oz > 0)
-                cells = std::max(cells, std::min(footprint_cells_bound(J, kBwdTiling), kBwdLdsCells));
+                cells = std::max(cells, affine_cells(J));
             any_M = any_M || B.jobs[i].g_M;
         }
         B.prefix[B.njobs] = (int32_t)total;
@@ -1207,25 +1326,15 @@ hipError_t launch_warp_bwd_batch(const BwdJob *jobs, int32_t n, double *partials
         const BatchKernel kern =
             i16 ? (narrow ? &k_warp_bwd_batch<int16_t, true> : &k_warp_bwd_batch<int16_t, false>)
                 : (narrow ? &k_warp_bwd_batch<float, true> : &k_warp_bwd_batch<float, false>);
-        const int grid =
-            total > 0 ? bwd_launch_grid(reinterpret_cast<const void *>(kern), lds, total) : 8;
-        if (any_M && total == 0) {     // else the kernel writes every row
-            const int64_t nz = (int64_t)B.njobs * grid * 12;
-            hipLaunchKernelGGL(k_zero_f64, dim3((unsigned)((nz + kThreads - 1) / kThreads)),
-                               dim3(kThreads), 0, s, part, nz);
-            hipError_t e = hipGetLastError();
-            if (e != hipSuccess)
-                return e;
-        }
         if (total > 0) {
-            hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), lds, s, B, part, cells);
+            hipLaunchKernelGGL(kern, dim3((unsigned)(8 * xcd_slots<kGroupLog>((int)total))),
+                               dim3(kThreads), lds, s, B, part, cells);
             hipError_t e = hipGetLastError();
             if (e != hipSuccess)
                 return e;
         }
         if (any_M) {
-            hipLaunchKernelGGL(k_reduce12_batch, dim3(B.njobs), dim3(kThreads), 0, s, B, part,
-                               grid);
+            hipLaunchKernelGGL(k_reduce12_batch, dim3(B.njobs), dim3(kThreads), 0, s, B, part);
             hipError_t e = hipGetLastError();
             if (e != hipSuccess)
                 return e;

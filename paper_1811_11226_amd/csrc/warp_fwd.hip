@@ -53,27 +53,6 @@ struct Box {
     int sx, sy, c0;
 };
 
-// A coordinate moved into [-2, n] without changing its sample: at or below -1
-// (and NaN) it goes to -2, at or above n to n.  There every corner is outside the volume,
-// so the trilinear value is fill and the nearest voxel is outside, which is what
-// the guard (-1, n) gives; a footprint of cells within [-2, n + 2), fill where
-// outside the volume, then needs no test per sample.
-__device__ __forceinline__ float guard_coord(float q, float n)
-{
-    return fminf(q > -1.0f ? q : -2.0f, n);
-}
-
-// A job in constant memory (kernel arguments or the batch's table, which no
-// kernel writes): its fields are scalar loads.  reload() hides the pointer's
-// origin, so that a phase's fields are loaded anew there rather than kept in
-// scalar registers through the phases before it (all of them together spill).
-typedef __attribute__((address_space(4))) const FwdJob *JobPtr;
-__device__ __forceinline__ JobPtr reload(JobPtr p)
-{
-    asm volatile("" : "+s"(p));
-    return p;
-}
-
 // All runs of one box along one sampling path (uniform).  Each thread owns runs
 // of 4 consecutive output voxels along z.  With a displacement (DISP) the box
 // has exactly one run per thread and its coordinates come precomputed in Q.
@@ -266,159 +245,6 @@ __device__ __forceinline__ void run_box(JobPtr Jp, const Box &B, int path, const
     }
 }
 
-// The quads (4 cells of a row) of a footprint window that this thread copies: quad
-// ql of rows row0, row0 + rpp, ... (mine of them), (cx, cy) the plane and row of the
-// first within the window.  The windows of a job's sub-tiles have the same
-// extents, so this is laid out once per tile.  NT threads take part.
-constexpr int kStageChunk = 4;
-struct StageWalk {
-    int row0, ql, cx, cy, mine;
-    int rpp, step_x, step_y, passes;   // uniform; rpp = step_x ey + step_y
-};
-
-template <int NT> __device__ __forceinline__ StageWalk stage_walk(int rows, int ey, int quads)
-{
-    StageWalk W;
-    W.row0 = W.ql = W.cx = W.cy = W.mine = W.step_x = W.step_y = 0;
-    W.passes = 0;
-    W.rpp = __builtin_amdgcn_readfirstlane(div_small(NT, quads, 1.0f / (float)quads));
-    if (W.rpp == 0)
-        return W;
-    W.passes = __builtin_amdgcn_readfirstlane(
-        div_small(rows + W.rpp - 1, W.rpp, 1.0f / (float)W.rpp));
-    W.row0 = div_small(threadIdx.x, quads, 1.0f / (float)quads);
-    W.ql = threadIdx.x - W.row0 * quads;
-    const float rcp_y = 1.0f / (float)ey;
-    W.step_x = __builtin_amdgcn_readfirstlane(div_small(W.rpp, ey, rcp_y));
-    W.step_y = W.rpp - W.step_x * ey;
-    W.cx = div_small(W.row0, ey, rcp_y);
-    W.cy = W.row0 - W.cx * ey;
-    W.mine = W.row0 < W.rpp ? (W.row0 + (W.passes - 1) * W.rpp < rows ? W.passes : W.passes - 1)
-                            : 0;
-    return W;
-}
-
-// Four raw cells c loaded from z = zc of a row, of which the quad's cell u is
-// c[s + u] (fill where s + u is not 0 .. 3, or ok is false), written as LDS cells.
-template <typename LT>
-__device__ __forceinline__ void store_shifted(const LT (&c)[4], int s, bool ok, LT fill, LT *dst)
-{
-    LT v[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        v[u] = fill;
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            v[u] = s + u == j ? c[j] : v[u];
-        v[u] = ok ? v[u] : fill;
-    }
-    store4(dst, v);
-}
-
-// Copies a window into LDS, kStageChunk loads of a thread in flight at once (12
-// took as long: lines fetched count, not round trips, and the registers cost a
-// wave per SIMD).  Quads that no sample of the box can use are not loaded
-// (FwdJob::reach; their cells are never read): a rotated box fills about half of
-// its window (CLIP; displaced boxes copy every quad).  That took the 16-volume
-// batch from 250 to 237 us.
-// inside: the window (whole quads) lies in the volume.  Otherwise each quad is
-// loaded from the nearest place inside the volume (of at least 4 cells along
-// z), and its cells outside the volume become fill as they are written.
-template <typename T, typename LT, bool CLIP>
-__device__ __forceinline__ void stage_window(const FwdJob &J, const Src &S, const StageWalk &W,
-                                             const int (&lo)[3], const float (&g)[3], int ey,
-                                             int pitch, bool inside, uint8_t *s_lds)
-{
-    constexpr int N = kStageChunk;
-    const float zq = (float)(4 * W.ql) + 1.5f;
-    float gz[3];
-#pragma unroll
-    for (int k = 0; k < 3; ++k)
-        gz[k] = CLIP ? __builtin_fmaf(J.inv[3 * k + 2], zq, g[k]) : 0.0f;
-    // whether a sample of the box can use the quad at row (cx, cy) of the window
-    auto reach = [&](int cx, int cy) {
-        if (!CLIP)
-            return true;
-        const float fx = (float)cx, fy = (float)cy;
-        bool r = true;
-#pragma unroll
-        for (int k = 0; k < 3; ++k)
-            r = r && fabsf(__builtin_fmaf(J.inv[3 * k], fx,
-                                          __builtin_fmaf(J.inv[3 * k + 1], fy, gz[k]))) <=
-                         J.reach[k];
-        return r;
-    };
-    constexpr uint32_t kNowhere = 0xffffffffu;     // past the buffer's end: no access, reads 0
-    typename QuadRaw<T>::type w[N];
-    uint32_t l = (uint32_t)(W.row0 * pitch + 4 * W.ql) * (uint32_t)sizeof(LT);
-    const uint32_t step = (uint32_t)(W.rpp * pitch) * (uint32_t)sizeof(LT);
-    int cx = W.cx, cy = W.cy;
-    if (inside) {
-        const int plane = S.ry * S.rsy;                    // elements
-        const uint32_t base = (uint32_t)(lo[0] * plane + lo[1] * S.rsy + lo[2]) *
-                              (uint32_t)sizeof(T);
-        uint32_t o = (uint32_t)(W.cx * plane + cy * S.rsy + 4 * W.ql) * (uint32_t)sizeof(T);
-        const uint32_t d = (uint32_t)(W.step_x * plane + W.step_y * S.rsy) * (uint32_t)sizeof(T);
-        const uint32_t dw = (uint32_t)(plane - ey * S.rsy) * (uint32_t)sizeof(T) + d;
-        for (int p0 = 0; p0 < W.passes; p0 += N) {
-#pragma unroll
-            for (int u = 0; u < N; ++u) {
-                w[u] = QuadRaw<T>::load_at(S.img, p0 + u < W.mine && reach(cx, cy) ? o : kNowhere,
-                                           base);
-                const int c = cy + W.step_y;
-                o += c >= ey ? dw : d;
-                cx += c >= ey ? W.step_x + 1 : W.step_x;
-                cy = c >= ey ? c - ey : c;
-            }
-#pragma unroll
-            for (int u = 0; u < N; ++u)
-                if (p0 + u < W.mine)
-                    QuadRaw<T>::store(w[u], reinterpret_cast<LT *>(s_lds + (l + u * step)));
-            l += N * step;
-        }
-        return;
-    }
-    const int gz0 = lo[2] + 4 * W.ql;
-    const int zc = min(max(gz0, 0), J.nz - 4), s = gz0 - zc;
-    const bool shifted = __any(s != 0);
-    const LT fill = (LT)J.fill;
-    for (int p0 = 0; p0 < W.passes; p0 += N) {
-        uint32_t rows_in = 0;
-#pragma unroll
-        for (int u = 0; u < N; ++u) {
-            const int gx = lo[0] + cx, gy = lo[1] + cy;
-            const bool in = (uint32_t)gx < (uint32_t)J.nx && (uint32_t)gy < (uint32_t)J.ny;
-            rows_in |= (in ? 1u : 0u) << u;
-            w[u] = QuadRaw<T>::load_at(
-                S.img,
-                in && p0 + u < W.mine && reach(cx, cy)
-                    ? elem_index(S, gx, gy, zc) * (uint32_t)sizeof(T)
-                    : kNowhere,
-                0);
-            const int c = cy + W.step_y;
-            cx += c >= ey ? W.step_x + 1 : W.step_x;
-            cy = c >= ey ? c - ey : c;
-        }
-#pragma unroll
-        for (int u = 0; u < N; ++u)
-            if (p0 + u < W.mine) {
-                LT c[4];
-                QuadRaw<T>::cells(w[u], c);
-                LT *dst = reinterpret_cast<LT *>(s_lds + (l + u * step));
-                const bool ok = (rows_in >> u) & 1;
-                if (shifted) {
-                    store_shifted<LT>(c, s, ok, fill, dst);
-                } else {
-#pragma unroll
-                    for (int v = 0; v < 4; ++v)
-                        c[v] = ok ? c[v] : fill;
-                    store4(dst, c);
-                }
-            }
-        l += N * step;
-    }
-}
-
 // Displacement tile (ALIGNED, LT: see fwd_tile_affine).  A displacement has no
 // a-priori footprint bound: the tile (one run of 4 z voxels per thread)
 // computes its coordinates once, reduces their cells, and stages that
@@ -439,7 +265,7 @@ __device__ __forceinline__ void fwd_tile_disp(JobPtr Jp, const Box &B0, const Ti
     float u[3][4];
     if (DISP == kDispSpline)
         spline_tile_u(J.ctrl, J.bs, B.x0, B.y0, B.z0, B.x1, B.y1, B.z1, x, y, z, 1, nvalid, mine,
-                      reinterpret_cast<float *>(s_lds), u);
+                      (int)threadIdx.x, reinterpret_cast<float *>(s_lds), u);
     const float nf[3] = {(float)J.nx, (float)J.ny, (float)J.nz};
     RunQ Q;
     int fmn[3] = {INT_MAX, INT_MAX, INT_MAX}, fmx[3] = {INT_MIN, INT_MIN, INT_MIN};
@@ -487,7 +313,7 @@ __device__ __forceinline__ void fwd_tile_disp(JobPtr Jp, const Box &B0, const Ti
         // whole quads inside the volume: the window of an inside tile may start earlier
         const bool whole = inside && 4 * quads <= J.nz;
         lo[2] = whole ? min(lo[2], J.nz - 4 * quads) : lo[2];
-        const StageWalk W = stage_walk<kThreads>(e[0] * e[1], e[1], quads);
+        const StageWalk W = stage_walk<kThreads>(e[0] * e[1], e[1], quads, (int)threadIdx.x);
         if (W.passes > 0 && J.nz >= 4) {
             const float g[3] = {0.0f, 0.0f, 0.0f};
             stage_window<T, LT, false>(J, S, W, lo, g, e[1], pitch, whole, s_lds);
@@ -535,7 +361,6 @@ __device__ __forceinline__ void fwd_tile_affine(JobPtr Jp, const Box &B0, const 
     {
         const FwdJob &J = *(const FwdJob *)reload(Jp);
         const Tiling SL = {J.sub[0], J.sub[1], J.sub[2]};
-        const int n[3] = {J.nx, J.ny, J.nz};
         const int e[3] = {J.box_e[0], J.box_e[1], J.box_e[2]};
         const int quads = (e[2] + 3) >> 2;
         // sub-tile i in lane i of each wave: its class and the window's first cell
@@ -544,40 +369,12 @@ __device__ __forceinline__ void fwd_tile_affine(JobPtr Jp, const Box &B0, const 
         const int bx = B0.x0 + ((lane >> (nz_log + ny_log)) << SL.lx);
         const int by = B0.y0 + (((lane >> nz_log) & ((1 << ny_log) - 1)) << SL.ly);
         const int bz = B0.z0 + ((lane & ((1 << nz_log) - 1)) << SL.lz);
-        if (J.nx != 0 && J.ny != 0 && J.nz != 0) {
-            float rb[3];
-            row_base(J.M, (float)bx, (float)by, rb);
-            bool outside = false, interior = true;
-            float qc[3];
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                const float q0 = coord(J.M, i, rb, (float)bz);
-                qc[i] = q0 + J.box_mid[i];
-                const float l = q0 + J.box_dn[i], h = q0 + J.box_up[i];
-                outside = outside || h <= -1.0f || l >= (float)n[i];
-                interior = interior && l >= 0.0f && h < (float)(n[i] - 1) &&
-                           (i == 2 ? 4 * quads : e[i]) <= n[i];
-                lo[i] = (int)fminf(fmaxf(floorf(l), -2.0f), (float)n[i]);
-            }
-            cls = outside ? kOutside : interior ? kInterior : kBoundary;
-            // the window inside the volume (interior: every row and quad of it),
-            // inside [-2, n + 2) otherwise
-#pragma unroll
-            for (int i = 0; i < 3; ++i)
-                lo[i] = min(lo[i], cls == kInterior ? n[i] - (i == 2 ? 4 * quads : e[i])
-                                                    : n[i] + 2 - e[i]);
-#pragma unroll
-            for (int k = 0; k < 3; ++k)
-                g[k] = __builtin_fmaf(
-                    J.inv[3 * k], (float)lo[0] - qc[0],
-                    __builtin_fmaf(J.inv[3 * k + 1], (float)lo[1] - qc[1],
-                                   J.inv[3 * k + 2] * ((float)lo[2] - qc[2])));
-        }
+        cls = box_window(J, (float)bx, (float)by, (float)bz, lo, g);
         const int nsub = 1 << (nx_log + ny_log + nz_log);  // at most 32
         todo = (uint32_t)__ballot(lane < nsub && bx <= B0.x1 && by <= B0.y1 && bz <= B0.z1);
         W.passes = 0;
         if (e[0] != 0 && __any(cls != kOutside)) {
-            W = stage_walk<kAffineThreads>(e[0] * e[1], e[1], quads);
+            W = stage_walk<kAffineThreads>(e[0] * e[1], e[1], quads, (int)threadIdx.x);
             fast = W.passes > 0 && J.nz >= 4;
         }
     }
@@ -868,6 +665,15 @@ static bool box_exact(const FwdJob &J)
 // 2.4 times slower on a 512 x 512 x 320 scan) when none fits: false.  As tiles
 // hold at most 2^14 voxels, a tile has at most 32 sub-tiles (the kernels
 // compute one sub-tile's geometry per lane of a wave).
+int32_t set_window(FwdJob &J, const Tiling &S)
+{
+    const int32_t cells = set_box(J, S);
+    set_reach(J, S);
+    if (!box_exact(J))
+        J.box_e[0] = 0;
+    return cells;
+}
+
 bool choose_subtile(FwdJob &J, const Tiling &TL, int32_t lds_cells)
 {
     bool fits = true;
