@@ -125,8 +125,11 @@ template <> struct QuadRaw<int16_t> {
     }
 };
 
-// floor(a / b) for 0 <= a < 2^24, 0 < b < 2^16: FP32 reciprocal estimate and
-// one integer correction step.
+// floor(a / b) for 0 <= a < 2^20, 0 < b < 2^16: FP32 estimate from rcp_b =
+// rcp_small(b), off by at most one (the reciprocal is good to 2^-23 and the product
+// to 2^-24, together less than 2^-2 of a quotient), and one integer correction step.
+// An IEEE quotient for the reciprocal took 11 instructions more, five times a tile.
+__device__ __forceinline__ float rcp_small(int b) { return __builtin_amdgcn_rcpf((float)b); }
 __device__ __forceinline__ int div_small(int a, int b, float rcp_b)
 {
     int q = (int)((float)a * rcp_b);
@@ -184,7 +187,7 @@ struct RowWalk {
     {
         ey = G.e[1];
         rpp = rows_per_pass;
-        const float rcp_y = 1.0f / (float)ey;
+        const float rcp_y = rcp_small(ey);
         step_x = div_small(rpp, ey, rcp_y);            // rpp = step_x * ey + step_y
         step_y = rpp - step_x * ey;
         row = first_row;
@@ -236,7 +239,7 @@ __device__ __forceinline__ void stage_footprint(const FwdJob &J, const Src &S, c
         // qpr lanes per row, floor(256 / qpr) rows per pass; lanes past the
         // last whole row stay idle (ql = qpr)
         lpr = qpr;
-        row0 = div_small(threadIdx.x, qpr, 1.0f / (float)qpr);
+        row0 = div_small(threadIdx.x, qpr, rcp_small(qpr));
         rpp = NT / qpr;
         ql = row0 < rpp ? threadIdx.x - row0 * qpr : qpr;
     } else {
@@ -331,14 +334,14 @@ template <int NT> __device__ __forceinline__ StageWalk stage_walk(int rows, int 
     StageWalk W;
     W.row0 = W.ql = W.cx = W.cy = W.mine = W.step_x = W.step_y = 0;
     W.passes = 0;
-    W.rpp = __builtin_amdgcn_readfirstlane(div_small(NT, quads, 1.0f / (float)quads));
+    W.rpp = __builtin_amdgcn_readfirstlane(div_small(NT, quads, rcp_small(quads)));
     if (W.rpp == 0)
         return W;
     W.passes = __builtin_amdgcn_readfirstlane(
-        div_small(rows + W.rpp - 1, W.rpp, 1.0f / (float)W.rpp));
-    W.row0 = div_small(tid, quads, 1.0f / (float)quads);
+        div_small(rows + W.rpp - 1, W.rpp, rcp_small(W.rpp)));
+    W.row0 = div_small(tid, quads, rcp_small(quads));
     W.ql = tid - W.row0 * quads;
-    const float rcp_y = 1.0f / (float)ey;
+    const float rcp_y = rcp_small(ey);
     W.step_x = __builtin_amdgcn_readfirstlane(div_small(W.rpp, ey, rcp_y));
     W.step_y = W.rpp - W.step_x * ey;
     W.cx = div_small(W.row0, ey, rcp_y);
@@ -504,12 +507,24 @@ __device__ __forceinline__ int box_window(const FwdJob &J, float x, float y, flo
     return cls;
 }
 
-// Minimum over the wave, as a scalar: DPP row shifts and broadcasts (one VALU
-// instruction a step; a shuffle goes through LDS), lane 63 holds the result.
-__device__ __forceinline__ int wave_min(int v)
+// Workgroup-wide min of mn[] and max of mx[] (3 ints each); every thread gets
+// the result, as scalars.  s_red: 4 x 8 ints of LDS, 16-byte aligned.  Contains
+// one barrier; the caller passes another before it calls again.
+//
+// In a wave by DPP row shifts and broadcasts, lane 63 holding the results: one VALU
+// instruction a step (a lane without a source takes the operation's identity, so that
+// the move folds into it; with the lane's own value instead it was three) and the
+// six values in turn (a value's steps wait for each other).  Tiles of 256^3 B-spline
+// warps, bound by vector instructions, spent 150 of 860 here; it is 60.
+__device__ __forceinline__ void block_minmax3(int mn[3], int mx[3], int (*s_red)[8])
 {
+    static_assert(kThreads == 256, "four waves");
+    typedef int i32x4 __attribute__((ext_vector_type(4)));
+    typedef int i32x2 __attribute__((ext_vector_type(2)));
+    int m[6] = {mn[0], mn[1], mn[2], ~mx[0], ~mx[1], ~mx[2]};  // max: min of the complement
 #define CTAUG_DPP_MIN(ctrl, rows)                                                                 \
-    v = min(v, __builtin_amdgcn_update_dpp(v, v, ctrl, rows, 0xF, false))
+    _Pragma("unroll") for (int i = 0; i < 6; ++i) m[i] =                                          \
+        min(m[i], __builtin_amdgcn_update_dpp(INT_MAX, m[i], ctrl, rows, 0xF, false))
     CTAUG_DPP_MIN(0x111, 0xF);         // row_shr:1, 2, 4, 8: lane 15 of each row of 16
     CTAUG_DPP_MIN(0x112, 0xF);
     CTAUG_DPP_MIN(0x114, 0xF);
@@ -517,31 +532,25 @@ __device__ __forceinline__ int wave_min(int v)
     CTAUG_DPP_MIN(0x142, 0xA);         // row_bcast:15 into rows 1 and 3
     CTAUG_DPP_MIN(0x143, 0xC);         // row_bcast:31 into rows 2 and 3
 #undef CTAUG_DPP_MIN
-    return __builtin_amdgcn_readlane(v, 63);
-}
-
-// Workgroup-wide min of mn[] and max of mx[] (3 ints each); every thread gets
-// the result, as scalars.  s_red: 6 x 4 ints of LDS, 16-byte aligned.  Contains
-// one barrier; the caller passes another before it calls again.
-__device__ __forceinline__ void block_minmax3(int mn[3], int mx[3], int (*s_red)[kThreads / 64])
-{
-    static_assert(kThreads == 256, "four waves");
-    typedef int i32x4 __attribute__((ext_vector_type(4)));
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int v = 0;
-#pragma unroll
-    for (int i = 0; i < 6; ++i) {      // max as the minimum of the complement
-        const int m = wave_min(i < 3 ? mn[i] : ~mx[i - 3]);
-        v = lane == i ? m : v;
+    if ((threadIdx.x & 63) == 63) {
+        int *w = s_red[threadIdx.x >> 6];
+        *reinterpret_cast<i32x4 *>(w) = i32x4{m[0], m[1], m[2], m[3]};
+        *reinterpret_cast<i32x2 *>(w + 4) = i32x2{m[4], m[5]};
     }
-    if (lane < 6)
-        s_red[lane][wave] = v;
     __syncthreads();
+    i32x4 a[4];
+    i32x2 b[4];
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        a[w] = *reinterpret_cast<const i32x4 *>(s_red[w]);
+        b[w] = *reinterpret_cast<const i32x2 *>(s_red[w] + 4);
+    }
 #pragma unroll
     for (int i = 0; i < 6; ++i) {
-        const i32x4 r = *reinterpret_cast<const i32x4 *>(s_red[i]);
-        const int m = __builtin_amdgcn_readfirstlane(min(min(r.x, r.y), min(r.z, r.w)));
-        (i < 3 ? mn[i] : mx[i - 3]) = i < 3 ? m : ~m;
+        const int r = i < 4 ? min(min(a[0][i], a[1][i]), min(a[2][i], a[3][i]))
+                            : min(min(b[0][i - 4], b[1][i - 4]), min(b[2][i - 4], b[3][i - 4]));
+        const int s = __builtin_amdgcn_readfirstlane(r);
+        (i < 3 ? mn[i] : mx[i - 3]) = i < 3 ? s : ~s;
     }
 }
 

@@ -319,11 +319,11 @@ __device__ __forceinline__ void load_run_g(JobPtr Jp, const float *__restrict__ 
         gv[k] = row_ok && z + 4 * k < J.oz ? g[v0 + 4 * k] : 0.0f;
 }
 
-// Largest of the wave's values, as a scalar (DPP, as wave_min).
+// Largest of the wave's values, as a scalar (DPP, as in block_minmax3).
 __device__ __forceinline__ uint32_t wave_max(uint32_t v)
 {
 #define CTAUG_DPP_MAX(ctrl, rows)                                                                 \
-    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, ctrl, rows, 0xF, false))
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, rows, 0xF, false))
     CTAUG_DPP_MAX(0x111, 0xF);
     CTAUG_DPP_MAX(0x112, 0xF);
     CTAUG_DPP_MAX(0x114, 0xF);
@@ -353,7 +353,7 @@ __device__ __forceinline__ void flush_cells(const A *s_acc, int planes, int ey, 
     const int xl = max(0, -lox), xh = min(planes, J.nx - lox);
     const int yl = max(0, -loy), ny = min(ey, J.ny - loy) - yl;
     const int lane = tid & 63, lpr = min(ez, 64);
-    const float rcp_l = 1.0f / (float)lpr;
+    const float rcp_l = rcp_small(lpr);
     const int rpw = __builtin_amdgcn_readfirstlane(div_small(64, lpr, rcp_l));
     const int r = div_small(lane, lpr, rcp_l);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -409,7 +409,7 @@ __device__ __forceinline__ void bwd_tile(JobPtr Jp, int t, bool want_ctrl, bool 
                                          float *__restrict__ g_img, float *__restrict__ g_disp,
                                          float *s_ctrl, int32_t lds_cells, int fix_bits,
                                          double (&acc)[12],
-                                         int (*s_red)[kThreads / 64], uint32_t *s_gmax)
+                                         int (*s_red)[8], uint32_t *s_gmax)
 {
     const Tiling TL = kBwdTiling;
     // the thread's index anew for each tile: what follows from it is then computed where
@@ -501,13 +501,8 @@ __device__ __forceinline__ void bwd_tile(JobPtr Jp, int t, bool want_ctrl, bool 
             int fmn[3], fmx[3];
 #pragma unroll
             for (int i = 0; i < 3; ++i) {
-                fmn[i] = fmx[i] = flr_i32(qv[0][i]);
-#pragma unroll
-                for (int k = 1; k < 4; ++k) {
-                    const int f = flr_i32(qv[k][i]);
-                    fmn[i] = min(fmn[i], f);
-                    fmx[i] = max(fmx[i], f);
-                }
+                fmn[i] = flr_i32(fminf(fminf(qv[0][i], qv[1][i]), fminf(qv[2][i], qv[3][i])));
+                fmx[i] = flr_i32(fmaxf(fmaxf(qv[0][i], qv[1][i]), fmaxf(qv[2][i], qv[3][i])));
             }
             block_minmax3(fmn, fmx, s_red);
             __syncthreads();           // a tile without a footprint passes no other
@@ -529,7 +524,8 @@ __device__ __forceinline__ void bwd_tile(JobPtr Jp, int t, bool want_ctrl, bool 
             }
             pitch = lds_pitch(e[2]);
             cls = outside ? kOutside : inside ? kInterior : kBoundary;
-            lds = !outside && (int64_t)e[0] * e[1] * pitch <= lds_cells;
+            lds = !outside && (int64_t)e[0] * e[1] <= lds_cells && pitch <= lds_cells &&
+                  e[0] * e[1] * pitch <= lds_cells;
         }
         if (lds && g_img) {
             // the tile's largest |g| over its guarded samples, as bits: reduced
@@ -846,7 +842,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
         __syncthreads();
     }
 
-    __shared__ __attribute__((aligned(16))) int s_red[6][kThreads / 64];
+    __shared__ __attribute__((aligned(16))) int s_red[4][8];
     __shared__ __attribute__((aligned(16))) uint32_t s_gmax[kThreads / 64];
 
     if constexpr (DISP == kDispNone) {
@@ -907,7 +903,7 @@ k_warp_bwd_batch(const BwdBatch B, double *__restrict__ partials, int32_t lds_ce
     int j = 0;                         // the job holding group gi (uniform)
     for (int i = 1; i < B.njobs; ++i)
         j += B.prefix[i] <= gi;
-    __shared__ __attribute__((aligned(16))) int s_red[6][kThreads / 64];
+    __shared__ __attribute__((aligned(16))) int s_red[4][8];
     __shared__ __attribute__((aligned(16))) uint32_t s_gmax[kThreads / 64];
     __shared__ double red[kThreads / 64][12];
     double acc[12];

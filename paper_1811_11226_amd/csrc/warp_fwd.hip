@@ -256,7 +256,7 @@ __device__ __forceinline__ void fwd_tile_disp(JobPtr Jp, const Box &B0, const Ti
 {
     const FwdJob &J = *(const FwdJob *)reload(Jp);
     Box B = B0;
-    __shared__ __attribute__((aligned(16))) int s_red[6][kThreads / 64];
+    __shared__ __attribute__((aligned(16))) int s_red[4][8];
     const int zr = threadIdx.x & ((1 << (TL.lz - 2)) - 1);
     const int rr = threadIdx.x >> (TL.lz - 2);
     const int x = B.x0 + (rr >> TL.ly), y = B.y0 + (rr & ((1 << TL.ly) - 1)), z = B.z0 + 4 * zr;
@@ -277,19 +277,23 @@ __device__ __forceinline__ void fwd_tile_disp(JobPtr Jp, const Box &B0, const Ti
         row_base(J.M, (float)x, (float)y, rb);
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            if (k >= nvalid)
-                break;
+            const int c = ALIGNED ? k : min(k, nvalid - 1);
             const float zf = (float)(z + k);
 #pragma unroll
             for (int i = 0; i < 3; ++i) {
-                Q.q[i][k] = guard_coord(
+                const float q = guard_coord(
                     coord(J.M, i, rb, zf) +
-                        (DISP == kDispField ? disp[i * nvox + v0 + k] : u[i][k]),
+                        (DISP == kDispField ? disp[i * nvox + v0 + c] : u[i][k]),
                     nf[i]);
-                const int f = flr_i32(Q.q[i][k]);
-                fmn[i] = min(fmn[i], f);
-                fmx[i] = max(fmx[i], f);
+                // past the output's end: the last voxel's
+                Q.q[i][k] = ALIGNED || k < nvalid ? q : Q.q[i][max(k, 1) - 1];
             }
+        }
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const float *q = Q.q[i];
+            fmn[i] = flr_i32(fminf(fminf(q[0], q[1]), fminf(q[2], q[3])));
+            fmx[i] = flr_i32(fmaxf(fmaxf(q[0], q[1]), fmaxf(q[2], q[3])));
         }
     }
     block_minmax3(fmn, fmx, s_red);
@@ -305,9 +309,10 @@ __device__ __forceinline__ void fwd_tile_disp(JobPtr Jp, const Box &B0, const Ti
         inside = inside && lo[i] >= 0 && lo[i] + e[i] <= n[i];
     }
     const int quads = (e[2] + 3) >> 2, pitch = lds_pitch(e[2]);
-    const int64_t cells = (int64_t)e[0] * e[1] * pitch;
+    const bool fits = (int64_t)e[0] * e[1] <= lds_cells && pitch <= lds_cells &&
+                      e[0] * e[1] * pitch <= lds_cells;
     int path = outside ? kPathOutside : kPathDirectBoundary;
-    if (!outside && cells <= lds_cells && (sizeof(LT) == 4 || (J.flags & kFlagFillInT))) {
+    if (!outside && fits && (sizeof(LT) == 4 || (J.flags & kFlagFillInT))) {
         path = inside ? kPathLdsInterior : kPathLdsBoundary;
         const Src S = make_src<T>(J);
         // whole quads inside the volume: the window of an inside tile may start earlier
@@ -825,8 +830,8 @@ __global__ __launch_bounds__(kThreads) void k_warp_labels_diag(FwdJob J, int32_t
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int x = x0 + (int)blockIdx.y;
-    const int sub = SUB ? div_small(lane, L, 1.0f / (float)L) : 0;
-    const int nsub = SUB ? div_small(64, L, 1.0f / (float)L) : 1;      // rows at once
+    const int sub = SUB ? div_small(lane, L, rcp_small(L)) : 0;
+    const int nsub = SUB ? div_small(64, L, rcp_small(L)) : 1;      // rows at once
     const int y0 = ((int)blockIdx.x * (kThreads / 64) + wave) * rows;
     const int y1 = min(y0 + rows, J.oy);
     const rsrc_t src = make_rsrc(J.lbl, (uint32_t)J.in_extent);

@@ -59,6 +59,23 @@ def test_more_tiles_than_rows():
     assert torch.equal(gm, g_M)
 
 
+# Windows with rows of more cells than a wave has lanes: along z 9 and 17 input
+# voxels per output voxel, in the interior and over the volume's ends.
+@pytest.mark.parametrize("nz,scale,shift", [(150, 9.0, 2.0), (150, 9.5, -9.0), (280, 17.0, 3.0),
+                                            (262, 17.0, -2.5)])
+def test_rows_past_a_wave(nz, scale, shift):
+    rng = np.random.default_rng(nz)
+    nin, nout = (9, 7, nz), (8, 5, 16)
+    img = rng.integers(-1000, 2000, nin).astype(np.float32)
+    g = rng.normal(0, 1, nout).astype(np.float32)
+    M = np.array([[1, 0, 0, 0.25], [0, 1, 0, 0.5], [0, 0, scale, shift]], np.float32)
+    r_img, r_M, _ = oracle.warp_backward(img, M, g, fill=-1000.0)
+    g_img, g_M = ctaug.warp_affine_backward(torch.from_numpy(img).cuda(), M,
+                                            torch.from_numpy(g).cuda(), fill=-1000.0)
+    _close(g_img.cpu().numpy(), r_img, "g_img")
+    _close(g_M.cpu().numpy(), r_M, "g_M")
+
+
 @pytest.mark.parametrize("n", [1, 3, 9])
 def test_batches_of_uneven_jobs(n):
     rng = np.random.default_rng(n)
