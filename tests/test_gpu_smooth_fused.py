@@ -31,3 +31,18 @@ def test_fused_smoothing(dims, radii, dtype):
     # weights that are rounded once and sum to 1
     tol = sum(2 * r + 3 for r in radii) * 2.0 ** -24 * np.abs(v.astype(np.float64)).max()
     assert np.abs(out - ref).max() <= tol
+
+
+# Even z extents from addresses that do not allow a lane's two voxels at once.
+@pytest.mark.parametrize("dtype", [torch.float32, torch.int16])
+@pytest.mark.parametrize("off_in,off_out", [(1, 0), (0, 1), (1, 1), (2, 2)])
+def test_misaligned_pairs(dtype, off_in, off_out):
+    dims, sigma = (11, 34, 126), [SIGMA[2], SIGMA[1], SIGMA[3]]
+    n = dims[0] * dims[1] * dims[2]
+    flat = torch.randint(-1000, 2000, (n + 2,), device="cuda").to(dtype)
+    v = flat[off_in:off_in + n].view(dims)
+    out = torch.full((n + 4,), 7.0, device="cuda")
+    ctaug.gaussian_smooth(v, sigma, out=out[off_out:off_out + n].view(dims))
+    ref = ctaug.gaussian_smooth(v.clone(), sigma)
+    assert torch.equal(out[off_out:off_out + n].view(dims), ref)
+    assert (out[:off_out] == 7.0).all() and (out[off_out + n:] == 7.0).all()
