@@ -193,6 +193,16 @@ template <> struct Elem<float> {
     {
         return raw(r, off, soff);
     }
+    // two neighbouring elements, from any element's address
+    static __device__ __forceinline__ void pair(rsrc_t r, uint32_t off, int32_t soff, float &a,
+                                                float &b)
+    {
+        typedef float f32x2 __attribute__((ext_vector_type(2)));
+        const f32x2 v =
+            __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(r, off, soff, 0));
+        a = v.x;
+        b = v.y;
+    }
 };
 template <> struct Elem<int16_t> {
     static __device__ __forceinline__ int16_t raw(rsrc_t r, uint32_t off, int32_t soff)
@@ -202,6 +212,13 @@ template <> struct Elem<int16_t> {
     static __device__ __forceinline__ float load(rsrc_t r, uint32_t off, int32_t soff)
     {
         return (float)raw(r, off, soff);
+    }
+    static __device__ __forceinline__ void pair(rsrc_t r, uint32_t off, int32_t soff, float &a,
+                                                float &b)
+    {
+        const int32_t v = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(r, off, soff, 0);
+        a = (float)(int16_t)(v & 0xffff);
+        b = (float)(v >> 16);
     }
 };
 
@@ -291,16 +308,11 @@ __device__ __forceinline__ float sample_interior(const Src &S, float qx, float q
 {
     const float fx = floorf(qx), fy = floorf(qy), fz = floorf(qz);
     const uint32_t off = elem_index(S, (int32_t)fx, (int32_t)fy, (int32_t)fz) * (uint32_t)sizeof(T);
-    constexpr uint32_t e = sizeof(T);
     float k[8];
-    k[0] = Elem<T>::load(S.img, off, 0);
-    k[1] = Elem<T>::load(S.img, off + e, 0);
-    k[2] = Elem<T>::load(S.img, off, S.sy);
-    k[3] = Elem<T>::load(S.img, off + e, S.sy);
-    k[4] = Elem<T>::load(S.img, off, S.sx);
-    k[5] = Elem<T>::load(S.img, off + e, S.sx);
-    k[6] = Elem<T>::load(S.img, off, S.sxy);
-    k[7] = Elem<T>::load(S.img, off + e, S.sxy);
+    Elem<T>::pair(S.img, off, 0, k[0], k[1]);
+    Elem<T>::pair(S.img, off, S.sy, k[2], k[3]);
+    Elem<T>::pair(S.img, off, S.sx, k[4], k[5]);
+    Elem<T>::pair(S.img, off, S.sxy, k[6], k[7]);
     return tri(k, qx - fx, qy - fy, qz - fz);
 }
 
@@ -312,8 +324,8 @@ __device__ __forceinline__ bool in_guard(float qx, float qy, float qz, int32_t n
 }
 
 // Corners of the cell floor(q) with `fill` for every corner outside the
-// volume.  Requires in_guard(q).  Out-of-volume corners are loaded from the
-// clamped index and then replaced by fill.
+// volume.  Requires in_guard(q).  Rows are loaded at clamped indices, two
+// neighbouring cells at once, and corners out of the volume then replaced by fill.
 template <typename T>
 __device__ __forceinline__ void corners_checked(const Src &S, float qx, float qy, float qz,
                                                 float fill, float k[8], float t[3],
@@ -332,17 +344,21 @@ __device__ __forceinline__ void corners_checked(const Src &S, float qx, float qy
     const bool vz[2] = {iz >= 0, iz + 1 < S.nz};
     const int32_t cx[2] = {max(ix, 0), min(ix + 1, S.nx - 1)};
     const int32_t cy[2] = {max(iy, 0), min(iy + 1, S.ny - 1)};
-    const int32_t cz[2] = {max(iz, 0), min(iz + 1, S.nz - 1)};
+    const int32_t z = max(min(iz, S.nz - 2), 0);           // the pair loaded
+    const bool first = iz == z, second = iz + 1 == z;      // corner 0 is its first; corner 1 is
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int c = 0; c < 2; ++c) {
-                const uint32_t off = elem_index(S, cx[a], cy[b], cz[c]) * (uint32_t)sizeof(T);
-                const float v = Elem<T>::load(S.img, off, 0);
-                k[4 * a + 2 * b + c] = (vx[a] && vy[b] && vz[c]) ? v : fill;
-            }
+        for (int b = 0; b < 2; ++b) {
+            const uint32_t off = elem_index(S, cx[a], cy[b], z) * (uint32_t)sizeof(T);
+            float u, v;
+            if (S.nz > 1)
+                Elem<T>::pair(S.img, off, 0, u, v);
+            else
+                u = v = Elem<T>::load(S.img, off, 0);
+            k[4 * a + 2 * b] = vx[a] && vy[b] && vz[0] ? (first ? u : v) : fill;
+            k[4 * a + 2 * b + 1] = vx[a] && vy[b] && vz[1] ? (second ? u : v) : fill;
+        }
 }
 
 template <typename T>

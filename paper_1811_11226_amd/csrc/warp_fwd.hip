@@ -128,22 +128,21 @@ __device__ __forceinline__ void run_box(JobPtr Jp, const Box &B, int path, const
                                  (float)c10[0], (float)c10[1], (float)c11[0], (float)c11[1]};
             return tri(kk, tx, ty, tz);
         };
+        // Runs past the output's end sample all four voxels where the box is interior or
+        // staged: its window covers the whole box, whatever part of it the output has.
         if (path == kPathLdsInterior) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                if (ALIGNED || k < nvalid)
-                    V[k] = cell(flr_i32(q[k][0]), flr_i32(q[k][1]), flr_i32(q[k][2]),
-                                __builtin_amdgcn_fractf(q[k][0]),
-                                __builtin_amdgcn_fractf(q[k][1]),
-                                __builtin_amdgcn_fractf(q[k][2]));
+                V[k] = cell(flr_i32(q[k][0]), flr_i32(q[k][1]), flr_i32(q[k][2]),
+                            __builtin_amdgcn_fractf(q[k][0]), __builtin_amdgcn_fractf(q[k][1]),
+                            __builtin_amdgcn_fractf(q[k][2]));
                 if (k == 1)
                     __builtin_amdgcn_sched_barrier(0);     // two voxels' corners at a time
             }
             if (labels)                // an interior box's nearest voxels are inside
 #pragma unroll
                 for (int k = 0; k < 4; ++k)
-                    if (ALIGNED || k < nvalid)
-                        L[k] = label_interior(S, q[k][0], q[k][1], q[k][2]);
+                    L[k] = label_interior(S, q[k][0], q[k][1], q[k][2]);
         } else if (path == kPathLdsBoundary) {
             if (DISP == kDispNone) {
                 const float nf[3] = {(float)J.nx, (float)J.ny, (float)J.nz};
@@ -155,35 +154,28 @@ __device__ __forceinline__ void run_box(JobPtr Jp, const Box &B, int path, const
             }
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                if (ALIGNED || k < nvalid) {
-                    const float fx = floorf(q[k][0]), fy = floorf(q[k][1]), fz = floorf(q[k][2]);
-                    V[k] = cell((int)fx, (int)fy, (int)fz, q[k][0] - fx, q[k][1] - fy,
-                                q[k][2] - fz);
-                }
+                const float fx = floorf(q[k][0]), fy = floorf(q[k][1]), fz = floorf(q[k][2]);
+                V[k] = cell((int)fx, (int)fy, (int)fz, q[k][0] - fx, q[k][1] - fy, q[k][2] - fz);
                 if (k & 1)
                     __builtin_amdgcn_sched_barrier(0);
             }
             if (labels)
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
-                    if (ALIGNED || k < nvalid)
-                        L[k] = label_clamped(S, q[k][0], q[k][1], q[k][2], lfill);
+                    L[k] = label_clamped(S, q[k][0], q[k][1], q[k][2], lfill);
                     if (k == 1)
                         __builtin_amdgcn_sched_barrier(0);
                 }
         } else if (DISP == kDispNone && path == kPathDirectInterior) {
+            // the run's loads together: its voxels share lines, which would else be
+            // fetched again
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                if (ALIGNED || k < nvalid)
-                    V[k] = sample_interior<T>(S, q[k][0], q[k][1], q[k][2]);
-                if (k == 1)
-                    __builtin_amdgcn_sched_barrier(0);
-            }
+            for (int k = 0; k < 4; ++k)
+                V[k] = sample_interior<T>(S, q[k][0], q[k][1], q[k][2]);
             if (labels)
 #pragma unroll
                 for (int k = 0; k < 4; ++k)
-                    if (ALIGNED || k < nvalid)
-                        L[k] = label_interior(S, q[k][0], q[k][1], q[k][2]);
+                    L[k] = label_interior(S, q[k][0], q[k][1], q[k][2]);
         } else if (path == kPathDirectBoundary) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
@@ -965,11 +957,38 @@ static int32_t disp_cells(const FwdJob &J)
     return (int32_t)std::min(std::max(cells, (double)least), (double)kDispLdsCells);
 }
 
+// Tile of a single call whose windows fit no reservation and which gathers from memory
+// (no LDS: the 60 KB that held nothing left two workgroups per CU).  Output rows along
+// z as long as they get, as every row of the input is read for itself, and as few
+// voxels beside as fill 256 threads: 128 x 128 x 107 voxels of a 512 x 512 x 320 scan
+// took 54 us in tiles of 8 x 16 x 16, 50 in 8 x 8 x 16, 40 in 4 x 8 x 128, and 55 in
+// 8 x 8 x 128 (too few workgroups).
+static Tiling gather_tiling(const FwdJob &J)
+{
+    int32_t lz = 4;
+    while (lz < 7 && (1 << lz) < J.oz)
+        ++lz;
+    return {lz == 4 ? 3 : 2, 3, lz};
+}
+
 hipError_t launch_warp_single(const FwdJob &J0, const Tiling &TL0, hipStream_t s)
 {
     FwdJob Js = J0;
     const bool displaced = J0.disp || J0.ctrl;
-    const Tiling TL = displaced ? kDispTiling : TL0;
+    const int32_t esz = (Js.flags & kFlagLds16) ? 2 : 4;
+    Tiling TL = displaced ? kDispTiling : TL0;
+    const int32_t bound = displaced ? disp_cells(Js) : footprint_cells_bound(Js, TL);
+    int32_t cells = lds_cells_for(displaced ? bound : std::min(bound, kAffineLdsCells), esz);
+    bool fits = choose_subtile(Js, TL, cells);
+    if (!fits) {
+        cells = lds_cells_for(bound, esz);
+        fits = choose_subtile(Js, TL, cells);
+    }
+    if (!fits && !displaced) {         // gathers from memory
+        TL = gather_tiling(Js);
+        cells = 0;
+        (void)choose_subtile(Js, TL, cells);
+    }
     Js.tiles_x = (Js.ox + (1 << TL.lx) - 1) >> TL.lx;
     Js.tiles_y = (Js.oy + (1 << TL.ly) - 1) >> TL.ly;
     Js.tiles_z = (Js.oz + (1 << TL.lz) - 1) >> TL.lz;
@@ -980,13 +999,6 @@ hipError_t launch_warp_single(const FwdJob &J0, const Tiling &TL0, hipStream_t s
     if (ntiles == 0)
         return hipSuccess;
     const int grid = 8 * xcd_slots(ntiles);
-    const int32_t esz = (J.flags & kFlagLds16) ? 2 : 4;
-    const int32_t bound = displaced ? disp_cells(J) : footprint_cells_bound(J, TL);
-    int32_t cells = lds_cells_for(displaced ? bound : std::min(bound, kAffineLdsCells), esz);
-    if (!choose_subtile(Js, TL, cells)) {
-        cells = lds_cells_for(bound, esz);
-        (void)choose_subtile(Js, TL, cells);
-    }
     const size_t lds = lds_bytes_for(cells, esz);
     const bool aligned = J.oz % 4 == 0;
     if (J.ctrl)

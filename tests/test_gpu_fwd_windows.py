@@ -62,6 +62,29 @@ def test_windows(name, nin, nout, dtype):
         plan.close()
 
 
+# Windows past every reservation: cells gathered in pairs along z, in tiles by the
+# output's z extent.
+@pytest.mark.parametrize("nin,nout", [((90, 80, 150), (9, 7, 17)), ((70, 75, 1), (6, 9, 16)),
+                                      ((81, 64, 2), (9, 8, 1)), ((60, 66, 3), (5, 6, 66)),
+                                      ((40, 90, 300), (3, 10, 130)), ((64, 50, 140), (7, 5, 15))])
+@pytest.mark.parametrize("turn", [False, True])
+@pytest.mark.parametrize("dtype", [np.float32, np.int16])
+def test_gathers(nin, nout, turn, dtype):
+    rng = np.random.default_rng(11)
+    whole = rng.integers(-1000, 2000, tuple(v + 1 for v in nin)).astype(dtype)
+    labels = rng.integers(1, 6, whole.shape).astype(np.int8)
+    box = tuple(slice(1, 1 + v) for v in nin)
+    A = 9.0 * (R if turn else np.diag([1.0, 1.0, min(1.0, nin[2] / (9.0 * nout[2]))]))
+    M = _map(A, nin, nout)
+    ref, lref = oracle.warp(np.ascontiguousarray(whole[box]), M, nout,
+                            lbl=np.ascontiguousarray(labels[box]), fill=-1000.0, label_fill=-3)
+    out, lout = ctaug.warp_affine(torch.from_numpy(whole).cuda()[box], M,
+                                  lbl=torch.from_numpy(labels).cuda()[box], fill=-1000.0,
+                                  label_fill=-3, out_dim=nout)
+    assert np.array_equal(lout.cpu().numpy(), lref)
+    assert np.all(np.abs(out.cpu().numpy() - ref) <= 1e-5 * np.maximum(np.abs(ref), 1000.0))
+
+
 @pytest.mark.parametrize("offset", [0.0, 3.0e6, -5.0e7])
 def test_large_coordinates(offset):
     """Offsets past what the windows admit take the gathers; all is fill there."""
