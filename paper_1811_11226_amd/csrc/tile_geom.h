@@ -5,8 +5,9 @@
 // per axis are the value at the box origin plus the negative / positive parts
 // of A_ij * span_j, widened by a bound on FP32 rounding.  From them: whether
 // every sample of the box fails the guard (outside), whether every trilinear
-// cell lies inside the volume (interior), and the AABB of input cells
-// floor(q) .. floor(q) + 1 of every guarded sample, clamped to [-1, n].
+// cell lies inside the volume (interior), and its window: the input cells
+// floor(q) .. floor(q) + 1 of every sample once coordinates are moved into
+// [-2, n] (guard_coord), of the same extents for all boxes of a job.
 #pragma once
 
 #include "device_common.h"

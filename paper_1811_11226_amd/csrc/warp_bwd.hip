@@ -1,6 +1,7 @@
 // warp_bwd.hip -- adjoint kernels of the warp (gfx950).
 //
-// Persistent workgroups over 8 x 8 x 16 output tiles.  For every output voxel
+// Workgroups take 8 x 8 x 16 output tiles, groups of consecutive ones (affine jobs) or
+// one wave of persistent workgroups (displacements).  For every output voxel
 // the upstream gradient is taken through the adjoint of the photometric chain
 // (gain, zero on the occluded slab), the forward coordinate and cell are
 // recomputed; the eight corner values
@@ -39,10 +40,10 @@
 namespace ctaug {
 
 // Launch shape of the backward pass: 8 x 8 x 16 voxel tiles (one run of 4 z
-// voxels per thread), persistent workgroups striding over their XCD's tiles
-// (xcd_tile), and at most kBwdLdsCells FP32 cells of input footprint per
-// workgroup (48 KB of LDS), used first for the staged image, then as the
-// adjoint accumulators of the same cells.
+// voxels per thread) in the XCD order (xcd_tile); for a displacement kBwdLdsCells
+// FP32 cells of input footprint per workgroup (48 KB of LDS), for an affine job its
+// windows' cells, used first for the staged image, then as the adjoint
+// accumulators of the same cells.
 constexpr Tiling kBwdTiling = {3, 3, 4};
 constexpr int32_t kBwdLdsCells = 12288;
 // An affine job whose windows need more takes up to this (60 KB, two workgroups
