@@ -821,8 +821,7 @@ extern "C" ctaug_status ctaug_warp_bspline_backward(const ctaug_vol *img_in, con
     float *g_disp = reinterpret_cast<float *>(w + m + field);
     double *adj_ws = reinterpret_cast<double *>(w + m + 2 * field);
     if (!empty(J)) {
-        const bool vec = od[2] % 4 == 0;   // workspace offsets are 256-byte aligned
-        if ((st = hip_status(launch_bspline_up(ctrl, G, od, u, vec, s))) != CTAUG_OK)
+        if ((st = hip_status(launch_bspline_up(ctrl, G, od, u, s))) != CTAUG_OK)
             return st;
         J.disp = u;
     }
@@ -843,8 +842,7 @@ extern "C" ctaug_status ctaug_bspline_upsample(const float *ctrl, const int64_t 
         return CTAUG_OK;
     if (!ctrl || !disp)
         return CTAUG_EINVAL;
-    const bool vec = out_dim[2] % 4 == 0 && (reinterpret_cast<uintptr_t>(disp) & 15u) == 0;
-    return hip_status(launch_bspline_up(ctrl, G, out_dim, disp, vec, as_stream(stream)));
+    return hip_status(launch_bspline_up(ctrl, G, out_dim, disp, as_stream(stream)));
 }
 
 extern "C" size_t ctaug_bspline_adjoint_workspace(const int64_t out_dim[3], const int64_t G[3])

@@ -88,7 +88,7 @@ bool bwd_ctrl_fused(const BsplineGeom &B);
 int bspline_max_grid();
 int64_t bspline_adj_ws_bytes(const int64_t od[3], const int64_t G[3]);
 hipError_t launch_bspline_up(const float *ctrl, const int64_t G[3], const int64_t od[3],
-                             float *disp, bool vec, hipStream_t s);
+                             float *disp, hipStream_t s);
 hipError_t launch_bspline_adj(const float *grad_disp, const int64_t od[3], const int64_t G[3],
                               float *grad_ctrl, double *ws, hipStream_t s);
 

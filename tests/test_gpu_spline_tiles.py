@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 import paper_1811_11226_amd as ctaug
 
 pytestmark = pytest.mark.gpu
@@ -49,3 +50,15 @@ def test_tiles_past_the_reservation_gather_the_same(std):
     ok = np.all([(a >= 0) & (a < v) for a, v in zip(at, n)], axis=0)
     ref = np.where(ok, img_np[tuple(np.clip(a, 0, v - 1) for a, v in zip(at, n))], 9.0)
     assert np.array_equal(out.cpu().numpy(), ref.astype(np.float32))
+
+
+# Upsampled fields at the edges of rows of 8 and of z runs of 256, as the parity-mode
+# field.
+@pytest.mark.parametrize("dims,grid", [((1, 1, 1), (4, 4, 4)), ((3, 7, 63), (5, 4, 9)),
+                                       ((2, 8, 64), (4, 6, 64)), ((5, 9, 257), (6, 5, 12)),
+                                       ((2, 17, 255), (4, 64, 5)), ((4, 16, 512), (64, 7, 30))])
+def test_upsampling_rows(dims, grid):
+    rng = np.random.default_rng(sum(dims))
+    c = rng.normal(0, 4, (3,) + grid).astype(np.float32)
+    u = ctaug.bspline_upsample(torch.from_numpy(c).cuda(), dims).cpu().numpy()
+    assert np.array_equal(u, oracle.bspline_upsample_f32(c, dims))
