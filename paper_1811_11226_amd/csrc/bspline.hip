@@ -25,9 +25,8 @@ __global__ __launch_bounds__(kThreads) void k_bspline_up(const float *__restrict
                                                          BsplineGeom G, float *__restrict__ disp)
 {
     __shared__ float P[kUpRows][3][kMaxG];
-    const int nyb = (G.oy + kUpRows - 1) / kUpRows;        // consecutive blocks write on
-    const int x = blockIdx.x / nyb;
-    const int y0 = (blockIdx.x - x * nyb) * kUpRows;
+    const int x = blockIdx.x;
+    const int y0 = blockIdx.y * kUpRows;
     const int rows = min(kUpRows, G.oy - y0);
     const int64_t nvox = (int64_t)G.ox * G.oy * G.oz;
 
@@ -296,8 +295,9 @@ hipError_t launch_bspline_up(const float *ctrl, const int64_t G[3], const int64_
     if (od[0] == 0 || od[1] == 0 || od[2] == 0)
         return hipSuccess;
     const BsplineGeom g = bspline_geom(G, od);
-    const unsigned grid = (unsigned)(od[0] * ((od[1] + kUpRows - 1) / kUpRows));
-    hipLaunchKernelGGL(k_bspline_up, dim3(grid), dim3(kThreads), 0, s, ctrl, g, disp);
+    // x and y apart: together they can pass 2^32 threads in a dimension
+    const dim3 grid((unsigned)od[0], (unsigned)((od[1] + kUpRows - 1) / kUpRows));
+    hipLaunchKernelGGL(k_bspline_up, grid, dim3(kThreads), 0, s, ctrl, g, disp);
     return hipGetLastError();
 }
 
