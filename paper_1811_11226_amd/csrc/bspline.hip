@@ -8,6 +8,8 @@
 #include "device_common.h"
 #include "launch.h"
 
+#include <algorithm>
+
 namespace ctaug {
 
 constexpr int kMaxG = 64;
@@ -86,6 +88,7 @@ __global__ __launch_bounds__(kThreads) void k_bspline_up(const float *__restrict
 // thread per row and per entry (z 47, y 30), now 17.
 constexpr int kAdjRows = 64;           // rows of a chunk: 16 per wave
 constexpr int kAdjSeg = 512;           // voxels along z whose weights are in LDS at once
+constexpr int kAdjGridX = 65536;       // planes in the grid's first dimension (2^32 threads at most)
 
 // CT: tiles of 16 controls along z.  NO: entries of T2 per thread.
 template <int CT, int NO>
@@ -101,7 +104,10 @@ __global__ __launch_bounds__(kThreads) void k_bspline_adj_plane(const float *__r
     __shared__ double s_part[kThreads];
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const float *plane = g + (int64_t)blockIdx.x * G.oy * G.oz;    // block = comp * ox + x
+    const int64_t p = (int64_t)blockIdx.y * kAdjGridX + blockIdx.x;        // comp * ox + x
+    if (p >= 3 * (int64_t)G.ox)
+        return;
+    const float *plane = g + p * G.oy * G.oz;
     const int n2 = G.gy * G.gz, per = kThreads / nsplit;
     const int part = t / per, e0 = t - part * per;
     double acc[NO];
@@ -212,7 +218,7 @@ __global__ __launch_bounds__(kThreads) void k_bspline_adj_plane(const float *__r
             }
         }
     }
-    double *out = T2 + (int64_t)blockIdx.x * n2;
+    double *out = T2 + p * n2;
     if (nsplit > 1) {                  // NO = 1
         s_part[t] = acc[0];
         __syncthreads();
@@ -311,7 +317,9 @@ hipError_t launch_bspline_adj(const float *grad_disp, const int64_t od[3], const
     if (g.ox > 0) {
         const bool vec = od[2] % 4 == 0 && (reinterpret_cast<uintptr_t>(grad_disp) & 15u) == 0;
         const int nsplit = n2 <= 64 ? 4 : n2 <= 128 ? 2 : 1;
-        const dim3 grid((unsigned)(3 * od[0]));
+        const int64_t planes = 3 * od[0];
+        const dim3 grid((unsigned)std::min<int64_t>(planes, kAdjGridX),
+                        (unsigned)((planes + kAdjGridX - 1) / kAdjGridX));
         auto launch = [&](auto kern) {
             hipLaunchKernelGGL(kern, grid, dim3(kThreads), 0, s, grad_disp, g, ws, vec ? 1 : 0,
                                nsplit);

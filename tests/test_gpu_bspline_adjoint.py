@@ -50,3 +50,14 @@ def test_nonfinite_entries_reach_their_own_controls(grid):
         assert np.array_equal(out[comp][~touched], clean[comp][~touched]) or np.allclose(
             out[comp][~touched], clean[comp][~touched], rtol=1e-5, atol=1e-5)
         assert np.all(np.isfinite(out[comp][~touched]))
+
+
+# More planes than the first dimension of the grid holds.
+@pytest.mark.parametrize("nx", [21845, 21846, 50000])
+def test_many_planes(nx):
+    rng = np.random.default_rng(nx)
+    g = rng.normal(0, 1, (3, nx, 2, 1)).astype(np.float32)
+    grid = (4, 4, 4)
+    out = ctaug.bspline_upsample_adjoint(torch.from_numpy(g).cuda(), grid).cpu().numpy()
+    ref = oracle.bspline_adjoint(g, grid)
+    assert np.linalg.norm(out - ref) <= 1e-4 * np.linalg.norm(ref)
