@@ -985,7 +985,12 @@ hipError_t launch_warp_single(const FwdJob &J0, const Tiling &TL0, hipStream_t s
         fits = choose_subtile(Js, TL, cells);
     }
     if (!fits && !displaced) {         // gathers from memory
-        TL = gather_tiling(Js);
+        const Tiling G = gather_tiling(Js);
+        const int64_t tiles = (((int64_t)Js.ox + (1 << G.lx) - 1) >> G.lx) *
+                              (((int64_t)Js.oy + (1 << G.ly) - 1) >> G.ly) *
+                              (((int64_t)Js.oz + (1 << G.lz) - 1) >> G.lz);
+        if (tiles < (int64_t)1 << 23)  // (2^32 threads at most; thin outputs keep theirs)
+            TL = G;
         cells = 0;
         (void)choose_subtile(Js, TL, cells);
     }
