@@ -244,6 +244,26 @@ __device__ __forceinline__ int32_t mad_i24(int32_t a, int32_t s, int32_t c)
     return r;
 }
 
+// An index as mad_i24 reads it: the index below 2^23, 2^24 less from there on.
+// Volumes have up to 2^24 cells along x and y.  Differences of such indices are those
+// of the indices themselves unless 2^23 lies between them, so the address of a cell of
+// the window [lo, lo + e) is exact, from the window's origin, where window24 holds.
+__device__ __forceinline__ int32_t low24(int32_t i) { return (int32_t)((uint32_t)i << 8) >> 8; }
+__device__ __forceinline__ bool window24(int32_t lo, int32_t e)
+{
+    return low24(lo) + e <= 1 << 23;
+}
+
+// What the byte strides sx, sy and sz times mad_i24's indices take as addend, modulo
+// 2^32, for addresses from the first cell of the window at lo.
+__device__ __forceinline__ int32_t window_origin(const int32_t (&lo)[3], int32_t sx, int32_t sy,
+                                                 int32_t sz)
+{
+    return (int32_t)(0u - ((uint32_t)low24(lo[0]) * (uint32_t)sx +
+                           (uint32_t)low24(lo[1]) * (uint32_t)sy +
+                           (uint32_t)lo[2] * (uint32_t)sz));
+}
+
 // at byte offset off + base (base uniform)
 __device__ __forceinline__ int8_t load_i8_at(rsrc_t r, uint32_t off, uint32_t base)
 {

@@ -526,7 +526,8 @@ __device__ __forceinline__ void bwd_tile(JobPtr Jp, int t, bool want_ctrl, bool 
             pitch = lds_pitch(e[2]);
             cls = outside ? kOutside : inside ? kInterior : kBoundary;
             lds = !outside && (int64_t)e[0] * e[1] <= lds_cells && pitch <= lds_cells &&
-                  e[0] * e[1] * pitch <= lds_cells;
+                  e[0] * e[1] * pitch <= lds_cells && window24(lo[0], e[0]) &&
+                  window24(lo[1], e[1]);
         }
         if (lds && g_img) {
             // the tile's largest |g| over its guarded samples, as bits: reduced
@@ -573,7 +574,7 @@ __device__ __forceinline__ void bwd_tile(JobPtr Jp, int t, bool want_ctrl, bool 
     const int x = x0 + xr, y = y0 + yr, z = z0 + zr;
     const bool row_ok = x <= x1 && y <= y1;
     const int sy = 4 * pitch, sx = 4 * sxy;                // bytes
-    const int c0 = -(lo[0] * sx + lo[1] * sy + lo[2] * 4);
+    const int c0 = window_origin(lo, sx, sy, 4);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const bool valid = row_ok && z + 4 * k <= z1;

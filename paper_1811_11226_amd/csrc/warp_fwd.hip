@@ -302,7 +302,8 @@ __device__ __forceinline__ void fwd_tile_disp(JobPtr Jp, const Box &B0, const Ti
     }
     const int quads = (e[2] + 3) >> 2, pitch = lds_pitch(e[2]);
     const bool fits = (int64_t)e[0] * e[1] <= lds_cells && pitch <= lds_cells &&
-                      e[0] * e[1] * pitch <= lds_cells;
+                      e[0] * e[1] * pitch <= lds_cells && window24(lo[0], e[0]) &&
+                      window24(lo[1], e[1]);
     int path = outside ? kPathOutside : kPathDirectBoundary;
     if (!outside && fits && (sizeof(LT) == 4 || (J.flags & kFlagFillInT))) {
         path = inside ? kPathLdsInterior : kPathLdsBoundary;
@@ -328,7 +329,7 @@ __device__ __forceinline__ void fwd_tile_disp(JobPtr Jp, const Box &B0, const Ti
         }
         B.sy = pitch * (int)sizeof(LT);
         B.sx = e[1] * B.sy;
-        B.c0 = -(lo[0] * B.sx + lo[1] * B.sy + lo[2] * (int)sizeof(LT));
+        B.c0 = window_origin(lo, B.sx, B.sy, (int)sizeof(LT));
         __syncthreads();
     }
     run_box<T, LT, ALIGNED, DISP>(Jp, B, path, TL, s_lds, Q);
@@ -402,7 +403,7 @@ __device__ __forceinline__ void fwd_tile_affine(JobPtr Jp, const Box &B0, const 
                               __builtin_amdgcn_readlane(lo[2], i)};
             B.sy = pitch * (int)sizeof(LT);
             B.sx = e1 * B.sy;
-            B.c0 = -(l[0] * B.sx + l[1] * B.sy + l[2] * (int)sizeof(LT));
+            B.c0 = window_origin(l, B.sx, B.sy, (int)sizeof(LT));
             if (used)
                 __syncthreads();       // the last sub-tile has been sampled
             if (fast) {
