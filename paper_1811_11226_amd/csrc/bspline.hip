@@ -250,14 +250,15 @@ __global__ __launch_bounds__(kThreads) void k_bspline_adj_x(const double *__rest
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int e = blockIdx.y * 64 + lane;
-    // planes x0 .. x1 - 1 hold every x with 0 <= gx - ix(x) <= 3 (ix does not decrease;
-    // a plane to spare at either end for the rounding of the estimate)
+    // planes x0 .. x1 - 1 hold every x with 0 <= gx - ix(x) <= 3: ix does not decrease,
+    // and the estimate, ix's own product and a plane number past 2^24 are each rounded by
+    // less than 2^-23 of ox
     int x0 = 0, x1 = G.ox;
     if (G.inv_hx > 0.0f) {
-        const float h = 1.0f / G.inv_hx;
-        x0 = min(max((int)((float)(gx - 3) * h) - 2, 0), G.ox);
+        const float h = 1.0f / G.inv_hx, n = (float)G.ox, spare = 3.0f + n * 0x1p-21f;
+        x0 = min((int)fminf(fmaxf((float)(gx - 3) * h - spare, 0.0f), n), G.ox);
         if (gx < G.gx - 4)
-            x1 = min(max((int)((float)(gx + 1) * h) + 3, 0), G.ox);
+            x1 = min((int)fminf((float)(gx + 1) * h + spare, n), G.ox);
     }
     const int quarter = (max(x1 - x0, 0) + 3) >> 2;
     const int xa = x0 + wave * quarter, xb = min(xa + quarter, x1);
