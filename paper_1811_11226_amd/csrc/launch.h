@@ -100,8 +100,8 @@ struct GaussTaps {
 };
 int32_t gauss_radius(float sigma);
 GaussTaps gauss_taps(float sigma);
-// All axes in one pass (radii of at most 4 on every axis, planes under 2^29
-// voxels).
+// Whether all axes go in one pass: radii of at most 4 on every axis, planes under
+// 2^29 voxels, and a volume for which it is the faster way.
 bool smooth_fused_ok(const int32_t R[3], const int32_t dim[3]);
 hipError_t launch_smooth_fused(const void *in, bool in_i16, float *out, const int32_t dim[3],
                                const float sigma[3], hipStream_t s);

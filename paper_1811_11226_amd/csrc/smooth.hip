@@ -1,10 +1,10 @@
 // smooth.hip -- separable Gaussian smoothing of the resampling pre-step
 // (gfx950).  Each axis is acc = w0 v, then acc = fma(w_d, v(-d) + v(+d), acc)
 // for d = 1 .. R, x first, then y, then z, with edge voxels repeated beyond
-// the volume; FP32 with weights normalised on the host in FP64.  Radii up to
-// kFusedMaxR on every axis take one fused pass (k_smooth_fused), larger ones a
-// pass per axis (k_smooth_axis); both evaluate the same chains, so the
-// results are the same bits.
+// the volume; FP32 with weights normalised on the host in FP64.  One fused pass
+// (k_smooth_fused) where the radii and the volume's size allow and pay for it
+// (smooth_fused_ok), else a pass per axis (k_smooth_axis); both evaluate the same
+// chains, so the results are the same bits.
 #include "device_common.h"
 #include "launch.h"
 
@@ -14,9 +14,9 @@
 namespace ctaug {
 
 // One pass over one axis, one thread per output voxel: the 2R+1 taps come from
-// L1/L2 (neighbouring threads share them).  Only for radii past kFusedMaxR:
-// reading and writing the volume once per axis took 1.29 ms for a
-// 512 x 512 x 320 int16 scan smoothed along all three axes.
+// L1/L2 (neighbouring threads share them).  For radii past kFusedMaxR and small
+// volumes (smooth_fused_ok): reading and writing the volume once per axis took 1.29
+// ms for a 512 x 512 x 320 int16 scan smoothed along all three axes.
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_smooth_axis(const T *__restrict__ in,
                                                           float *__restrict__ out, int32_t nx,
@@ -260,35 +260,77 @@ GaussTaps gauss_taps(float sigma)
     return K;
 }
 
+// Launch shape of the fused pass at largest radius rm: nyt row tiles, nzs z segments of
+// zlen outputs, nxc x chunks of cx planes.  At most 1024 workgroups in all where the
+// chunks decide, which is a round at R = 1 (4 resident per CU), two at R = 2 and 3 (2, by
+// their registers) and four at R = 4 (1); and at least 4 P planes a chunk, as a chunk
+// starts by loading P - 1 planes anew.
+struct FusedShape {
+    int32_t nyt, nzs, zlen, cx, nxc;
+};
+static FusedShape fused_shape(int32_t rm, const int32_t dim[3])
+{
+    const int32_t seg = 2 * (64 - 2 * ((rm + 1) / 2)), rows = kFusedWaves * kRowsOut;
+    FusedShape S;
+    S.nzs = (dim[2] + seg - 1) / seg;
+    S.zlen = ((dim[2] + S.nzs - 1) / S.nzs + 1) & ~1;
+    S.nyt = (dim[1] + rows - 1) / rows;
+    const int64_t tiles = (int64_t)S.nyt * S.nzs;
+    const int32_t most = std::max(1, dim[0] / (4 * (2 * rm + 1)));
+    S.nxc = (int32_t)std::min<int64_t>(most, std::max<int64_t>(1, 1024 / tiles));
+    S.cx = (dim[0] + S.nxc - 1) / S.nxc;
+    S.nxc = (dim[0] + S.cx - 1) / S.cx;
+    return S;
+}
+
+// Whether the axes go in one pass: a plane's byte offsets are 31-bit (scalar offsets of
+// its buffer), radii fit the ring, and it is the faster way.  The fused pass walks its
+// planes in turn, a barrier each, in as many workgroups as the volume gives; a pass per
+// axis is bound by its blocks (one per row and 256 voxels) and, the larger the radius, by
+// its loads, and is not under 5 us a launch.  Times in us, fitted to measurements from
+// 32^3 to 512^2 x 64 voxels: a fused pass takes 3.5 and per plane walked 0.67, 0.87, 1.23
+// or 1.61 (R = 1 .. 4), in each round of resident workgroups; an axis 3, 0.43 per 1000
+// blocks, and per 10^6 voxels 0.33, 0.5, 0.83 or 1.5.  Volumes from 4 * 10^6 voxels on
+// are fused for nearly all radii (there the fused pass is bound by memory).  Per axis
+// against fused, measured: 64^3 R = 4 21 / 107 us; 96^3 R = 2 21 / 25, R = 3 23 / 44; 128 x
+// 128 x 60 R = 2 32 / 23, R = 3 32 / 44; 160 x 160 x 100 R = 3 48 / 44, R = 4 53 / 70; 192
+// x 192 x 96 R = 4 71 / 68, z alone with R = 2 19 / 24.
 bool smooth_fused_ok(const int32_t R[3], const int32_t dim[3])
 {
-    // a plane's byte offsets are 31-bit (scalar offsets of its buffer)
-    return (int64_t)dim[1] * dim[2] < (int64_t)1 << 29 && R[0] <= kFusedMaxR && R[1] <= kFusedMaxR && R[2] <= kFusedMaxR;
+    if ((int64_t)dim[1] * dim[2] >= (int64_t)1 << 29)
+        return false;
+    int32_t rm = 1;
+    for (int a = 0; a < 3; ++a) {
+        if (R[a] > kFusedMaxR)
+            return false;
+        rm = std::max(rm, R[a]);
+    }
+    constexpr double kPlane[kFusedMaxR + 1] = {0.0, 0.67, 0.87, 1.23, 1.61};
+    constexpr double kVoxels[kFusedMaxR + 1] = {0.0, 0.33e-6, 0.5e-6, 0.83e-6, 1.5e-6};
+    constexpr int32_t kResident[kFusedMaxR + 1] = {0, 1024, 512, 512, 256};
+    const FusedShape S = fused_shape(rm, dim);
+    const double groups = (double)S.nyt * S.nzs * S.nxc;
+    const double fused = 3.5 + std::ceil(groups / kResident[rm]) * S.cx * kPlane[rm];
+    const double rows = (double)dim[0] * dim[1];
+    const double axis = 3.0 + 0.43e-3 * rows * ((dim[2] + kThreads - 1) / kThreads);
+    double passes = 0.0;
+    for (int a = 0; a < 3; ++a)
+        passes += R[a] > 0 ? std::max(axis + kVoxels[R[a]] * rows * dim[2], 5.0) : 0.0;
+    return fused <= passes;
 }
 
 template <int RM>
 static void launch_fused_r(const void *in, bool in_i16, float *out, const int32_t dim[3],
                            const FusedTaps &K, hipStream_t s)
 {
-    constexpr int H = (RM + 1) / 2;
-    constexpr int kSeg = 2 * (64 - 2 * H);
-    constexpr int kRows = kFusedWaves * kRowsOut;
-    const int32_t nzs = (dim[2] + kSeg - 1) / kSeg;
-    const int32_t zlen = ((dim[2] + nzs - 1) / nzs + 1) & ~1;
-    const int32_t nyt = (dim[1] + kRows - 1) / kRows;
-    // x chunks: one wave of resident workgroups (4 per CU at most: 32 waves), but
-    // at least 4 P planes each, as a chunk starts by loading P - 1 planes anew
-    const int64_t tiles = (int64_t)nyt * nzs;
-    const int32_t most = std::max(1, dim[0] / (4 * (2 * RM + 1)));
-    const int32_t nxc = (int32_t)std::min<int64_t>(most, std::max<int64_t>(1, 1024 / tiles));
-    const int32_t cx = (dim[0] + nxc - 1) / nxc;
-    const int64_t grid = tiles * ((dim[0] + cx - 1) / cx);
+    const FusedShape S = fused_shape(RM, dim);
+    const int64_t grid = (int64_t)S.nyt * S.nzs * S.nxc;
     const uintptr_t at = reinterpret_cast<uintptr_t>(in);
     const bool pair = dim[2] % 2 == 0 && (reinterpret_cast<uintptr_t>(out) & 7u) == 0 &&
                       (at & (in_i16 ? 3u : 7u)) == 0;
     auto launch = [&](auto kern, auto *src) {
         hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * kFusedWaves), 0, s, src, out,
-                           dim[0], dim[1], dim[2], nyt, nzs, zlen, cx, K);
+                           dim[0], dim[1], dim[2], S.nyt, S.nzs, S.zlen, S.cx, K);
     };
     if (in_i16)
         launch(pair ? &k_smooth_fused<int16_t, RM, true> : &k_smooth_fused<int16_t, RM, false>,
