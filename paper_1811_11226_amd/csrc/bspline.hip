@@ -9,6 +9,7 @@
 #include "launch.h"
 
 #include <algorithm>
+#include <cmath>
 
 namespace ctaug {
 
@@ -236,20 +237,104 @@ __global__ __launch_bounds__(kThreads) void k_bspline_adj_plane(const float *__r
             out[e0 + i * per] = acc[i];
 }
 
-// grad_ctrl[comp][gx][gy][gz] = sum_x B_{gx - ix(x)}(t(x)) T2[comp][x][gy][gz], FP64: block
-// (comp * Gx + gx, 64 entries); each wave sums a quarter of the planes that reach
-// gx, in order, and the quarters are added in order (one thread per entry took 27
-// us for 117 planes, waiting for each load).
+// The same sums in two passes over memory, where a plane has too many rows or controls for
+// one workgroup (bspline_adj_by_planes).  z: T1[comp][x][y][gz] = sum_z B_{gz - iz(z)}(t(z)) g[comp][x][y][z],
+// one thread per (comp, x, y) row streaming z with 16-byte loads when the
+// rows are aligned.  The z-cell index is nondecreasing along the row, so the
+// four controls a voxel touches slide as a window of four FP32 accumulators;
+// each control's sum is stored once, when the window moves past it.
+__global__ __launch_bounds__(kThreads) void k_bspline_adj_z(const float *__restrict__ g,
+                                                            BsplineGeom G, float *__restrict__ T1,
+                                                            int vec)
+{
+    const int64_t nrows = 3 * (int64_t)G.ox * G.oy;
+    const int64_t row = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (row >= nrows)
+        return;
+    const float *src = g + row * G.oz;
+    float *dst = T1 + row * G.gz;
+    float w[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    int32_t cur = 0;
+    auto add = [&](int z, float v) {
+        int32_t iz;
+        float tz, Bz[4];
+        bs_cell(z, G.inv_hz, G.gz, iz, tz);
+        while (cur < iz) {             // controls below iz are complete
+            dst[cur] = w[0];
+            w[0] = w[1];
+            w[1] = w[2];
+            w[2] = w[3];
+            w[3] = 0.0f;
+            ++cur;
+        }
+        bs_basis(tz, Bz);
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            w[c] = __builtin_fmaf(Bz[c], v, w[c]);
+    };
+    if (vec) {
+        for (int z = 0; z < G.oz; z += 4) {
+            const f32x4 v = *reinterpret_cast<const f32x4 *>(src + z);
+            add(z, v.x);
+            add(z + 1, v.y);
+            add(z + 2, v.z);
+            add(z + 3, v.w);
+        }
+    } else {
+        for (int z = 0; z < G.oz; ++z)
+            add(z, src[z]);
+    }
+    for (int c = 0; c < 4; ++c)
+        dst[cur + c] = w[c];
+    for (int gz = cur + 4; gz < G.gz; ++gz)
+        dst[gz] = 0.0f;
+}
+
+// y: T2[comp][x][gy][gz] = sum_y B_{gy - iy(y)}(t(y)) T1[comp][x][y][gz], FP64,
+// one thread per output, y in a fixed order.
+__global__ __launch_bounds__(kThreads) void k_bspline_adj_y(const float *__restrict__ T1,
+                                                            BsplineGeom G, double *__restrict__ T2)
+{
+    const int64_t total = 3 * (int64_t)G.ox * G.gy * G.gz;
+    const int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (e >= total)
+        return;
+    const int gz = (int)(e % G.gz);
+    const int gy = (int)((e / G.gz) % G.gy);
+    const int64_t cx = e / ((int64_t)G.gz * G.gy);          // comp * ox + x
+    // rows y whose cell reaches control gy: iy in [gy - 3, gy]
+    double s = 0.0;
+    for (int y = 0; y < G.oy; ++y) {
+        int32_t iy;
+        float ty, By[4];
+        bs_cell(y, G.inv_hy, G.gy, iy, ty);
+        const int b = gy - iy;
+        if (b < 0 || b > 3)
+            continue;
+        bs_basis(ty, By);
+        s += (double)By[b] * (double)T1[(cx * G.oy + y) * G.gz + gz];
+    }
+    T2[e] = s;
+}
+
+// grad_ctrl[comp][gx][gy][gz] = sum_x B_{gx - ix(x)}(t(x)) T2[comp][x][gy][gz], FP64: blocks
+// of control plane comp * Gx + gx.  SPLIT: 64 entries a block; each wave sums a quarter of
+// the planes that reach gx, in order, and the quarters are added in order (one thread per
+// entry took 27 us for 117 planes, waiting for each load).  Otherwise 256 entries, all
+// planes in order: up to 16 of them are in flight at once, and the quarters would cost
+// more than they save (4 to 30 planes with 64^3 controls: 4 to 12 % slower).
+constexpr int kAdjSplitPlanes = 16;
+
+template <bool SPLIT>
 __global__ __launch_bounds__(kThreads) void k_bspline_adj_x(const double *__restrict__ T2,
                                                             BsplineGeom G,
                                                             float *__restrict__ grad_ctrl)
 {
-    __shared__ double s_part[kThreads / 64][64];
     const int n2 = G.gy * G.gz;
     const int comp = blockIdx.x / G.gx, gx = blockIdx.x - comp * G.gx;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int e = blockIdx.y * 64 + lane;
+    const int e = SPLIT ? blockIdx.y * 64 + lane : blockIdx.y * kThreads + threadIdx.x;
     // planes x0 .. x1 - 1 hold every x with 0 <= gx - ix(x) <= 3: ix does not decrease,
     // and the estimate, ix's own product and a plane number past 2^24 are each rounded by
     // less than 2^-23 of ox
@@ -260,8 +345,8 @@ __global__ __launch_bounds__(kThreads) void k_bspline_adj_x(const double *__rest
         if (gx < G.gx - 4)
             x1 = min((int)fminf((float)(gx + 1) * h + spare, n), G.ox);
     }
-    const int quarter = (max(x1 - x0, 0) + 3) >> 2;
-    const int xa = x0 + wave * quarter, xb = min(xa + quarter, x1);
+    const int quarter = SPLIT ? (max(x1 - x0, 0) + 3) >> 2 : 0;
+    const int xa = SPLIT ? x0 + wave * quarter : x0, xb = SPLIT ? min(xa + quarter, x1) : x1;
     const double *src = T2 + (int64_t)comp * G.ox * n2 + min(e, n2 - 1);
     double s = 0.0;
 #pragma unroll 8
@@ -275,17 +360,22 @@ __global__ __launch_bounds__(kThreads) void k_bspline_adj_x(const double *__rest
         const double v = src[(int64_t)x * n2];
         s = (uint32_t)a < 4u ? s + (double)w * v : s;
     }
-    s_part[wave][lane] = s;
-    __syncthreads();
-    if (wave == 0 && e < n2)
-        grad_ctrl[(int64_t)blockIdx.x * n2 + e] =
-            (float)(((s_part[0][lane] + s_part[1][lane]) + s_part[2][lane]) + s_part[3][lane]);
+    if constexpr (SPLIT) {
+        __shared__ double s_part[kThreads / 64][64];
+        s_part[wave][lane] = s;
+        __syncthreads();
+        if (wave == 0 && e < n2)
+            grad_ctrl[(int64_t)blockIdx.x * n2 + e] =
+                (float)(((s_part[0][lane] + s_part[1][lane]) + s_part[2][lane]) + s_part[3][lane]);
+    } else if (e < n2) {
+        grad_ctrl[(int64_t)blockIdx.x * n2 + e] = (float)s;
+    }
 }
 
 int bspline_max_grid() { return kMaxG; }
 
-// Workspace of the adjoint: T2 (FP64, 3 x ox x Gy x Gz), from its start.  (Callers'
-// workspaces still hold what a pass of its own over z would need besides.)
+// Workspace of the adjoint: T1 (FP32, 3 x ox x oy x Gz; the passes' alone), then T2 (FP64,
+// 3 x ox x Gy x Gz) at a 256-byte aligned offset.
 static int64_t adj_t1_bytes(const int64_t od[3], const int64_t G[3])
 {
     return ((3 * od[0] * od[1] * G[2] * (int64_t)sizeof(float)) + 255) & ~(int64_t)255;
@@ -308,6 +398,33 @@ hipError_t launch_bspline_up(const float *ctrl, const int64_t G[3], const int64_
     return hipGetLastError();
 }
 
+// Whether the z and y sums go plane by plane (k_bspline_adj_plane) or in a pass each.  A
+// plane's workgroup walks 64 rows at a time, 16 voxels a step, then adds these rows to
+// its entries one after the other, so its time grows with the plane and the grid,
+// whatever else is idle; the passes take every row and every entry at once, but read
+// and write the field's rows singly.  Estimates in us, fitted to 430 pairs of 33 fields
+// (20^3 to 256^3, 20000 x 1 x 4 to 1 x 2000 x 2000) and 13 grids, of which they choose the
+// slower one by more than 7 % in three.  Passes against planes, measured: 128^3 with 8^3
+// controls 55 / 28, 16^3 45 / 32, 32^3 47 / 53, 64^3 108 / 119; 16 x 512 x 512 with 8^3
+// 150 / 153, 32^3 105 / 375; 1 x 2000 x 2000 with 8^3 549 / 2530; 8 x 8 x 4000 with 8^3
+// 300 / 110; 512 x 512 x 64 with 32^3 618 / 302.
+bool bspline_adj_by_planes(const BsplineGeom &g, bool vec)
+{
+    const double planes = 3.0 * g.ox, n2 = (double)g.gy * g.gz;
+    const double rows = n2 <= 64 ? 16.0 : n2 <= 128 ? 32.0 : 64.0;     // per thread of a chunk
+    const double entry = n2 > 4 * kThreads                        ? 0.77
+                         : g.gz > 16 || n2 > (double)kThreads ? 0.17
+                                                              : 0.08;
+    const double chunk = std::ceil(g.oz / 16.0) * (g.gz > 16 ? 0.9 : 0.52) + rows * entry;
+    const double by_planes = std::ceil(g.oy / (double)kAdjRows) * chunk *
+                             std::pow(std::max(1.0, planes / 900.0), 0.75);
+    const double z = std::max(g.oz * (vec ? 0.086 : 0.18),
+                              planes * g.oy * g.oz * (vec ? 1.7e-6 : 5.6e-6));
+    const double y = g.oy * (0.045 + 0.20 * std::min(1.0, 4.0 / (g.gy - 3))) +
+                     planes * n2 * g.oy * 0.17e-6;
+    return by_planes <= z + y + 3.4;
+}
+
 hipError_t launch_bspline_adj(const float *grad_disp, const int64_t od[3], const int64_t G[3],
                               float *grad_ctrl, double *ws, hipStream_t s)
 {
@@ -315,33 +432,50 @@ hipError_t launch_bspline_adj(const float *grad_disp, const int64_t od[3], const
     if (od[0] == 0 || od[1] == 0 || od[2] == 0)
         g.ox = 0;                      // no voxels: every control gradient is 0
     const int n2 = g.gy * g.gz;
+    float *T1 = reinterpret_cast<float *>(ws);
+    double *T2 = reinterpret_cast<double *>(reinterpret_cast<char *>(ws) + adj_t1_bytes(od, G));
     if (g.ox > 0) {
         const bool vec = od[2] % 4 == 0 && (reinterpret_cast<uintptr_t>(grad_disp) & 15u) == 0;
-        const int nsplit = n2 <= 64 ? 4 : n2 <= 128 ? 2 : 1;
         const int64_t planes = 3 * od[0];
-        const dim3 grid((unsigned)std::min<int64_t>(planes, kAdjGridX),
-                        (unsigned)((planes + kAdjGridX - 1) / kAdjGridX));
-        auto launch = [&](auto kern) {
-            hipLaunchKernelGGL(kern, grid, dim3(kThreads), 0, s, grad_disp, g, ws, vec ? 1 : 0,
-                               nsplit);
-        };
-        if (g.gz <= 16) {
-            if (n2 <= kThreads)
-                launch(&k_bspline_adj_plane<1, 1>);
-            else
-                launch(&k_bspline_adj_plane<1, 4>);            // at most 64 x 16
-        } else if (n2 <= 4 * kThreads) {
-            launch(&k_bspline_adj_plane<4, 4>);
+        if (bspline_adj_by_planes(g, vec)) {
+            const int nsplit = n2 <= 64 ? 4 : n2 <= 128 ? 2 : 1;
+            const dim3 grid((unsigned)std::min<int64_t>(planes, kAdjGridX),
+                            (unsigned)((planes + kAdjGridX - 1) / kAdjGridX));
+            auto launch = [&](auto kern) {
+                hipLaunchKernelGGL(kern, grid, dim3(kThreads), 0, s, grad_disp, g, T2, vec ? 1 : 0,
+                                   nsplit);
+            };
+            if (g.gz <= 16) {
+                if (n2 <= kThreads)
+                    launch(&k_bspline_adj_plane<1, 1>);
+                else
+                    launch(&k_bspline_adj_plane<1, 4>);        // at most 64 x 16
+            } else if (n2 <= 4 * kThreads) {
+                launch(&k_bspline_adj_plane<4, 4>);
+            } else {
+                launch(&k_bspline_adj_plane<4, 16>);
+            }
         } else {
-            launch(&k_bspline_adj_plane<4, 16>);
+            auto blocks = [](int64_t n) { return dim3((unsigned)((n + kThreads - 1) / kThreads)); };
+            hipLaunchKernelGGL(k_bspline_adj_z, blocks(planes * od[1]), dim3(kThreads), 0, s,
+                               grad_disp, g, T1, vec ? 1 : 0);
+            hipError_t e = hipGetLastError();
+            if (e != hipSuccess)
+                return e;
+            hipLaunchKernelGGL(k_bspline_adj_y, blocks(planes * n2), dim3(kThreads), 0, s, T1, g,
+                               T2);
         }
         hipError_t e = hipGetLastError();
         if (e != hipSuccess)
             return e;
     }
-    hipLaunchKernelGGL(k_bspline_adj_x,
-                       dim3((unsigned)(3 * g.gx), (unsigned)((n2 + 63) / 64)), dim3(kThreads), 0, s,
-                       ws, g, grad_ctrl);
+    // planes that reach a control: its four cells' of h
+    const double reach = std::min((double)g.ox, 4.0 * g.ox / (g.gx - 3) + 2.0);
+    const bool split = reach > kAdjSplitPlanes;
+    const int per = split ? 64 : kThreads;
+    hipLaunchKernelGGL(split ? &k_bspline_adj_x<true> : &k_bspline_adj_x<false>,
+                       dim3((unsigned)(3 * g.gx), (unsigned)((n2 + per - 1) / per)),
+                       dim3(kThreads), 0, s, T2, g, grad_ctrl);
     return hipGetLastError();
 }
 

@@ -89,6 +89,8 @@ int bspline_max_grid();
 int64_t bspline_adj_ws_bytes(const int64_t od[3], const int64_t G[3]);
 hipError_t launch_bspline_up(const float *ctrl, const int64_t G[3], const int64_t od[3],
                              float *disp, hipStream_t s);
+// Whether the adjoint's z and y sums go plane by plane; vec: rows of whole, aligned quads.
+bool bspline_adj_by_planes(const BsplineGeom &g, bool vec);
 hipError_t launch_bspline_adj(const float *grad_disp, const int64_t od[3], const int64_t G[3],
                               float *grad_ctrl, double *ws, hipStream_t s);
 
