@@ -15,22 +15,26 @@ namespace ctaug {
 
 constexpr int kMaxG = 64;
 
-// Upsampling, kUpRows rows y of one x per workgroup (a wave takes every fourth).  The
-// bound is writing the field, so what a voxel costs besides its 12 FMAs is shared:
-// the rows' profiles are summed in one go, and a thread computes the cells and
-// weights of its four z once for all its rows.  Neighbouring lanes take neighbouring z,
-// so that rows of any extent are stored whole.  With four rows and four z in a row per
-// lane: 117 x 130 x 151 in 16.3 us, now 10.4; 200 x 190 x 210 in 42, now 24; 256^3
-// 42, now 39 (5.2 TB/s).  4 rows: 12, 29, 45.
+// Upsampling, nrows (up to kUpRows) rows y of one x and zlen voxels of them per workgroup
+// (a wave takes every fourth row).  The bound is writing the field, so what a voxel costs
+// besides its 12 FMAs is shared: the rows' profiles are summed in one go, and a thread
+// computes the cells and weights of its four z once for all its rows.  Neighbouring lanes
+// take neighbouring z, so that rows of any extent are stored whole.  With four rows and
+// four z in a row per lane: 117 x 130 x 151 in 16.3 us, now 10.4; 200 x 190 x 210 in 42,
+// now 24; 256^3 42, now 39 (5.2 TB/s).  4 rows: 12, 29, 45; but four rows, and rows in
+// parts, where whole rows by eight leave CUs idle (8 x 8 x 4000 18.5 us a call, now 8.0; 1 x 2000 x
+// 2000 with 64^3 controls 16.6, now 13.8).
 constexpr int kUpRows = 8;
+constexpr int kUpBlocks = 1024;        // workgroups wanted: four per CU
 
 __global__ __launch_bounds__(kThreads) void k_bspline_up(const float *__restrict__ ctrl,
-                                                         BsplineGeom G, float *__restrict__ disp)
+                                                         BsplineGeom G, float *__restrict__ disp,
+                                                         int nrows, int zlen)
 {
     __shared__ float P[kUpRows][3][kMaxG];
     const int x = blockIdx.x;
-    const int y0 = blockIdx.y * kUpRows;
-    const int rows = min(kUpRows, G.oy - y0);
+    const int y0 = blockIdx.y * nrows;
+    const int rows = min(nrows, G.oy - y0);
     const int64_t nvox = (int64_t)G.ox * G.oy * G.oz;
 
     for (int e = threadIdx.x; e < rows * 3 * G.gz; e += kThreads) {
@@ -42,7 +46,8 @@ __global__ __launch_bounds__(kThreads) void k_bspline_up(const float *__restrict
     __syncthreads();
 
     const int lane = threadIdx.x & 63;
-    for (int z = lane; z < G.oz; z += 256) {
+    const int z0 = blockIdx.z * zlen, z1 = min(z0 + zlen, G.oz);
+    for (int z = z0 + lane; z < z1; z += 256) {
         int32_t iz[4];
         float Bz[4][4];
 #pragma unroll
@@ -66,7 +71,7 @@ __global__ __launch_bounds__(kThreads) void k_bspline_up(const float *__restrict
                 }
 #pragma unroll
             for (int k = 0; k < 4; ++k)
-                if (z + 64 * k < G.oz)
+                if (z + 64 * k < z1)
 #pragma unroll
                     for (int comp = 0; comp < 3; ++comp)
                         out[comp * nvox + 64 * k] = u[comp][k];
@@ -393,8 +398,14 @@ hipError_t launch_bspline_up(const float *ctrl, const int64_t G[3], const int64_
         return hipSuccess;
     const BsplineGeom g = bspline_geom(G, od);
     // x and y apart: together they can pass 2^32 threads in a dimension
-    const dim3 grid((unsigned)od[0], (unsigned)((od[1] + kUpRows - 1) / kUpRows));
-    hipLaunchKernelGGL(k_bspline_up, grid, dim3(kThreads), 0, s, ctrl, g, disp);
+    const int64_t by8 = od[0] * ((od[1] + kUpRows - 1) / kUpRows);
+    const int nrows = by8 <= kUpBlocks ? kUpRows / 2 : kUpRows;
+    const int64_t ny = (od[1] + nrows - 1) / nrows, runs = (od[2] + 255) / 256;
+    const int64_t nz = std::min(runs, std::max<int64_t>(1, kUpBlocks / (od[0] * ny)));
+    const int64_t zlen = 256 * ((runs + nz - 1) / nz);
+    const dim3 grid((unsigned)od[0], (unsigned)ny, (unsigned)((od[2] + zlen - 1) / zlen));
+    hipLaunchKernelGGL(k_bspline_up, grid, dim3(kThreads), 0, s, ctrl, g, disp, nrows,
+                       (int)zlen);
     return hipGetLastError();
 }
 
