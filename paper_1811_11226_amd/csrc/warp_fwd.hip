@@ -553,52 +553,49 @@ __global__ __launch_bounds__(batch_threads(MODE)) void k_warp_batch(const FwdJob
     }
 }
 
-// Upper bound on the footprint cells of any tile of job J (see box_geom).
-int32_t footprint_cells_bound(const FwdJob &J, const Tiling &TL)
-{
-    const int t[3] = {1 << TL.lx, 1 << TL.ly, 1 << TL.lz};
-    const int n[3] = {J.nx, J.ny, J.nz};
-    int64_t cells = 1;
-    for (int i = 0; i < 3; ++i) {
-        double span = 2.0 * (double)J.delta[i];
-        for (int j = 0; j < 3; ++j)
-            span += std::fabs((double)J.M[4 * i + j]) * (double)(t[j] - 1);
-        int64_t e = std::min<int64_t>((int64_t)std::floor(span) + 3, (int64_t)n[i] + 2);
-        e = std::max<int64_t>(e, 1);
-        if (i == 2)
-            e = lds_pitch((int32_t)e);       // LDS row pitch
-        cells *= e;
-        if (cells > (int64_t)1 << 30)
-            return 1 << 30;
-    }
-    return (int32_t)cells;
-}
-
-// The footprint window of sub-tile shape S of job J (FwdJob::box_*); its LDS
-// cells.  The window of axis i holds the cells floor(l) .. floor(h) + 1 of any
-// coordinate range [l, h] of width at most span (delta on either side
-// included): floor(span) + 3, and no more than the n + 4 cells [-2, n + 2) that
-// clamped coordinates reach.
-static int32_t set_box(FwdJob &J, const Tiling &S)
+// The footprint window of sub-tile shape S of job J: the range (dn, up) of axis i about
+// its first voxel's coordinate, its cells e[i], and the LDS cells of the whole.  The window
+// of axis i holds the cells floor(l) .. floor(h) + 1 of any coordinate range [l, h] of width
+// at most span (delta on either side included): floor(span) + 3, and no more than the n + 4
+// cells [-2, n + 2) that clamped coordinates reach.
+static int32_t window_cells(const FwdJob &J, const Tiling &S, double (&dn)[3], double (&up)[3],
+                            int32_t (&e)[3])
 {
     const int t[3] = {1 << S.lx, 1 << S.ly, 1 << S.lz};
     const int n[3] = {J.nx, J.ny, J.nz};
     int64_t cells = 1;
     for (int i = 0; i < 3; ++i) {
-        double dn = -(double)J.delta[i], up = (double)J.delta[i];
+        dn[i] = -(double)J.delta[i];
+        up[i] = (double)J.delta[i];
         for (int j = 0; j < 3; ++j) {
             const double d = (double)J.M[4 * i + j] * (double)(t[j] - 1);
-            (d < 0.0 ? dn : up) += d;
+            (d < 0.0 ? dn[i] : up[i]) += d;
         }
-        J.box_dn[i] = (float)dn;
-        J.box_up[i] = (float)up;
-        const double e = std::min(std::floor(up - dn) + 3.0, (double)n[i] + 4.0);
-        J.box_e[i] = (int32_t)e;
-        if (i == 2)
-            J.box_pitch = lds_pitch(J.box_e[2]);
-        cells = std::min<int64_t>(cells * (i == 2 ? J.box_pitch : J.box_e[i]), (int64_t)1 << 30);
+        e[i] = (int32_t)std::min({std::floor(up[i] - dn[i]) + 3.0, (double)n[i] + 4.0, 0x1p30});
+        cells = std::min<int64_t>(cells * (i == 2 ? lds_pitch(e[2]) : e[i]), (int64_t)1 << 30);
     }
     return (int32_t)cells;
+}
+
+// LDS cells that hold the window of any tile of job J.
+int32_t footprint_cells_bound(const FwdJob &J, const Tiling &TL)
+{
+    double dn[3], up[3];
+    int32_t e[3];
+    return window_cells(J, TL, dn, up, e);
+}
+
+// The window of sub-tile shape S into FwdJob::box_*; its LDS cells.
+static int32_t set_box(FwdJob &J, const Tiling &S)
+{
+    double dn[3], up[3];
+    const int32_t cells = window_cells(J, S, dn, up, J.box_e);
+    for (int i = 0; i < 3; ++i) {
+        J.box_dn[i] = (float)dn[i];
+        J.box_up[i] = (float)up[i];
+    }
+    J.box_pitch = lds_pitch(J.box_e[2]);
+    return cells;
 }
 
 // Which quads of the window the samples of sub-tile shape S can use
