@@ -959,17 +959,14 @@ static int32_t disp_cells(const FwdJob &J)
 }
 
 // Tile of a single call whose windows fit no reservation and which gathers from memory
-// (no LDS: the 60 KB that held nothing left two workgroups per CU).  Output rows along
-// z as long as they get, as every row of the input is read for itself, and as few
-// voxels beside as fill 256 threads: 128 x 128 x 107 voxels of a 512 x 512 x 320 scan
-// took 54 us in tiles of 8 x 16 x 16, 50 in 8 x 8 x 16, 40 in 4 x 8 x 128, and 55 in
-// 8 x 8 x 128 (too few workgroups).
+// (no LDS: the 60 KB that held nothing left two workgroups per CU): 4 x 8 x 32 voxels.
+// Along z a tile reads whole lines of few rows where the map keeps to the rows (128 x 128 x
+// 107 voxels of a 512 x 512 x 320 int16 scan: 20 us; 31 in 8 x 16 x 16, 28 in 8 x 8 x 16, 29 in
+// 4 x 8 x 128); where it turns, a long tile spreads over as many rows as voxels (turned by
+// 10 degrees 84 us; 91, 87, 143; 160 x 160 x 120 of 400 x 400 x 300 82; 100, 77, 251).
 static Tiling gather_tiling(const FwdJob &J)
 {
-    int32_t lz = 4;
-    while (lz < 7 && (1 << lz) < J.oz)
-        ++lz;
-    return {lz == 4 ? 3 : 2, 3, lz};
+    return J.oz > 16 ? Tiling{2, 3, 5} : Tiling{3, 3, 4};
 }
 
 hipError_t launch_warp_single(const FwdJob &J0, const Tiling &TL0, hipStream_t s)
