@@ -958,6 +958,21 @@ static int32_t disp_cells(const FwdJob &J)
     return (int32_t)std::min(std::max(cells, (double)least), (double)kDispLdsCells);
 }
 
+// Whether the sub-tile windows of an affine job (choose_subtile) are worth staging.  A
+// voxel reads 8 cells, so a window of many cells per voxel costs more than it shares.
+// Where z runs keep to an input row, gathers read whole lines, and win from 10 cells per
+// voxel on (512 x 512 x 320 int16 to 256 x 256 x 160: 81 us staged, 42 gathered; FP32 95 and
+// 73; at 8 cells and a factor of 1.8 they take 0.9 to 1.2 times as long); and always where
+// only sub-tiles of 4 voxels along z fit (400 x 400 x 300 to 160 x 160 x 120 turned by 2
+// degrees: int16 100 and 55 us, FP32 141 and 78).
+static bool staging_pays(const FwdJob &J)
+{
+    const double cells = (double)J.box_e[0] * J.box_e[1] * J.box_pitch;
+    const double voxels = (double)(1 << (J.sub[0] + J.sub[1] + J.sub[2]));
+    const double rows = 31.0 * (std::fabs((double)J.M[2]) + std::fabs((double)J.M[6]));
+    return !(rows < 0.25 && cells >= 10.0 * voxels) && (J.sub[2] > 2 || J.oz <= 4);
+}
+
 // Tile of a single call whose windows fit no reservation and which gathers from memory
 // (no LDS: the 60 KB that held nothing left two workgroups per CU): 4 x 8 x 32 voxels.
 // Along z a tile reads whole lines of few rows where the map keeps to the rows (128 x 128 x
@@ -977,11 +992,7 @@ hipError_t launch_warp_single(const FwdJob &J0, const Tiling &TL0, hipStream_t s
     Tiling TL = displaced ? kDispTiling : TL0;
     const int32_t bound = displaced ? disp_cells(Js) : footprint_cells_bound(Js, TL);
     int32_t cells = lds_cells_for(displaced ? bound : std::min(bound, kAffineLdsCells), esz);
-    bool fits = choose_subtile(Js, TL, cells);
-    if (!fits) {
-        cells = lds_cells_for(bound, esz);
-        fits = choose_subtile(Js, TL, cells);
-    }
+    const bool fits = choose_subtile(Js, TL, cells) && (displaced || staging_pays(Js));
     if (!fits && !displaced) {         // gathers from memory
         const Tiling G = gather_tiling(Js);
         const int64_t tiles = (((int64_t)Js.ox + (1 << G.lx) - 1) >> G.lx) *
