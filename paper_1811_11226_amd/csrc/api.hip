@@ -1063,7 +1063,7 @@ ctaug_status apply_tiling(ctaug_batch_plan *p, const ctaug_tuning &t)
     } else if (t.lds_cells == 0) {
         // the largest footprint of the current jobs, with headroom for later
         // updates, up to kAffineLdsCells unless a job needs more; tiles that
-        // still exceed it are staged as sub-tiles
+        // still exceed it are staged as sub-tiles, or gather
         int64_t need = 0;
         for (int i = 0; i < p->n; ++i)
             need = std::max<int64_t>(need, footprint_cells_bound(p->jobs[i], TL));
@@ -1071,8 +1071,8 @@ ctaug_status apply_tiling(ctaug_batch_plan *p, const ctaug_tuning &t)
         cells = lds_cells_for((int32_t)need, p->elem_bytes);
         const int32_t few = kAffineLdsCells * 4 / p->elem_bytes;
         bool fits = true;
-        for (int i = 0; i < p->n; ++i)
-            fits = choose_subtile(p->jobs[i], TL, few) && fits;
+        for (int i = 0; i < p->n; ++i)     // (gathers along rows take all workgroups they get)
+            fits = (choose_subtile(p->jobs[i], TL, few) || keeps_rows(p->jobs[i])) && fits;
         if (fits)
             cells = std::min(cells, few);
     } else if (cells > lds_cells_cap(p->elem_bytes)) {

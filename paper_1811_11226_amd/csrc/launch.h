@@ -38,6 +38,8 @@ int32_t lds_cells_cap(int32_t elem_bytes);
 int32_t lds_cells_for(int32_t bound, int32_t elem_bytes);
 size_t lds_bytes_for(int32_t cells, int32_t elem_bytes);
 bool choose_subtile(FwdJob &J, const Tiling &TL, int32_t lds_cells);
+// Whether a run of 32 voxels along z keeps to a row of the input.
+bool keeps_rows(const FwdJob &J);
 // The footprint window of tiles of shape S (FwdJob::box_*, reach; box_e[0] = 0
 // where coordinates are too large for one): its LDS cells.
 int32_t set_window(FwdJob &J, const Tiling &S);

@@ -652,14 +652,26 @@ static bool box_exact(const FwdJob &J)
     return J.nx < (1 << 22) && J.ny < (1 << 22) && J.nz < (1 << 22);
 }
 
-// Sub-tile shape of job J for tile TL and an LDS reservation of lds_cells
-// cells (into J.sub and J.box_*): the whole tile when its window fits;
-// otherwise the sub-box of the tile with the most voxels (at least 2^9, or
-// the tile's own count if smaller; z extent >= 4) whose window fits, fewest
-// cells per voxel among equals; the whole tile and no window (direct gathers,
-// 2.4 times slower on a 512 x 512 x 320 scan) when none fits: false.  As tiles
-// hold at most 2^14 voxels, a tile has at most 32 sub-tiles (the kernels
-// compute one sub-tile's geometry per lane of a wave).
+bool keeps_rows(const FwdJob &J)
+{
+    return 31.0 * (std::fabs((double)J.M[2]) + std::fabs((double)J.M[6])) < 0.25;
+}
+
+// Whether the windows (set in J) of sub-tiles S of tiles TL are worth staging.  A voxel
+// reads 8 cells, so a window of many cells per voxel costs more than it shares.  Where z
+// runs keep to an input row (keeps_rows), gathers read whole lines, and win from 10 cells per voxel on
+// (512 x 512 x 320 int16 to 256 x 256 x 160: 81 us staged, 42 gathered; FP32 95 and 73; at 8
+// cells and a factor of 1.8 they take 0.9 to 1.2 times as long); and always where only
+// sub-tiles of 4 voxels along z fit (400 x 400 x 300 to 160 x 160 x 120 turned by 1 degree:
+// int16 89 and 45 us, FP32 136 and 63).
+static bool staging_pays(const FwdJob &J, const Tiling &S, const Tiling &TL)
+{
+    const double cells = (double)J.box_e[0] * J.box_e[1] * J.box_pitch;
+    const double voxels = (double)(1 << (S.lx + S.ly + S.lz));
+    const bool flat = S.lz == 2 && TL.lz > 2 && J.oz > 4;
+    return !(keeps_rows(J) && cells >= 10.0 * voxels) && !flat;
+}
+
 int32_t set_window(FwdJob &J, const Tiling &S)
 {
     const int32_t cells = set_box(J, S);
@@ -669,6 +681,14 @@ int32_t set_window(FwdJob &J, const Tiling &S)
     return cells;
 }
 
+// Sub-tile shape of job J for tile TL and an LDS reservation of lds_cells
+// cells (into J.sub and J.box_*): the whole tile when its window fits;
+// otherwise the sub-box of the tile with the most voxels (at least 2^9, or
+// the tile's own count if smaller; z extent >= 4) whose window fits, fewest
+// cells per voxel among equals; the whole tile and no window (direct gathers,
+// 2.4 times slower on a 512 x 512 x 320 scan) when none fits or staging it
+// does not pay: false.  As tiles hold at most 2^14 voxels, a tile has at most
+// 32 sub-tiles (the kernels compute one sub-tile's geometry per lane of a wave).
 bool choose_subtile(FwdJob &J, const Tiling &TL, int32_t lds_cells)
 {
     bool fits = true;
@@ -698,6 +718,11 @@ bool choose_subtile(FwdJob &J, const Tiling &TL, int32_t lds_cells)
             fits = best_log >= 0;
         }
         (void)set_box(J, best);
+        if (fits && !staging_pays(J, best, TL)) {
+            fits = false;
+            best = TL;
+            (void)set_box(J, best);
+        }
         set_reach(J, best);
         if (!fits)
             J.box_e[0] = 0;
@@ -958,21 +983,6 @@ static int32_t disp_cells(const FwdJob &J)
     return (int32_t)std::min(std::max(cells, (double)least), (double)kDispLdsCells);
 }
 
-// Whether the sub-tile windows of an affine job (choose_subtile) are worth staging.  A
-// voxel reads 8 cells, so a window of many cells per voxel costs more than it shares.
-// Where z runs keep to an input row, gathers read whole lines, and win from 10 cells per
-// voxel on (512 x 512 x 320 int16 to 256 x 256 x 160: 81 us staged, 42 gathered; FP32 95 and
-// 73; at 8 cells and a factor of 1.8 they take 0.9 to 1.2 times as long); and always where
-// only sub-tiles of 4 voxels along z fit (400 x 400 x 300 to 160 x 160 x 120 turned by 2
-// degrees: int16 100 and 55 us, FP32 141 and 78).
-static bool staging_pays(const FwdJob &J)
-{
-    const double cells = (double)J.box_e[0] * J.box_e[1] * J.box_pitch;
-    const double voxels = (double)(1 << (J.sub[0] + J.sub[1] + J.sub[2]));
-    const double rows = 31.0 * (std::fabs((double)J.M[2]) + std::fabs((double)J.M[6]));
-    return !(rows < 0.25 && cells >= 10.0 * voxels) && (J.sub[2] > 2 || J.oz <= 4);
-}
-
 // Tile of a single call whose windows fit no reservation and which gathers from memory
 // (no LDS: the 60 KB that held nothing left two workgroups per CU): 4 x 8 x 32 voxels.
 // Along z a tile reads whole lines of few rows where the map keeps to the rows (128 x 128 x
@@ -992,7 +1002,7 @@ hipError_t launch_warp_single(const FwdJob &J0, const Tiling &TL0, hipStream_t s
     Tiling TL = displaced ? kDispTiling : TL0;
     const int32_t bound = displaced ? disp_cells(Js) : footprint_cells_bound(Js, TL);
     int32_t cells = lds_cells_for(displaced ? bound : std::min(bound, kAffineLdsCells), esz);
-    const bool fits = choose_subtile(Js, TL, cells) && (displaced || staging_pays(Js));
+    const bool fits = choose_subtile(Js, TL, cells);
     if (!fits && !displaced) {         // gathers from memory
         const Tiling G = gather_tiling(Js);
         const int64_t tiles = (((int64_t)Js.ox + (1 << G.lx) - 1) >> G.lx) *
