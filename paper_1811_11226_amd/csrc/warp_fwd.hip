@@ -166,7 +166,7 @@ __device__ __forceinline__ void run_box(JobPtr Jp, const Box &B, int path, const
                     if (k == 1)
                         __builtin_amdgcn_sched_barrier(0);
                 }
-        } else if (DISP == kDispNone && path == kPathDirectInterior) {
+        } else if (path == kPathDirectInterior) {
             // the run's loads together: its voxels share lines, which would else be
             // fetched again
 #pragma unroll
@@ -304,7 +304,7 @@ __device__ __forceinline__ void fwd_tile_disp(JobPtr Jp, const Box &B0, const Ti
     const bool fits = (int64_t)e[0] * e[1] <= lds_cells && pitch <= lds_cells &&
                       e[0] * e[1] * pitch <= lds_cells && window24(lo[0], e[0]) &&
                       window24(lo[1], e[1]);
-    int path = outside ? kPathOutside : kPathDirectBoundary;
+    int path = outside ? kPathOutside : inside ? kPathDirectInterior : kPathDirectBoundary;
     if (!outside && fits && (sizeof(LT) == 4 || (J.flags & kFlagFillInT))) {
         path = inside ? kPathLdsInterior : kPathLdsBoundary;
         const Src S = make_src<T>(J);

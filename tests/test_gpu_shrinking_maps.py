@@ -35,3 +35,26 @@ def test_shrinking(nout, scale, turn, dtype):
         torch.cuda.synchronize()
         assert torch.equal(o2, out) and torch.equal(l2, lout), (tile, cells)
         plan.close()
+
+
+# Tiles past the reservation inside the volume (their cells gathered without tests), over
+# its faces, and outside it.
+@pytest.mark.parametrize("nout", [(33, 31, 40), (16, 17, 19)])
+@pytest.mark.parametrize("scale,std", [(3.0, 1.0), (4.5, 6.0), (0.9, 25.0)])
+@pytest.mark.parametrize("dtype", [np.float32, np.int16])
+def test_displaced(nout, scale, std, dtype):
+    nin = tuple(int(v * max(scale, 2.0)) + 1 for v in nout)
+    rng = np.random.default_rng(sum(nin))
+    img = rng.integers(-1000, 2000, nin).astype(dtype)
+    lbl = rng.integers(1, 6, nin).astype(np.int8)
+    M = _map(scale * _rot(0.1, -0.2, 0.15), nin, nout)
+    ctrl = rng.normal(0, std, (3, 6, 5, 7)).astype(np.float32)
+    u = oracle.bspline_upsample_f32(ctrl, nout)
+    ref, lref = oracle.warp(img, M, nout, lbl=lbl, disp=u, fill=-1000.0, label_fill=-3)
+    t = lambda a: torch.from_numpy(a).cuda()  # noqa: E731
+    for out, lout in (ctaug.warp_displacement(t(img), M, t(u), lbl=t(lbl), fill=-1000.0,
+                                              label_fill=-3),
+                      ctaug.warp_bspline(t(img), M, t(ctrl), lbl=t(lbl), fill=-1000.0,
+                                         label_fill=-3, out_dim=nout)):
+        assert np.array_equal(lout.cpu().numpy(), lref)
+        assert np.all(np.abs(out.cpu().numpy() - ref) <= 1e-5 * np.maximum(np.abs(ref), 1000.0))
