@@ -528,8 +528,11 @@ ctaug_status ctaug_batch_plan_replay(ctaug_batch_plan *plan, void *stream);
  * `reps` launches each, after one warm-up) and keep the fastest in the plan
  * and in the autotune cache (under this device and the plan's batch class).
  * The jobs' outputs are overwritten (with identical results).  Synchronises
- * `stream`.  best (host, may be NULL) receives the choice; times_ms (host
- * float[n_cand], may be NULL) the mean time per launch of each candidate. */
+ * `stream`.  best (host, may be NULL) receives the choice as the plan holds it
+ * (ctaug_batch_plan_get_tuning: a reservation of 0 cells by its size); the cache
+ * keeps the candidate, so that later plans size theirs from their own jobs.
+ * times_ms (host float[n_cand], may be NULL): the mean time per launch of each
+ * candidate. */
 ctaug_status ctaug_batch_plan_autotune(ctaug_batch_plan *plan, const ctaug_tuning *cand,
                                        int32_t n_cand, int32_t reps, void *stream,
                                        ctaug_tuning *best, float *times_ms);
@@ -546,12 +549,13 @@ ctaug_status ctaug_batch_plan_destroy(ctaug_batch_plan *plan);
  * draws noise.
  *
  * lookup: *found = 1 and *out = the entry for these jobs on the current
- * device, else *found = 0 (jobs validated as by ctaug_batch_plan_create;
- * ENODEV without a device).  save: write every entry as text to path (a
- * header line, then one line per entry).  load: read such a file and merge
- * its entries (replacing equal keys); *n_entries (may be NULL) receives the
- * count; a malformed file (bad header, field count or launch shape) merges
- * nothing and returns EINVAL.  clear: drop every entry.  Host only. */
+ * device, as a plan of them would hold it, else *found = 0 (jobs validated as
+ * by ctaug_batch_plan_create; ENODEV without a device).  save: write every
+ * entry as text to path (a header line, then one line per entry).  load: read
+ * such a file and merge its entries (replacing equal keys); *n_entries (may be
+ * NULL) receives the count; a malformed file (bad header, field count or launch
+ * shape) merges nothing and returns EINVAL.  clear: drop every entry.  Host
+ * only. */
 ctaug_status ctaug_autotune_cache_lookup(const ctaug_job *jobs, int32_t n_jobs, ctaug_tuning *out,
                                          int32_t *found);
 ctaug_status ctaug_autotune_cache_save(const char *path);

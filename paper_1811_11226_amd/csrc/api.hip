@@ -1028,6 +1028,54 @@ void destroy_graph(ctaug_batch_plan *p)
     }
 }
 
+// The launch shape that jobs take under tuning t, as a plan holds and reports it: a
+// reservation of 0 cells sized from the jobs' footprints, the displacement tile for
+// B-spline jobs.  Leaves the jobs' tiles and flags set for it.
+ctaug_status resolve_tuning(std::vector<FwdJob> &jobs, bool spline, bool all_i16,
+                            const ctaug_tuning &t, ctaug_tuning &out, Tiling &TL,
+                            int32_t &elem_bytes)
+{
+    const ctaug_status st = tiling_of(&t, TL);
+    if (st != CTAUG_OK)
+        return st;
+    if (spline)                         // B-spline jobs: displacement tiles, FP32 cells
+        TL = kDispTiling;
+    elem_bytes = (t.lds_format == 1 && all_i16 && !spline) ? 2 : 4;
+    for (FwdJob &J : jobs) {
+        set_tiles(J, TL);
+        if (elem_bytes == 2)
+            J.flags |= kFlagLds16;
+        else
+            J.flags &= ~kFlagLds16;
+    }
+    out = t;
+    if (spline) {
+        out.lds_cells = lds_cells_for(kDispLdsCells, 4);
+        out.tile[0] = 1 << TL.lx;
+        out.tile[1] = 1 << TL.ly;
+        out.tile[2] = 1 << TL.lz;
+        out.lds_format = 0;
+    } else if (t.lds_cells == 0) {
+        // the largest footprint of the current jobs, with headroom for later
+        // updates, up to kAffineLdsCells unless a job needs more; tiles that
+        // still exceed it are staged as sub-tiles, or gather
+        int64_t need = 0;
+        for (const FwdJob &J : jobs)
+            need = std::max<int64_t>(need, footprint_cells_bound(J, TL));
+        need = std::min<int64_t>(need + need / 4 + 64, 1 << 20);
+        out.lds_cells = lds_cells_for((int32_t)need, elem_bytes);
+        const int32_t few = kAffineLdsCells * 4 / elem_bytes;
+        bool fits = true;
+        for (FwdJob &J : jobs)          // (gathers along rows take all workgroups they get)
+            fits = (choose_subtile(J, TL, few) || keeps_rows(J)) && fits;
+        if (fits)
+            out.lds_cells = std::min(out.lds_cells, few);
+    } else if (t.lds_cells > lds_cells_cap(elem_bytes)) {
+        return CTAUG_EINVAL;
+    }
+    return CTAUG_OK;
+}
+
 // Recompute tile counts / prefix sums / grid for the plan's tiling and upload
 // the prefix and job tables (synchronous: only at creation and retuning).
 // Both uploads wait for the plan's last launch, run or replay first, so that
@@ -1037,47 +1085,21 @@ void destroy_graph(ctaug_batch_plan *p)
 ctaug_status apply_tiling(ctaug_batch_plan *p, const ctaug_tuning &t)
 {
     Tiling TL;
-    ctaug_status st = tiling_of(&t, TL);
+    ctaug_tuning tune;
+    const ctaug_status st = resolve_tuning(p->jobs, p->spline, p->all_i16, t, tune, TL,
+                                           p->elem_bytes);
     if (st != CTAUG_OK)
         return st;
-    if (p->spline)                      // B-spline jobs: displacement tiles, FP32 cells
-        TL = kDispTiling;
     std::vector<int32_t> prefix(p->n + 1, 0);
     int64_t total = 0;
-    p->elem_bytes = (t.lds_format == 1 && p->all_i16 && !p->spline) ? 2 : 4;
     for (int i = 0; i < p->n; ++i) {
-        set_tiles(p->jobs[i], TL);
-        if (p->elem_bytes == 2)
-            p->jobs[i].flags |= kFlagLds16;
-        else
-            p->jobs[i].flags &= ~kFlagLds16;
         prefix[i] = (int32_t)total;
         total += (int64_t)p->jobs[i].tiles_x * p->jobs[i].tiles_y * p->jobs[i].tiles_z;
     }
     if (total > (int64_t)kMaxElems)
         return CTAUG_ESHAPE;
     prefix[p->n] = (int32_t)total;
-    int32_t cells = t.lds_cells < 0 ? 0 : t.lds_cells;
-    if (p->spline) {
-        cells = lds_cells_for(kDispLdsCells, 4);
-    } else if (t.lds_cells == 0) {
-        // the largest footprint of the current jobs, with headroom for later
-        // updates, up to kAffineLdsCells unless a job needs more; tiles that
-        // still exceed it are staged as sub-tiles, or gather
-        int64_t need = 0;
-        for (int i = 0; i < p->n; ++i)
-            need = std::max<int64_t>(need, footprint_cells_bound(p->jobs[i], TL));
-        need = std::min<int64_t>(need + need / 4 + 64, 1 << 20);
-        cells = lds_cells_for((int32_t)need, p->elem_bytes);
-        const int32_t few = kAffineLdsCells * 4 / p->elem_bytes;
-        bool fits = true;
-        for (int i = 0; i < p->n; ++i)     // (gathers along rows take all workgroups they get)
-            fits = (choose_subtile(p->jobs[i], TL, few) || keeps_rows(p->jobs[i])) && fits;
-        if (fits)
-            cells = std::min(cells, few);
-    } else if (cells > lds_cells_cap(p->elem_bytes)) {
-        return CTAUG_EINVAL;
-    }
+    const int32_t cells = std::max(tune.lds_cells, 0);
     for (int i = 0; i < p->n; ++i)
         (void)choose_subtile(p->jobs[i], TL, cells);
     if (p->upload_recorded && hipEventSynchronize(p->upload_done) != hipSuccess)
@@ -1089,14 +1111,7 @@ ctaug_status apply_tiling(ctaug_batch_plan *p, const ctaug_tuning &t)
             hipSuccess)
         return CTAUG_EHIP;
     p->TL = TL;
-    p->tune = t;
-    p->tune.lds_cells = t.lds_cells < 0 && !p->spline ? -1 : cells;
-    if (p->spline) {
-        p->tune.tile[0] = 1 << TL.lx;
-        p->tune.tile[1] = 1 << TL.ly;
-        p->tune.tile[2] = 1 << TL.lz;
-        p->tune.lds_format = 0;
-    }
+    p->tune = tune;
     p->lds_cells = cells;
     p->total = (int32_t)total;
     ++p->generation;                    // descriptors prepared for the old tiling are stale
@@ -1309,7 +1324,18 @@ extern "C" ctaug_status ctaug_autotune_cache_lookup(const ctaug_job *jobs, int32
     int cus = 0;
     if (!device_id(arch, cus))
         return CTAUG_ENODEV;
-    *found = cache_find(tune_key(arch, cus, js, jobs[0].ctrl != nullptr), *out) ? 1 : 0;
+    const bool spline = jobs[0].ctrl != nullptr;
+    ctaug_tuning t;
+    *found = cache_find(tune_key(arch, cus, js, spline), t) ? 1 : 0;
+    if (!*found)
+        return CTAUG_OK;
+    bool all_i16 = true;
+    for (const FwdJob &J : js)
+        all_i16 = all_i16 && J.dtype == kI16;
+    Tiling TL;
+    int32_t elem_bytes;
+    if (resolve_tuning(js, spline, all_i16, t, *out, TL, elem_bytes) != CTAUG_OK)
+        *out = t;                      // a loaded entry that no plan takes, as it was loaded
     return CTAUG_OK;
 }
 
@@ -1641,9 +1667,9 @@ extern "C" ctaug_status ctaug_batch_plan_autotune(ctaug_batch_plan *p, const cta
     st = apply_tiling(p, cand[best_i]);
     if (st != CTAUG_OK)
         return st;
-    // the choice as the plan now holds it (a reservation of 0 cells, sized from the
-    // jobs, by its size), so that the cache, *best and the plan agree
-    cache_put(tune_key(p->arch, p->num_cu, p->jobs, p->spline), p->tune);
+    // the candidate as it was given: a reservation of 0 cells is sized from the jobs of
+    // each plan that takes it
+    cache_put(tune_key(p->arch, p->num_cu, p->jobs, p->spline), cand[best_i]);
     if (best)
         *best = p->tune;
     return CTAUG_OK;
