@@ -29,7 +29,6 @@ __device__ __host__ __forceinline__ int lds_pitch(int e)
 
 // A footprint window, uniform over the workgroup.
 struct TileGeom {
-    int cls;                           // kOutside / kInterior / kBoundary
     int lo[3], e[3];                   // input cells [lo, lo + e)
     int quads;                         // 4-cell quads staged per row: ceil(e[2] / 4)
     int pitch;                         // LDS row pitch: 4 * quads, padded to 4 mod 8 cells
@@ -77,10 +76,6 @@ __device__ __forceinline__ void copy_quad(rsrc_t r, uint32_t off, float *dst, in
 template <typename T> struct QuadRaw;
 template <> struct QuadRaw<float> {
     typedef u32x4 type;
-    static __device__ __forceinline__ type load(rsrc_t r, uint32_t e)
-    {
-        return __builtin_amdgcn_raw_buffer_load_b128(r, e * 4u, 0, 0);
-    }
     // at byte offset off + base (base uniform)
     static __device__ __forceinline__ type load_at(rsrc_t r, uint32_t off, uint32_t base)
     {
@@ -99,10 +94,6 @@ template <> struct QuadRaw<float> {
 };
 template <> struct QuadRaw<int16_t> {
     typedef u32x2 type;
-    static __device__ __forceinline__ type load(rsrc_t r, uint32_t e)
-    {
-        return __builtin_amdgcn_raw_buffer_load_b64(r, e * 2u, 0, 0);
-    }
     static __device__ __forceinline__ type load_at(rsrc_t r, uint32_t off, uint32_t base)
     {
         return __builtin_amdgcn_raw_buffer_load_b64(r, off, base, 0);
@@ -218,19 +209,15 @@ struct RowWalk {
 
 // Copy the tile's input image footprint into LDS in the LDS cell type, with
 // fill in cells outside the volume (labels are gathered from global memory
-// while sampling, so that the LDS holds image cells only).  The footprint is
-// e[0] x e[1] rows of `quads` quads of 4 cells (row pitch G.pitch cells).
-// A row of at most 16 quads is taken by `quads` consecutive lanes, one quad
-// each, so a workgroup covers floor(256 / quads) rows per pass with every lane
-// but the last 256 mod quads busy; a longer row is taken by 16 lanes (a lane
-// takes quads q, q + 16, ...).  Rows advance by additions (RowWalk), with no
-// per-quad division or multiplication.  An interior footprint (every quad
-// inside the volume, see box_geom) of at most 16 quads per row is copied
-// without any test: each lane issues the loads of four rows before it
-// converts and writes them.  Other footprints test each row and quad: rows
-// outside the volume are filled without loads, quads crossing its z ends
-// load per cell from clamped indices.
-template <typename T, typename LT, int NT = kThreads>
+// while sampling, so that the LDS holds image cells only): windows that
+// stage_window does not take, of volumes of fewer than 4 cells along z or rows of
+// more quads than a workgroup has threads.  The footprint is e[0] x e[1] rows of
+// `quads` quads of 4 cells (row pitch G.pitch cells).  A row of at most 16 quads
+// is taken by `quads` consecutive lanes, one quad each; a longer row by 16 lanes (a
+// lane takes quads q, q + 16, ...).  Rows advance by additions (RowWalk).  Rows
+// outside the volume are filled without loads, quads crossing its z ends load
+// per cell from clamped indices.
+template <typename T, typename LT>
 __device__ __forceinline__ void stage_footprint(const FwdJob &J, const Src &S, const TileGeom &G,
                                                 LT *s_img)
 {
@@ -241,47 +228,16 @@ __device__ __forceinline__ void stage_footprint(const FwdJob &J, const Src &S, c
         // last whole row stay idle (ql = qpr)
         lpr = qpr;
         row0 = div_small(threadIdx.x, qpr, rcp_small(qpr));
-        rpp = NT / qpr;
+        rpp = kThreads / qpr;
         ql = row0 < rpp ? threadIdx.x - row0 * qpr : qpr;
     } else {
         lpr = 16;
         row0 = threadIdx.x >> 4;
-        rpp = NT >> 4;
+        rpp = kThreads >> 4;
         ql = threadIdx.x & 15;
     }
     RowWalk W;
     W.init(S, G, row0, rpp, 4 * min(ql, qpr - 1));
-    const bool fast = G.cls == kInterior && G.lo[2] >= 0 && G.lo[2] + 4 * qpr <= J.nz &&
-                      qpr <= 16;
-    if (fast) {
-        if (ql >= qpr)
-            return;                    // lanes past the last whole row stay idle
-        const int gz0 = G.lo[2] + 4 * ql;
-        constexpr int B = 4;           // rows whose loads are in flight together
-        for (; W.row < rows;) {
-            uint32_t e[B];
-            int l[B];
-            bool ok[B];
-#pragma unroll
-            for (int u = 0; u < B; ++u) {
-                ok[u] = W.row < rows;
-                e[u] = (uint32_t)(W.e_row + gz0);
-                l[u] = W.l_row;
-                W.next();
-            }
-            typename QuadRaw<T>::type w[B];
-#pragma unroll
-            for (int u = 0; u < B; ++u)
-                w[u] = QuadRaw<T>::load(S.img, ok[u] ? e[u] : e[0]);   // in the volume either way
-#pragma unroll
-            for (int u = 0; u < B; ++u) {
-                if (!ok[u])
-                    break;
-                QuadRaw<T>::store(w[u], s_img + l[u]);
-            }
-        }
-        return;
-    }
     for (; W.row < rows; W.next()) {
         const int gx = G.lo[0] + W.cx, gy = G.lo[1] + W.cy;
         const bool row_in = (unsigned)gx < (unsigned)J.nx && (unsigned)gy < (unsigned)J.ny;

@@ -558,7 +558,6 @@ __device__ __forceinline__ void bwd_tile(JobPtr Jp, int t, bool want_ctrl, bool 
                 }
                 G.quads = quads;
                 G.pitch = pitch;
-                G.cls = kBoundary;
                 stage_footprint<T, float>(J, S, G, s_cells);
             }
             __syncthreads();

@@ -31,10 +31,6 @@
 
 namespace ctaug {
 
-// Workgroup size: affine tiles, displacement tiles (one run per thread).
-constexpr int kAffineThreads = 256;
-template <int DISP> constexpr int kFwdThreads = DISP == kDispNone ? kAffineThreads : kThreads;
-
 enum : int { kPathOutside, kPathLdsInterior, kPathLdsBoundary, kPathDirectInterior,
              kPathDirectBoundary };
 
@@ -80,7 +76,7 @@ __device__ __forceinline__ void run_box(JobPtr Jp, const Box &B, int path, const
     const int8_t lfill = (int8_t)J.label_fill;
     const bool labels = (J.flags & kFlagLabels) != 0;
 
-    for (int r = threadIdx.x; r < nruns; r += kFwdThreads<DISP>) {
+    for (int r = threadIdx.x; r < nruns; r += kThreads) {
         if (DISP != kDispNone && r != (int)threadIdx.x)
             break;
         const int zr = r & ((1 << runs_z_log) - 1);
@@ -305,7 +301,7 @@ __device__ __forceinline__ void fwd_tile_disp(JobPtr Jp, const Box &B0, const Ti
                       e[0] * e[1] * pitch <= lds_cells && window24(lo[0], e[0]) &&
                       window24(lo[1], e[1]);
     int path = outside ? kPathOutside : inside ? kPathDirectInterior : kPathDirectBoundary;
-    if (!outside && fits && (sizeof(LT) == 4 || (J.flags & kFlagFillInT))) {
+    if (!outside && fits) {
         path = inside ? kPathLdsInterior : kPathLdsBoundary;
         const Src S = make_src<T>(J);
         // whole quads inside the volume: the window of an inside tile may start earlier
@@ -324,7 +320,6 @@ __device__ __forceinline__ void fwd_tile_disp(JobPtr Jp, const Box &B0, const Ti
             }
             G.quads = quads;
             G.pitch = pitch;
-            G.cls = kBoundary;
             stage_footprint<T, LT>(J, S, G, reinterpret_cast<LT *>(s_lds));
         }
         B.sy = pitch * (int)sizeof(LT);
@@ -372,7 +367,7 @@ __device__ __forceinline__ void fwd_tile_affine(JobPtr Jp, const Box &B0, const 
         todo = (uint32_t)__ballot(lane < nsub && bx <= B0.x1 && by <= B0.y1 && bz <= B0.z1);
         W.passes = 0;
         if (e[0] != 0 && __any(cls != kOutside)) {
-            W = stage_walk<kAffineThreads>(e[0] * e[1], e[1], quads, (int)threadIdx.x);
+            W = stage_walk<kThreads>(e[0] * e[1], e[1], quads, (int)threadIdx.x);
             fast = W.passes > 0 && J.nz >= 4;
         }
     }
@@ -421,8 +416,7 @@ __device__ __forceinline__ void fwd_tile_affine(JobPtr Jp, const Box &B0, const 
                 }
                 G.quads = (G.e[2] + 3) >> 2;
                 G.pitch = pitch;
-                G.cls = c;
-                stage_footprint<T, LT, kAffineThreads>(J, S, G, reinterpret_cast<LT *>(s_lds));
+                stage_footprint<T, LT>(J, S, G, reinterpret_cast<LT *>(s_lds));
             }
             __syncthreads();
             used = true;
@@ -473,7 +467,7 @@ extern __shared__ __attribute__((aligned(16))) uint8_t s_footprint[];
 
 // Single job, job in kernel arguments, one workgroup per tile.
 template <typename T, bool ALIGNED, int DISP>
-__global__ __launch_bounds__(kFwdThreads<DISP>) void k_warp_single(FwdJob J, Tiling TL, int32_t ntiles,
+__global__ __launch_bounds__(kThreads) void k_warp_single(FwdJob J, Tiling TL, int32_t ntiles,
                                                           int32_t lds_cells)
 {
     const int b = blockIdx.x;
@@ -507,13 +501,8 @@ __device__ __forceinline__ int job_of(const int32_t *__restrict__ prefix, int nj
 // (xcd_tile; persistent when gridDim.x is a few per CU).  MODE fixes
 // the input and LDS cell types when every job shares them (fewer code paths
 // in the kernel, less register pressure); kBatchMixed dispatches per job.
-constexpr int batch_threads(int mode)
-{
-    return mode == kBatchSplineI16 || mode == kBatchSplineF32 || mode == kBatchSplineMixed
-               ? kThreads : kAffineThreads;
-}
 template <bool ALIGNED, int MODE>
-__global__ __launch_bounds__(batch_threads(MODE)) void k_warp_batch(const FwdJob *__restrict__ jobs,
+__global__ __launch_bounds__(kThreads) void k_warp_batch(const FwdJob *__restrict__ jobs,
                                                          const int32_t *__restrict__ prefix,
                                                          int32_t njobs, Tiling TL,
                                                          int32_t lds_cells)
@@ -754,17 +743,17 @@ static void launch_single_t(const FwdJob &J, const Tiling &TL, int ntiles, int32
 {
     if (J.dtype == kI16) {
         if (aligned)
-            hipLaunchKernelGGL((k_warp_single<int16_t, true, DISP>), dim3(grid), dim3(kFwdThreads<DISP>), lds,
+            hipLaunchKernelGGL((k_warp_single<int16_t, true, DISP>), dim3(grid), dim3(kThreads), lds,
                                s, J, TL, ntiles, cells);
         else
-            hipLaunchKernelGGL((k_warp_single<int16_t, false, DISP>), dim3(grid), dim3(kFwdThreads<DISP>),
+            hipLaunchKernelGGL((k_warp_single<int16_t, false, DISP>), dim3(grid), dim3(kThreads),
                                lds, s, J, TL, ntiles, cells);
     } else {
         if (aligned)
-            hipLaunchKernelGGL((k_warp_single<float, true, DISP>), dim3(grid), dim3(kFwdThreads<DISP>), lds,
+            hipLaunchKernelGGL((k_warp_single<float, true, DISP>), dim3(grid), dim3(kThreads), lds,
                                s, J, TL, ntiles, cells);
         else
-            hipLaunchKernelGGL((k_warp_single<float, false, DISP>), dim3(grid), dim3(kFwdThreads<DISP>), lds,
+            hipLaunchKernelGGL((k_warp_single<float, false, DISP>), dim3(grid), dim3(kThreads), lds,
                                s, J, TL, ntiles, cells);
     }
 }
@@ -1041,31 +1030,31 @@ static void launch_batch_mode(int mode, const FwdJob *jobs_dev, const int32_t *p
 {
     switch (mode) {
     case kBatchI16F32:
-        hipLaunchKernelGGL((k_warp_batch<ALIGNED, kBatchI16F32>), dim3(grid), dim3(batch_threads(mode)), lds,
+        hipLaunchKernelGGL((k_warp_batch<ALIGNED, kBatchI16F32>), dim3(grid), dim3(kThreads), lds,
                            s, jobs_dev, prefix_dev, njobs, TL, lds_cells);
         break;
     case kBatchI16I16:
-        hipLaunchKernelGGL((k_warp_batch<ALIGNED, kBatchI16I16>), dim3(grid), dim3(batch_threads(mode)), lds,
+        hipLaunchKernelGGL((k_warp_batch<ALIGNED, kBatchI16I16>), dim3(grid), dim3(kThreads), lds,
                            s, jobs_dev, prefix_dev, njobs, TL, lds_cells);
         break;
     case kBatchF32:
-        hipLaunchKernelGGL((k_warp_batch<ALIGNED, kBatchF32>), dim3(grid), dim3(batch_threads(mode)), lds, s,
+        hipLaunchKernelGGL((k_warp_batch<ALIGNED, kBatchF32>), dim3(grid), dim3(kThreads), lds, s,
                            jobs_dev, prefix_dev, njobs, TL, lds_cells);
         break;
     case kBatchSplineI16:
-        hipLaunchKernelGGL((k_warp_batch<ALIGNED, kBatchSplineI16>), dim3(grid), dim3(batch_threads(mode)),
+        hipLaunchKernelGGL((k_warp_batch<ALIGNED, kBatchSplineI16>), dim3(grid), dim3(kThreads),
                            lds, s, jobs_dev, prefix_dev, njobs, TL, lds_cells);
         break;
     case kBatchSplineF32:
-        hipLaunchKernelGGL((k_warp_batch<ALIGNED, kBatchSplineF32>), dim3(grid), dim3(batch_threads(mode)),
+        hipLaunchKernelGGL((k_warp_batch<ALIGNED, kBatchSplineF32>), dim3(grid), dim3(kThreads),
                            lds, s, jobs_dev, prefix_dev, njobs, TL, lds_cells);
         break;
     case kBatchSplineMixed:
-        hipLaunchKernelGGL((k_warp_batch<ALIGNED, kBatchSplineMixed>), dim3(grid), dim3(batch_threads(mode)),
+        hipLaunchKernelGGL((k_warp_batch<ALIGNED, kBatchSplineMixed>), dim3(grid), dim3(kThreads),
                            lds, s, jobs_dev, prefix_dev, njobs, TL, lds_cells);
         break;
     default:
-        hipLaunchKernelGGL((k_warp_batch<ALIGNED, kBatchMixed>), dim3(grid), dim3(batch_threads(mode)), lds,
+        hipLaunchKernelGGL((k_warp_batch<ALIGNED, kBatchMixed>), dim3(grid), dim3(kThreads), lds,
                            s, jobs_dev, prefix_dev, njobs, TL, lds_cells);
     }
 }
