@@ -507,11 +507,11 @@ ctaug_status ctaug_batch_plan_update_prepared(ctaug_batch_plan *plan,
 ctaug_status ctaug_batch_jobs_destroy(ctaug_batch_jobs *jobs);
 
 /* Enqueue: upload the job table (async copy from pinned staging) and run one
- * persistent launch that warps every job.  Results equal ctaug_warp_affine
+ * launch that warps every job.  Results equal ctaug_warp_affine
  * (ctaug_warp_bspline) on each job, bit for bit. */
 ctaug_status ctaug_batch_plan_launch(ctaug_batch_plan *plan, void *stream);
 
-/* Enqueue only the persistent launch, reading the job table uploaded by the
+/* Enqueue only the launch, reading the job table uploaded by the
  * last launch, replay or autotune (no upload): re-runs the same descriptors,
  * e.g. after the caller refilled the same input buffers in place.  EINVAL
  * before the first launch or replay. */

@@ -2,7 +2,7 @@
 
 C ABI: include/ctaug.h, implemented by libctaug.so (HIP kernels in csrc/).
 Python: `ops` (one function per C entry point), `autograd` (differentiable
-warps), `BatchPlan` (persistent batched launch with HIP graph and autotuner).
+warps), `BatchPlan` (batched launch with HIP graph and autotuner).
 """
 from . import ops
 from .ops import (BatchPlan, Pipeline, affine_matrix, autotune_cache_clear, autotune_cache_load,

@@ -90,8 +90,8 @@ __global__ __launch_bounds__(kThreads) void k_bspline_up(const float *__restrict
 // each a part of every 64 rows, added in a fixed order at the end).  The weights
 // come from LDS tables of the cell and the four weights of a position.  A row
 // with a non-finite value is summed over its nonzero weights alone, as 0 times it
-// would reach every control.  117 x 130 x 151, 8^3 controls: 77 us with one
-// thread per row and per entry (z 47, y 30), now 17.
+// would reach every control.  117 x 130 x 151, 8^3 controls, under the profiler: 31 us,
+// where the two passes with one thread per row and per entry take 77 (z 47, y 30).
 constexpr int kAdjRows = 64;           // rows of a chunk: 16 per wave
 constexpr int kAdjSeg = 512;           // voxels along z whose weights are in LDS at once
 constexpr int kAdjGridX = 65536;       // planes in the grid's first dimension (2^32 threads at most)
@@ -243,8 +243,8 @@ __global__ __launch_bounds__(kThreads) void k_bspline_adj_plane(const float *__r
 }
 
 // The same sums in two passes over memory, where a plane has too many rows or controls for
-// one workgroup (bspline_adj_by_planes).  z: T1[comp][x][y][gz] = sum_z B_{gz - iz(z)}(t(z)) g[comp][x][y][z],
-// one thread per (comp, x, y) row streaming z with 16-byte loads when the
+// one workgroup (bspline_adj_by_planes).  z: T1[comp][x][y][gz] = sum_z B_{gz - iz(z)}(t(z))
+// g[comp][x][y][z], one thread per (comp, x, y) row streaming z with 16-byte loads when the
 // rows are aligned.  The z-cell index is nondecreasing along the row, so the
 // four controls a voxel touches slide as a window of four FP32 accumulators;
 // each control's sum is stored once, when the window moves past it.

@@ -55,13 +55,14 @@ struct Box {
 //
 // What bounds the affine warps is shared between the vector memory path (lines of
 // footprint and labels fetched through L1: without the staging loads the
-// 16-volume batch takes 170 us of 241, without the label gathers 198, without the
-// stores 198) and VALU issue (57 % busy; 158 instructions per voxel before,
-// 134 now), so the per-voxel chain is kept short: floor and fraction are one instruction each where q >= 0 (v_cvt_flr_i32_f32,
-// v_fract_f32 equals q - floor(q) there), the LDS byte address three (24-bit
-// multiply-adds on strides that are the job's, one origin per box), and the
-// samples of a boundary box cost the same as an interior one's plus the clamp
-// above (fill cells are staged).
+// 16-volume batch took 170 us of 241, without the label gathers 198, without the
+// stores 198) and VALU issue (72 % of the CUs' busy cycles there, 148 instructions
+// per voxel; 76 % and 133 for a 512 x 512 x 320 scan), so the per-voxel chain is
+// kept short: floor and fraction are one instruction each where q >= 0
+// (v_cvt_flr_i32_f32, v_fract_f32 equals q - floor(q) there), the LDS byte address
+// three (24-bit multiply-adds on strides that are the job's, one origin per box),
+// and the samples of a boundary box cost the same as an interior one's plus the
+// clamp above (fill cells are staged).
 //
 // INNER: tiles of a displacement inside the volume that are gathered sample without tests
 // (1.3 to 1.5 times faster on maps that shrink to a third).  That path costs a warp whose
@@ -505,7 +506,7 @@ __device__ __forceinline__ int job_of(const int32_t *__restrict__ prefix, int nj
 
 // Batch of jobs from a device table.  prefix[j] = first global tile of job j,
 // prefix[njobs] = total.  Workgroups stride over the tiles of their XCD
-// (xcd_tile; persistent when gridDim.x is a few per CU).  MODE fixes
+// (xcd_tile): one tile each, or several when a tuning asks for a few workgroups per CU.  MODE fixes
 // the input and LDS cell types when every job shares them (fewer code paths
 // in the kernel, less register pressure); kBatchMixed dispatches per job.
 template <bool ALIGNED, int MODE>
@@ -599,8 +600,9 @@ static int32_t set_box(FwdJob &J, const Tiling &S)
 // lies in (c - 1, c + 1) per axis, a quad c .. c + 3 along z when it lies in (c -
 // 1, c + 4); so p lies in A^-1 of that block, along output axis k within sum_j
 // |A^-1_kj| r_j of its centre (r = 1, 1, 2.5).  The slack takes the rounding of
-// q and of the kernel's FP32 test, whose terms stay under 2^11 for the inverses
-// admitted here; other maps copy every quad.
+// q and of the kernel's FP32 test: with |A^-1| <= 8 and windows of at most 30704 cells,
+// no axis longer than 3412 of them, its terms stay under 2^14, and five roundings of
+// them under 2^-7; other maps copy every quad.
 static void set_reach(FwdJob &J, const Tiling &S)
 {
     const int t[3] = {1 << S.lx, 1 << S.ly, 1 << S.lz};
@@ -655,8 +657,8 @@ bool keeps_rows(const FwdJob &J)
 
 // Whether the windows (set in J) of sub-tiles S of tiles TL are worth staging.  A voxel
 // reads 8 cells, so a window of many cells per voxel costs more than it shares.  Where z
-// runs keep to an input row (keeps_rows), gathers read whole lines, and win from 10 cells per voxel on
-// (512 x 512 x 320 int16 to 256 x 256 x 160: 81 us staged, 42 gathered; FP32 95 and 73; at 8
+// runs keep to an input row (keeps_rows), gathers read whole lines, and win from 10 cells
+// per voxel on (512 x 512 x 320 int16 to 256 x 256 x 160: 81 us staged, 42 gathered; FP32 95 and 73; at 8
 // cells and a factor of 1.8 they take 0.9 to 1.2 times as long); and always where only
 // sub-tiles of 4 voxels along z fit (400 x 400 x 300 to 160 x 160 x 120 turned by 1 degree:
 // int16 89 and 45 us, FP32 136 and 63).
@@ -823,9 +825,9 @@ __global__ __launch_bounds__(kThreads) void k_warp_labels(FwdJob J, int32_t runs
 // V voxels each, 64 / L rows at once (SUB: two or more; rows past 64 V voxels in
 // segments).  A row costs one store per lane, and V byte gathers, which a wave
 // with one row at a time skips where its input row is the last one's; four rows'
-// gathers are in flight together (one at a time a small map waits for each: 31
-// us where the general kernel took 24).  What is left is the output's own traffic: 512 x 512
-// x 320 from 160 x 160 x 100 takes 30 us, 103 with the general kernel.
+// gathers are in flight together (one at a time a small map waits for each: 31 us
+// where the general kernel took 24).  What is left is the output's own traffic:
+// 512 x 512 x 320 from 160 x 160 x 100 takes 30 us, 103 with the general kernel.
 // Coordinates are those of row_base and coord (the products with 0 add nothing),
 // nearest voxels and the guard those of label_checked.
 template <int V, bool SUB>

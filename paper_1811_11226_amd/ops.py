@@ -439,7 +439,7 @@ def _job_array(jobs):
 
 
 class BatchPlan:
-    """One persistent launch over a batch of jobs (device job table, pinned
+    """One launch over a batch of jobs (device job table, pinned
     staging, optional HIP graph, autotuned launch shape)."""
 
     def __init__(self, jobs, tile=None, wg_per_cu=0, lds_cells=0, lds_format=0):
